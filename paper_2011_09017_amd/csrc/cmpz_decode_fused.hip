@@ -554,28 +554,41 @@ bool plan_decode_fused(TensorD *t, uint32_t sub)
 
 // One launch over the tensors of the group that have a plan (and a second one, of the variant
 // that shares planes between waves, over those with few large planes).  Five workgroups are
-// resident per compute unit.  A small call gets one round of them (a second round would build its
-// decode tables for little work); a large one up to six rounds, dealt to the tensors in proportion
+// resident per compute unit.  A small launch gets one round of them (a second round would build its
+// decode tables for little work); a large one up to six rounds, dealt to its tensors in proportion
 // to their elements, so that workgroups of different cost (small planes cost more per element than
 // large ones) even out and the chip does not idle while the last round's slowest workgroup
 // finishes.  Measured on the ResNet-18-shaped stream (17 tensors, 591 M elements): 1.00 / 0.96 /
 // 0.93 / 0.94 / 0.94 / 0.94 ms for 3 / 4 / 5 / 6 / 8 / 12 rounds.  No more than a tensor has items
-// for, at least one.
+// for, at least one.  The two launches run one after the other: each deals its own rounds (dealt
+// from a common count, the 4096 shared planes of that stream at batch 64 got 448 workgroups of the
+// 1280 that fit and took 366 us, with 1280 about 240; as plain items of the other launch about 150).
 void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st)
 {
-    uint64_t total = 0;
-    for (uint32_t k = 0; k < b.n; ++k) if (b.t[k].nitems) total += b.t[k].numel;
     const uint64_t slots = 5ull * cus;
-    uint64_t rounds = total / (slots * 16384ull * kWaves);   // at least 16 K elements per wave and round
-    rounds = rounds < 1 ? 1 : rounds > 6 ? 6 : rounds;
-    const uint64_t deal = slots * rounds;
     for (uint32_t k = 0; k < b.n; ++k) {
         TensorD &t = b.t[k];
-        // Large planes, fewer of them than the chip holds waves (one wave per plane would leave it
-        // half empty): a workgroup per plane, its waves side by side on the plane's bands.
-        if (t.nitems && t.big) t.big = (t.nitems < slots * kWaves && t.shape[2] > t.Rb) ? 2u : 1u;
+        // Few large planes (one wave per plane would leave the chip half empty): a workgroup per
+        // plane, its waves side by side on the plane's bands.  It has to pay for its barriers, for
+        // waves without a band in the plane's last round and for columns that do not fill four
+        // waves, so the fewer bands a plane has the sooner a wave per plane is the better one.
+        // Measured, shared / a wave per plane: planes of 224x224 (25 bands), 3072 of them 249 / 282 us,
+        // 4480: 359 / 356; 160x160 (14), 2304: 108 / 139; 112x112 (7), 2304: 66 / 73, 3072: 81 / 77,
+        // 3840: 102 / 86; 56x56 (2), 768: 22 / 25, 1536: 29 / 27, 2624: 42 / 31.
+        if (!t.nitems || !t.big) continue;
+        const uint32_t nbands = (t.shape[2] + t.Rb - 1) / t.Rb;
+        const uint64_t waves = slots * kWaves;
+        const uint64_t limit = nbands >= 12u ? waves : nbands > 4u ? waves / 2u : waves / 4u;
+        t.big = (nbands > 1u && t.nitems < limit) ? 2u : 1u;
     }
     for (uint32_t shared = 0; shared < 2; ++shared) {
+        uint64_t total = 0;
+        for (uint32_t k = 0; k < b.n; ++k)
+            if (b.t[k].nitems && (b.t[k].big == 2) == (shared == 1)) total += b.t[k].numel;
+        if (!total) continue;
+        uint64_t rounds = total / (slots * 16384ull * kWaves);   // at least 16 K elements per wave and round
+        rounds = rounds < 1 ? 1 : rounds > 6 ? 6 : rounds;
+        const uint64_t deal = slots * rounds;
         uint32_t grid = 0;
         for (uint32_t k = 0; k < b.n; ++k) {
             TensorD &t = b.t[k];
@@ -588,7 +601,6 @@ void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st
             if (t.nwg < 1) t.nwg = 1;
             grid += t.nwg;
         }
-        if (!grid) continue;
         if (shared) {
             switch (b.sub) {
             case 32:  launch(prof, kKDecodeFused, k_decode_fused<32, true>, dim3(grid), dim3(kThreads), st, b); break;
