@@ -30,6 +30,47 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
+// One exchange of a bitonic merge: a and b hold the keys of the lower and the upper lane of the
+// lane's pair; the lower lane keeps the smaller one.
+__device__ __forceinline__ uint64_t keep_of_pair(uint64_t a, uint64_t b, bool upper)
+{
+    return ((b < a) != upper) ? b : a;
+}
+template <int CTRL>
+__device__ __forceinline__ uint64_t exchange_dpp(uint64_t k, bool upper)
+{
+    const uint64_t p = ((uint64_t)dpp_u32<CTRL, 0xf>((uint32_t)(k >> 32)) << 32) | dpp_u32<CTRL, 0xf>((uint32_t)k);
+    return ((p < k) != upper) ? p : k;
+}
+// lane ^ 4: four lanes up in the even banks of a row, four down in the odd ones
+__device__ __forceinline__ uint32_t lane_xor4(uint32_t v)
+{
+    const int up = __builtin_amdgcn_update_dpp((int)v, (int)v, 0x104, 0xf, 0x5, false);     // row_shl:4
+    return (uint32_t)__builtin_amdgcn_update_dpp(up, (int)v, 0x114, 0xf, 0xA, false);       // row_shr:4
+}
+
+// A bitonic sequence of distinct keys, one per lane, into ascending order over the lanes.
+__device__ __forceinline__ uint64_t bitonic_merge_64(uint64_t k, int lane)
+{
+    {   // lane ^ 32: the swap of halves leaves both keys of a pair in both its lanes
+        const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(k >> 32), (uint32_t)(k >> 32), false, false);
+        const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)k, (uint32_t)k, false, false);
+        k = keep_of_pair(((uint64_t)h[0] << 32) | l[0], ((uint64_t)h[1] << 32) | l[1], (lane & 32) != 0);
+    }
+    {   // lane ^ 16: the same by rows
+        const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(k >> 32), (uint32_t)(k >> 32), false, false);
+        const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)k, (uint32_t)k, false, false);
+        k = keep_of_pair(((uint64_t)h[0] << 32) | l[0], ((uint64_t)h[1] << 32) | l[1], (lane & 16) != 0);
+    }
+    k = exchange_dpp<0x128>(k, (lane & 8) != 0);             // row_ror:8
+    {
+        const uint64_t p = ((uint64_t)lane_xor4((uint32_t)(k >> 32)) << 32) | lane_xor4((uint32_t)k);
+        k = ((p < k) != ((lane & 4) != 0)) ? p : k;
+    }
+    k = exchange_dpp<0x4E>(k, (lane & 2) != 0);              // quad_perm 2,3,0,1
+    return exchange_dpp<0xB1>(k, (lane & 1) != 0);           // quad_perm 1,0,3,2
+}
+
 __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
 {
     // one workgroup per tensor of the group
@@ -43,13 +84,10 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     __shared__ uint16_t leaf_sym[kMaxSym];
     __shared__ uint32_t node_w[kMaxSym + 192];   // internal node weights in creation order, kInf = not made
     __shared__ uint16_t parent[2 * kMaxSym];     // node ids: leaves 0..n-1, internal n..2n-2
-    __shared__ uint32_t pair_w[64];              // weights of a round's nodes in their common order
     __shared__ uint32_t len_of[kMaxSym];         // code length per symbol
     __shared__ uint32_t wave_cnt[16][64];
-    __shared__ uint32_t bl_count[64];
     __shared__ uint64_t first_code[64];
     __shared__ uint32_t wave_used[16];
-    __shared__ uint32_t max_len_s;
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const uint32_t nsym = 2 * b.radius;
@@ -63,8 +101,6 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     }
     b.hist_copy[ti * kMaxSym + tid] = cnt;
     len_of[tid] = 0;
-    if (tid < 64) { bl_count[tid] = 0; first_code[tid] = 0; }
-    if (tid == 0) max_len_s = 0;
 
     // 2. compact the used symbols (ballot + per-wave offsets)
     const unsigned long long used_mask = __ballot(cnt != 0);
@@ -117,46 +153,30 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     //    of the same weight, each queue in its own order -- and joins them two by two.  A node made
     //    now weighs at least t, the sum of the two lightest unused nodes, and queues up behind every
     //    node that exists already; so all unused nodes of weight <= t keep their places in that
-    //    order whatever is made from them, and a whole round of them can be joined at once: every
-    //    lane looks at one leaf and one internal node of the 64 next of either queue, finds their
-    //    places in the common order by binary search in the other queue, and the pairs (0,1), (2,3),
-    //    ... become the new nodes, already in order of weight.  Activation histograms need about
-    //    twenty rounds where the sequential rule needs hundreds of steps.
+    //    order whatever is made from them, and a whole round of them can be joined at once: the next
+    //    64 nodes of either queue are merged into their common order, one node per lane, and the
+    //    pairs (0,1), (2,3), ... become the new nodes, already in order of weight.  Activation
+    //    histograms need about twenty rounds where the sequential rule needs hundreds of steps.
+    //    Both windows are ascending, so the lighter of leaf i and node 63-i, over all lanes, are the
+    //    64 lightest of the 128 as a bitonic sequence, which six exchanges between lanes sort
+    //    without touching LDS.  A round is one wave's latency and nothing else.  Against places found
+    //    by binary search in LDS (four dependent accesses), LDS counters for the lengths and a serial
+    //    loop over the first codes the kernel went from 22.6 to 14.8 us on one 64x56x56 activation,
+    //    32.6 to 22.4 us on 64x256x56x56 (eb 5e-3) and 39.4 to 26.0 us with all 1024 symbols in use.
     if (__builtin_amdgcn_readfirstlane(wv) == 0 && __builtin_amdgcn_readfirstlane((int)n) >= 2) {
         const uint32_t nu = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);   // n came from LDS: tell the compiler it is uniform
         const uint32_t steps = nu - 1;
         uint32_t ql = 0, qi = 0, m = 0;                      // leaves used, internal nodes used, internal nodes made
         while (m < steps) {
-            const uint32_t *lw = leaf_w + ql, *iw = node_w + qi;
-            const uint32_t LB = lw[lane];                    // kInf past the last leaf
-            const uint32_t IB = iw[lane];                    // kInf at and past node m
-            const uint64_t l0 = rdlane(LB, 0), l1 = rdlane(LB, 1), i0 = rdlane(IB, 0), i1 = rdlane(IB, 1);
-            uint64_t t = l0 + l1;                            // the two lightest of the four heads
-            t = (l0 + i0 < t) ? l0 + i0 : t;
-            t = (i0 + i1 < t) ? i0 + i1 : t;
+            const uint32_t lw = leaf_w[ql + lane];           // kInf past the last leaf
+            const uint32_t iw = node_w[qi + 63 - lane];      // kInf at and past node m
+            // place in the window, leaves before nodes: the order among equal weights
+            const uint64_t kl = ((uint64_t)lw << 32) | (uint32_t)lane, ki = ((uint64_t)iw << 32) | (uint32_t)(127 - lane);
+            const uint64_t k = bitonic_merge_64(ki < kl ? ki : kl, lane);
+            const uint32_t w = (uint32_t)(k >> 32), id = (uint32_t)k;
+            const uint64_t t = (uint64_t)rdlane(w, 0) + rdlane(w, 1);
             const uint32_t t32 = (t < (uint64_t)kInf) ? (uint32_t)t : kInf - 1u;
-            const bool inL = LB <= t32, inI = IB <= t32;     // a prefix of either window
-            // places in the common order: internal nodes lighter than the leaf come before it, leaves
-            // no heavier than the internal node before that one.  Counts are exact up to 64, and a
-            // node with 64 others in front of it is not part of this round anyway.
-            // (searches with three pivots per step: three dependent LDS accesses instead of six)
-            uint32_t before_leaf = 0, before_node = 0;
-#pragma unroll
-            for (uint32_t step = 16; step >= 1; step >>= 2) {
-                const uint32_t a1 = iw[before_leaf + step - 1], a2 = iw[before_leaf + 2 * step - 1], a3 = iw[before_leaf + 3 * step - 1];
-                const uint32_t c1 = lw[before_node + step - 1], c2 = lw[before_node + 2 * step - 1], c3 = lw[before_node + 3 * step - 1];
-                before_leaf += (((a1 < LB) ? 1u : 0u) + ((a2 < LB) ? 1u : 0u) + ((a3 < LB) ? 1u : 0u)) * step;
-                before_node += (((c1 <= IB) ? 1u : 0u) + ((c2 <= IB) ? 1u : 0u) + ((c3 <= IB) ? 1u : 0u)) * step;
-            }
-            {
-                const uint32_t a = iw[before_leaf], c = lw[before_node];    // counts of 63 may be 64
-                before_leaf += (a < LB) ? 1u : 0u;
-                before_node += (c <= IB) ? 1u : 0u;
-            }
-            const uint32_t rank_leaf = (uint32_t)lane + before_leaf, rank_node = (uint32_t)lane + before_node;
-            const uint32_t avail = (uint32_t)__popcll(__ballot(inL)) + (uint32_t)__popcll(__ballot(inI));
-            uint32_t npairs = avail >> 1;
-            npairs = npairs < 32u ? npairs : 32u;
+            uint32_t npairs = (uint32_t)__popcll(__ballot(w <= t32)) >> 1;       // (a prefix of the lanes)
             npairs = npairs < steps - m ? npairs : steps - m;
             // the two lightest nodes always weigh <= t, so a round joins at least one pair; a histogram
             // whose counts do not add up below 2^32 (damaged scratch memory) could break that: leave
@@ -165,14 +185,14 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
                 if (lane == 0) atomicOr(b.status, kStInternal);
                 break;
             }
-            const bool use_leaf = inL && rank_leaf < 2u * npairs, use_node = inI && rank_node < 2u * npairs;
-            if (use_leaf) { pair_w[rank_leaf] = LB; parent[ql + lane] = (uint16_t)(nu + m + (rank_leaf >> 1)); }
-            if (use_node) { pair_w[rank_node] = IB; parent[nu + qi + lane] = (uint16_t)(nu + m + (rank_node >> 1)); }
+            const bool used = (uint32_t)lane < 2u * npairs, leaf = id < 64u;
+            const uint32_t sum = w + dpp_u32<0xB1, 0xf>(w);                      // with the pair's other node
+            if (used) parent[leaf ? ql + id : nu + qi + (id - 64u)] = (uint16_t)(nu + m + ((uint32_t)lane >> 1));
+            if (used && !(lane & 1)) node_w[m + ((uint32_t)lane >> 1)] = sum;
             wave_lds_sync();
-            if ((uint32_t)lane < npairs) node_w[m + lane] = pair_w[2 * lane] + pair_w[2 * lane + 1];
-            wave_lds_sync();
-            ql += (uint32_t)__popcll(__ballot(use_leaf));
-            qi += (uint32_t)__popcll(__ballot(use_node));
+            const uint32_t nl = (uint32_t)__popcll(__ballot(used && leaf));
+            ql += nl;
+            qi += 2u * npairs - nl;
             m += npairs;
         }
     }
@@ -188,21 +208,47 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
             for (uint32_t v = tid; v != root && depth < 64u; v = parent[v] & (2 * kMaxSym - 1)) ++depth;
         }
         len_of[leaf_sym[tid]] = depth;
-        atomicAdd(&bl_count[depth & 63u], 1u);
-        atomicMax(&max_len_s, depth);
     }
     __syncthreads();
 
-    // 6. canonical codes: first code of each length, then rank within the length
-    if (tid == 0) {
-        uint64_t code = 0;
-        for (int L = 1; L < 64; ++L) {
-            code = (code + (uint64_t)(L > 1 ? bl_count[L - 1] : 0u)) << 1;
-            first_code[L] = code;
-        }
+    // 6. canonical codes.  Every wave ranks its symbols within their lengths; then wave 0, a lane per
+    //    length, turns the waves' counts into offsets and finds the first code of its length: with
+    //    P = the sum of count[j] << (48 - j) over all shorter lengths j it is P >> (48 - length).
+    const uint32_t L = len_of[tid] & 63u;
+    uint32_t in_wave = 0;
+    wave_cnt[wv][lane] = 0;
+    wave_lds_sync();
+    unsigned long long remaining = __ballot(L != 0);
+    while (remaining) {                                   // wave-uniform
+        const uint32_t Lx = rdlane(L, (uint32_t)__ffsll((long long)remaining) - 1u);
+        const unsigned long long same = __ballot(L == Lx);
+        if (L == Lx) in_wave = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+        if (lane == 0) wave_cnt[wv][Lx] = (uint32_t)__popcll(same);
+        remaining &= ~same;
     }
-    const uint32_t L = len_of[tid];
-    const uint32_t rank = rank_within_length(L, wave_cnt, tid);       // contains barriers
+    __syncthreads();
+    if (wv == 0) {
+        uint32_t total = 0;
+#pragma unroll
+        for (int k = 0; k < kCbThreads / kWave; ++k) {
+            const uint32_t c = wave_cnt[k][lane];
+            wave_cnt[k][lane] = total;                    // symbols of this length in earlier waves
+            total += c;
+        }
+        const unsigned long long present = __ballot(total != 0);
+        const uint32_t max_len = present ? 63u - (uint32_t)__builtin_clzll(present) : 0u;
+        // (below 2^48 in all: three limbs of 24 bits, each scanned in 32 bits without overflow)
+        const bool real = lane >= 1 && lane <= (int)kMaxCodeLen;
+        const uint64_t sl = real ? ((uint64_t)total << (kMaxCodeLen - lane)) : 0ull;
+        const uint32_t i0 = wave_inclusive_sum((uint32_t)(sl & 0xffffffu));
+        const uint32_t i1 = wave_inclusive_sum((uint32_t)((sl >> 24) & 0xffffffu));
+        const uint32_t i2 = wave_inclusive_sum((uint32_t)(sl >> 48));
+        const uint64_t excl = (uint64_t)i0 + ((uint64_t)i1 << 24) + ((uint64_t)i2 << 48) - sl;
+        first_code[lane] = real ? (excl >> (kMaxCodeLen - lane)) : 0ull;
+        if (lane == 0) b.tmeta[ti].max_len = max_len;
+    }
+    __syncthreads();
+    const uint32_t rank = wave_cnt[wv][L] + in_wave;
     const uint64_t entry = L ? (((uint64_t)L << 56) | (first_code[L] + rank)) : 0ull;
     b.codes[ti * kMaxSym + tid] = entry;
     b.lens[ti * kMaxSym + tid] = (uint8_t)L;
@@ -212,7 +258,6 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     // container section `lens`: 2*radius bytes, zero padded to a multiple of 16
     const uint32_t padded = (nsym + 15u) & ~15u;
     if ((uint32_t)tid < padded && oref.cap >= kHeaderBytes + padded) out[kHeaderBytes + tid] = ((uint32_t)tid < nsym) ? (uint8_t)L : 0;
-    if (tid == 0) b.tmeta[ti].max_len = max_len_s;
 }
 
 }  // namespace

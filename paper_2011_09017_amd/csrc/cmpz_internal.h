@@ -315,29 +315,6 @@ __device__ __forceinline__ void wave_segmented_sum(int32_t &v, uint32_t &f)
 }
 #undef CMPZ_SEG_STEP
 
-// For each of 1024 symbols (one per thread, 16 waves): how many symbols with a smaller index
-// have the same nonzero code length L.  wave_cnt is LDS scratch; contains a barrier.
-__device__ __forceinline__ uint32_t rank_within_length(uint32_t L, uint32_t (*wave_cnt)[64], int tid)
-{
-    const int lane = tid & 63, wv = tid >> 6;
-    for (int k = tid; k < 16 * 64; k += 1024) (&wave_cnt[0][0])[k] = 0;
-    __syncthreads();
-    uint32_t in_wave = 0;
-    unsigned long long remaining = __ballot(L != 0);
-    while (remaining) {                                   // wave-uniform
-        const int leader = __ffsll((long long)remaining) - 1;
-        const uint32_t Lx = __shfl(L, leader);
-        const unsigned long long m = __ballot(L == Lx);
-        if (L == Lx) in_wave = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-        if (lane == leader) wave_cnt[wv][Lx & 63u] = (uint32_t)__popcll(m);
-        remaining &= ~m;
-    }
-    __syncthreads();
-    uint32_t base = 0;
-    if (L) for (int k = 0; k < wv; ++k) base += wave_cnt[k][L & 63u];
-    return base + in_wave;
-}
-
 // Kernel identifiers for the optional per-kernel timing (cmp_profile).
 enum KernelId : int {
     kKQuantLorenzoHist = 0, kKCodebook, kKLengths, kKScan, kKPack, kKClear,

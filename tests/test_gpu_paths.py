@@ -1,4 +1,5 @@
-"""GPU parity of the decode plans: the shapes and counts at which the launch rule changes its variant.
+"""GPU parity at the edges of the kernels' paths: the shapes, counts and sizes at which a launch rule
+changes its variant or a kernel its loop.
 
 Bar: container and reconstruction equal the CPU oracle's bit for bit.
 """
@@ -46,3 +47,25 @@ def check(gpu, orc, shapes, eb, sub, zero_blocks=0, k=5, p_zero=0.6):
 ])
 def test_shared_planes_or_one_wave_each(gpu, orc, shapes):
     check(gpu, orc, shapes, 1e-2, 32)
+
+
+@pytest.mark.parametrize("nsym", [4, 62, 64, 66, 126, 128, 130, 500])
+@pytest.mark.parametrize("weights", [(1,), (1, 2, 3, 4, 8), (1, 1, 50, 2000)])
+def test_codebook_around_its_window(gpu, orc, nsym, weights):
+    """Used symbols around the 64 nodes of either queue that a round of the merge looks at, with counts
+    that tie within and across the queues: code lengths and codes of the sequential rule."""
+    eb = 1e-2
+    _, _, s, _ = orc.constants(eb)
+    rng = np.random.default_rng(nsym + len(weights))
+    v = np.repeat(np.arange(1, nsym // 2 + 1), rng.choice(weights, nsym // 2))
+    rng.shuffle(v)
+    d = np.stack([v, -v], axis=1).reshape(-1)                    # (v, -v): the running sums stay small
+    d = np.concatenate([d, np.zeros((-d.size) % 64, np.int64)])
+    q = np.cumsum(d.reshape(-1, 64), axis=1)
+    x = (q.astype(np.float32) * np.float32(s)).reshape(1, -1, 1, 64)
+    ctx = gpu.Context(sub=32, max_numel=x.size)
+    buf, size, rc = ctx.compress(torch.from_numpy(x).cuda(), eb)
+    orc_rc, obuf, osize, st = orc.compress(x, eb, orc.Config(sub=32), want_stages=True)
+    assert rc == 0 and orc_rc == 0
+    assert np.array_equal(ctx.stage(gpu.CMP_STAGE_LENS).numpy(), st.lens)
+    assert size == osize and np.array_equal(buf[:size].cpu().numpy(), obuf)
