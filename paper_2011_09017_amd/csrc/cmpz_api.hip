@@ -98,7 +98,7 @@ uint64_t carve_scratch(Scratch *sc, uint8_t *base, uint64_t max_numel, uint64_t 
 {
     Scratch s;
     s.max_chunks = (max_numel + kChunk - 1) / kChunk + kBatchMax;       // every tensor of a call rounds up
-    s.max_ranges = (s.max_chunks + kPackChunks - 1) / kPackChunks + kBatchMax;
+    s.max_ranges = (s.max_chunks + kPackChunksMin - 1) / kPackChunksMin + kBatchMax;
     uint64_t off = 0;
     auto carve = [&](uint64_t bytes) { uint64_t o = off; off = align_up(off + bytes, 256); return base + o; };
     s.sym = reinterpret_cast<uint16_t *>(carve(2 * (s.max_chunks * kChunk + 16)));   // whole chunks: readable past numel
@@ -266,9 +266,7 @@ void group_add(BatchC *b, const CheckedTensor &c, void *d_out, size_t out_cap)
     for (int i = 0; i < 4; ++i) t.shape[i] = c.shape[i];
     t.numel = (uint32_t)c.numel; t.nchunks = c.lay.nchunks; t.eb_bits = c.eb_bits; t.r = c.r;
     t.chunk_base = b->total_chunks;
-    t.pack_base = b->pack_wgs;
     b->total_chunks += t.nchunks;
-    b->pack_wgs += (t.nchunks + kPackChunks - 1) / kPackChunks;
     t.divW = FastDiv::make(c.shape[3]);
     t.divHW = FastDiv::make(c.shape[2] * c.shape[3]);
 }
@@ -294,6 +292,26 @@ void group_plan_sweep(BatchC *b, uint32_t cus)
         TensorC &t = b->t[k];
         t.sweep_base = b->sweep_wgs;
         if (sweep1_tiled_fits(t.shape[3])) b->sweep_wgs += (t.nchunks + b->sweep_chunks - 1) / b->sweep_chunks;
+    }
+}
+
+// Chunks per workgroup of the bit-count and packing kernels, once all tensors of the group are known.
+// Their waves take whole chunks one after the other, so a call of few chunks wants them spread over
+// the chip, one per wave; a workgroup also loads the code table and the offsets, so a large call wants
+// sixteen.  The line is where the next smaller range still gives every compute unit four workgroups.
+// Whole compressions with 16 / with 4 or 8 chunks: 49 chunks 55.9 / 38.9 us, 784: 63.1 / 44.1, 3136
+// (4 chunks): 75.7 / 61.2, 9075 (8): 105.4 / 96.5, 12544 (8): 131.0 / 125.2; 25088: 218.0 / 216.5 with 8,
+// and 144 256 chunks are slower with 8 (packing 241 / 254 us).
+void group_plan_pack(BatchC *b, uint32_t cus)
+{
+    uint32_t pc = kPackChunks;
+    while (pc > kPackChunksMin && b->total_chunks < 4u * cus * pc) pc /= 2;
+    b->pack_chunks = pc;
+    b->pack_wgs = 0;
+    for (uint32_t k = 0; k < b->n; ++k) {
+        TensorC &t = b->t[k];
+        t.pack_base = b->pack_wgs;
+        b->pack_wgs += (t.nchunks + pc - 1) / pc;
     }
 }
 
@@ -347,6 +365,7 @@ int cmp_compress_batch(cmp_ctx *ctx, int n, const float *const *d_x, const int64
             ++i;
         }
         group_plan_sweep(&b, ctx->cus);
+        group_plan_pack(&b, ctx->cus);
         group_launch_begin(b, &ctx->prof, st);
         group_launch_finish(b, &ctx->prof, st);
         ctx->last_numel = b.t[0].numel;
@@ -430,6 +449,7 @@ int cmp_compress_static(int device, const cmp_config *cfg, const float *d_x, con
     group_add(&b, ck, d_out, out_cap);
     // (at most 2^22 elements: one round of workgroups whatever the device has)
     group_plan_sweep(&b, 256);
+    group_plan_pack(&b, 256);
     // the array keeps the last call's contents, whatever that call was: what the first sweep adds
     // to must start at zero (a fill kernel, so that the call can be captured into a graph)
     launch_clear(b, nullptr, st);
@@ -482,6 +502,7 @@ int cmp_arena_push(cmp_ctx *ctx, void *d_arena, size_t arena_cap, void *d_state,
     group_add(&b, ck, d_arena, arena_cap);
     b.t[0].arena = static_cast<const ArenaState *>(d_state);
     group_plan_sweep(&b, ctx->cus);
+    group_plan_pack(&b, ctx->cus);
     group_launch_begin(b, &ctx->prof, st);
     group_launch_finish(b, &ctx->prof, st);
     launch_arena_pushed(b, static_cast<ArenaState *>(d_state), slot, st);
@@ -555,6 +576,7 @@ int cmp_compress_begin(cmp_ctx *ctx, const float *d_x, const int64_t shape[4], f
     group_begin(&b, ctx->cfg, ctx->s);
     group_add(&b, c, nullptr, 0);
     group_plan_sweep(&b, ctx->cus);
+    group_plan_pack(&b, ctx->cus);
     group_launch_begin(b, &ctx->prof, static_cast<hipStream_t>(stream));
     if (hipGetLastError() != hipSuccess) return CMP_E_HIP;
     ctx->has_pending = true;

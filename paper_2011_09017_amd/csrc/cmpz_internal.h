@@ -100,10 +100,11 @@ enum MetaWord : int {
 // Chunks of all tensors of a call are numbered consecutively (tensor t owns the global chunks
 // chunk_base .. chunk_base + nchunks - 1); the symbol scratch holds whole chunks, so tensor t's
 // symbols start at element chunk_base * 4096.  The bit-count and packing kernels give a workgroup
-// a range of kPackChunks consecutive chunks of one tensor; those ranges are numbered
+// a range of pack_chunks consecutive chunks of one tensor; those ranges are numbered
 // consecutively too (tensor t owns pack_base .. ).
 constexpr int      kBatchMax   = 24;        // tensors per launch group (kernel arguments hold their descriptors)
-constexpr uint32_t kPackChunks = 16;        // chunks per workgroup of the bit-count and packing kernels
+constexpr uint32_t kPackChunks = 16;        // chunks per workgroup of the bit-count and packing kernels: at most,
+constexpr uint32_t kPackChunksMin = 4;      // and at least (one per wave)
 
 // A stack of containers in one device buffer whose bookkeeping lives on the device: where the
 // next container goes is known to the GPU only (it depends on the sizes of the containers before
@@ -160,6 +161,7 @@ struct BatchC {
     uint32_t zero_blocks;       // 1: sub-blocks of zero residuals are not coded (container version 2)
     uint32_t sweep_chunks;      // chunks per workgroup in the first sweep
     uint32_t sweep_wgs, pack_wgs, total_chunks;
+    uint32_t pack_chunks;       // chunks per workgroup of the bit-count and packing kernels (at most kPackChunks)
     // context scratch
     uint16_t   *sym;            // whole chunks of 4096 symbols, 8192 bytes apart.  Every quarter of a chunk (1024
                                 // symbols, 2048 bytes apart) holds 16 bits per symbol or, if not marked wide,

@@ -3,7 +3,7 @@
 //
 //   k_lengths  one streaming pass over the symbols (8 or 16 bits each, as the first sweep left
 //              them): the bit count of every sub-block (written straight into the container),
-//              of every chunk and of every range of kPackChunks chunks;
+//              of every chunk and of every range of up to kPackChunks chunks;
 //   k_scan     one workgroup per tensor: exclusive prefix sums of the ranges' payload units
 //              and outlier counts, the container header, the decision whether it fits;
 //   k_pack     the same ranges again: chunk offsets from the range's prefix, the codewords of
@@ -69,8 +69,8 @@ __global__ __launch_bounds__(kThreads) void k_lengths(BatchC b)
     const uint32_t range = b.pack_wgs - 1u - blockIdx.x;
     const uint32_t ti = tensor_of_range(b, range);
     const TensorC &tc = b.t[ti];
-    const uint32_t c0 = (range - tc.pack_base) * kPackChunks;
-    const uint32_t nq = (tc.nchunks - c0 < kPackChunks) ? tc.nchunks - c0 : kPackChunks;
+    const uint32_t c0 = (range - tc.pack_base) * b.pack_chunks;
+    const uint32_t nq = (tc.nchunks - c0 < b.pack_chunks) ? tc.nchunks - c0 : b.pack_chunks;
     const uint32_t numel = tc.numel;
     static_assert(kMaxSym / 4 == kThreads, "one word of the length table per thread");
     lens_s[tid] = reinterpret_cast<const uint32_t *>(b.lens + (uint64_t)ti * kMaxSym)[tid];
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(BatchC b)
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const uint32_t ti = blockIdx.x;
     const TensorC &tc = b.t[ti];
-    const uint32_t nr = (tc.nchunks + kPackChunks - 1) / kPackChunks;
+    const uint32_t nr = (tc.nchunks + b.pack_chunks - 1) / b.pack_chunks;
     uint32_t *__restrict__ ru = b.range_units + tc.pack_base;
     uint32_t *__restrict__ ro = b.range_outl + tc.pack_base;
     const uint32_t *__restrict__ rb = b.range_bits + tc.pack_base;
@@ -314,8 +314,8 @@ __global__ __launch_bounds__(kThreads, ZB ? 5 : 6) void k_pack(BatchC b)
     const TensorC &tc = b.t[ti];
     const TensorMeta &tm = b.tmeta[ti];
     if (tm.skip) return;                             // uniform: the container does not fit, its header says so
-    const uint32_t c0 = (blockIdx.x - tc.pack_base) * kPackChunks;
-    const uint32_t nq = (tc.nchunks - c0 < kPackChunks) ? tc.nchunks - c0 : kPackChunks;
+    const uint32_t c0 = (blockIdx.x - tc.pack_base) * b.pack_chunks;
+    const uint32_t nq = (tc.nchunks - c0 < b.pack_chunks) ? tc.nchunks - c0 : b.pack_chunks;
     const uint32_t numel = tc.numel;
     const bool short_codes = tm.max_len <= kShortMax;                // uniform
     const Layout lay = make_layout(numel, b.radius, b.sub);

@@ -69,3 +69,14 @@ def test_codebook_around_its_window(gpu, orc, nsym, weights):
     assert rc == 0 and orc_rc == 0
     assert np.array_equal(ctx.stage(gpu.CMP_STAGE_LENS).numpy(), st.lens)
     assert size == osize and np.array_equal(buf[:size].cpu().numpy(), obuf)
+
+
+@pytest.mark.parametrize("chunks", [1, 3, 4, 5, 16, 17])
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+@pytest.mark.parametrize("zero_blocks", [0, 1])
+def test_ranges_of_few_chunks(gpu, orc, chunks, extra, zero_blocks):
+    """Tensors that end at or beside the end of a chunk and of a workgroup's range of chunks, alone in a
+    call and after another tensor."""
+    n = chunks * 4096 + extra
+    check(gpu, orc, [(1, 1, 1, n)], 1e-2, 64, zero_blocks, p_zero=0.8)
+    check(gpu, orc, [(2, 3, 37, 41), (1, n, 1, 1), (1, 1, 64, 65)], 1e-3, 32, zero_blocks, p_zero=0.8)
