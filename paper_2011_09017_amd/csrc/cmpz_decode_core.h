@@ -25,8 +25,8 @@ struct DecodeTables {
                                   // (symbol - radius) in 10 bits, two's complement, three to a word
                                   // (read only for codewords that neither table level resolves)
     uint64_t first[kMaxCodeLen + 2];   // first canonical code of each length (indexed by the length)
-    uint32_t count[kMaxCodeLen + 2];   // codes of each length
-    uint32_t offs[kMaxCodeLen + 2];    // index into sorted[] of the first symbol of each length
+    uint32_t last32[kMaxCodeLen + 2];  // largest left-aligned 32-bit value that belongs to a code of at most that length
+    uint32_t base[kMaxCodeLen + 2];    // what turns a code of each length into its index in the ordered symbols (mod 2^32)
     uint32_t t32;                 // left-aligned threshold above which codes are longer than kLB
     uint32_t sh;                  // level-2 shift
     uint32_t has_long;            // any code longer than kLB bits
@@ -40,6 +40,12 @@ __device__ __forceinline__ uint32_t sorted_at(const DecodeTables &T, uint32_t i)
 {
     const uint32_t w = i / 3u;
     return (T.sorted3[w] >> (10u * (i - 3u * w))) & 1023u;
+}
+
+// Codes of length L: the first code of the next length is twice the one after the last of these.
+__device__ __forceinline__ uint64_t codes_of_length(const DecodeTables &T, uint32_t L)
+{
+    return (T.first[L + 1] >> 1) - T.first[L];
 }
 
 // Cooperative copy global -> LDS (both are the same struct).
@@ -186,7 +192,12 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
         const uint64_t incl = (uint64_t)i0 + ((uint64_t)i1 << 24) + ((uint64_t)i2 << 48);
         const uint64_t excl = incl - sl;
         const uint64_t first = (lane >= 1 && lane <= (int)kMaxCodeLen) ? (excl >> (kMaxCodeLen - lane)) : 0ull;
-        if (lane <= (int)kMaxCodeLen) { T.first[lane] = first; T.count[lane] = cnt; T.offs[lane] = offs; }
+        if (lane <= (int)kMaxCodeLen) {
+            T.first[lane] = first;
+            T.last32[lane] = (uint32_t)(incl >> (kMaxCodeLen - 32)) - 1u;
+            T.base[lane] = offs - (uint32_t)first;
+        }
+        if (lane == (int)kMaxCodeLen) T.first[lane + 1] = (first + cnt) << 1;
         lim[lane] = incl;
         if (lane == 63) {
             uint32_t bad = 0;
@@ -215,7 +226,7 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
     // symbols ordered by (length, symbol)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        if (L[q]) sorted[T.offs[L[q]] + wave_cnt[q * 4 + wv][L[q]] + in_wave[q]] = (uint16_t)((q * 256 + tid - a.radius) & 1023u);
+        if (L[q]) sorted[T.base[L[q]] + (uint32_t)T.first[L[q]] + wave_cnt[q * 4 + wv][L[q]] + in_wave[q]] = (uint16_t)((q * 256 + tid - a.radius) & 1023u);
     __syncthreads();
 
     // level 1: entry idx is the codeword (if any, of at most kLB bits) that prefixes idx
@@ -232,7 +243,7 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
 #pragma unroll
             for (uint32_t k = 1; k <= kLB; ++k) l += (idx >= l1[k]) ? 1u : 0u;
             uint32_t e = 0;
-            if (l <= kLB) e = sorted[T.offs[l] + (idx >> (kLB - l)) - (uint32_t)T.first[l]] | (l << 10);
+            if (l <= kLB) e = sorted[T.base[l] + (idx >> (kLB - l))] | (l << 10);
             T.t1[idx] = (uint16_t)e;
         }
     }
@@ -256,7 +267,7 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
         for (int k = 0; k < kPer; ++k) {
             uint32_t e = 0;
             if (has_long && v[k] < (1ull << 32) && l[k] <= lmax)
-                e = sorted[T.offs[l[k]] + (uint32_t)((v[k] >> (32 - l[k])) - T.first[l[k]])] | (l[k] << 10);
+                e = sorted[T.base[l[k]] + (uint32_t)(v[k] >> (32 - l[k]))] | (l[k] << 10);
             T.t2[tid + 256 * k] = (uint16_t)e;
         }
     }
@@ -343,8 +354,8 @@ __device__ __forceinline__ uint32_t decode_run(const DecodeTables &T, RD rd, uin
                 uint32_t len = 0, sy = 0;                    // no match: residual 0
                 for (uint32_t L = has_long ? first_unresolved_length(sh) : kLB + 1; L <= T.max_len; ++L) {
                     const uint64_t code = w64 >> (64 - L);
-                    if (code >= T.first[L] && code - T.first[L] < T.count[L]) {
-                        sy = sorted_at(T, T.offs[L] + (uint32_t)(code - T.first[L]));
+                    if (code >= T.first[L] && code - T.first[L] < codes_of_length(T, L)) {
+                        sy = sorted_at(T, T.base[L] + (uint32_t)code);
                         len = L;
                         break;
                     }
@@ -377,8 +388,13 @@ __device__ __forceinline__ uint32_t decode_run(const DecodeTables &T, RD rd, uin
 // whatever the stream holds; the caller's buffer has that many words behind the staged ones
 // (stage_tail_words).
 constexpr uint32_t stage_tail_words(uint32_t count) { return count * kMaxCodeLen / 32 + 4; }
+//
+// BOTH: the two table levels are looked up side by side, and only codewords that neither resolves
+// take a branch.  Five more instructions per step, so not for loops that keep the vector units busy
+// (32 codes per sub-block: 0.937 -> 0.952 ms on the ResNet-18-shaped stream), but a shorter chain
+// where codes of more than kLB bits are common (64x256x56x56 at eb 5e-3, pooled: 277 -> 243 us).
 constexpr int kStagePad = 4;
-template <class PUT>
+template <bool BOTH, class PUT>
 __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint32_t *S, uint32_t pos,
                                                uint32_t count, uint32_t skip, PUT put, bool &bad)
 {
@@ -402,35 +418,45 @@ __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint
     for (uint32_t k = 0; k < count; ++k) {
         const uint32_t hi = __builtin_amdgcn_alignbit(wa, wb, npos);
         uint32_t e = *reinterpret_cast<const uint16_t *>(t1 + ((hi >> (31 - kLB)) & (2u * kT1Size - 2u)));
+        if (BOTH) {
+            uint32_t i2 = (hi - t32) >> sh;                   // (below t32 the first level has the codeword)
+            i2 = i2 < kT2Size ? i2 : kT2Size - 1;
+            const uint32_t e2 = T.t2[i2];
+            e = e ? e : e2;
+        }
         if (__builtin_expect(e == 0, 0)) {
-            {
+            if (!BOTH) {
                 // (a codebook without long codes has a second table of zeros: no test for that case)
                 uint32_t i2 = (hi - t32) >> sh;
                 i2 = i2 < kT2Size ? i2 : kT2Size - 1;
                 e = T.t2[i2];
             }
             if (__builtin_expect(e == 0, 0)) {
-                // canonical search over the lengths the second level does not resolve: up to 31 bits
-                // in 32-bit arithmetic (a code below the first one of its length wraps to a difference
-                // of at least 2^31, far above any count), beyond that on a 64-bit window
+                // canonical search over the lengths the second level does not resolve.  Up to 31 bits the
+                // length is the first one whose largest value is not below the window: four lengths per
+                // look at the table, so that an LDS round trip or two settle what took two per length
+                // (64x256x56x56 at eb 5e-3 and 128 codes per sub-block: 243 -> 232 us).
                 uint32_t len = 0, sy = 0;                     // no match: residual 0
                 const uint32_t max_len = T.max_len;
                 uint32_t L = first_unresolved_length(sh);
-                for (; L <= max_len && L < 32u; ++L) {
-                    const uint32_t rel = (hi >> (32u - L)) - (uint32_t)T.first[L];
-                    if (rel < T.count[L]) {
-                        sy = sorted_at(T, T.offs[L] + rel);
-                        len = L;
-                        break;
+                while (L <= max_len && L < 32u) {
+                    const uint32_t n = ((hi > T.last32[L]) ? 1u : 0u) + ((hi > T.last32[L + 1]) ? 1u : 0u) +
+                                       ((hi > T.last32[L + 2]) ? 1u : 0u) + ((hi > T.last32[L + 3]) ? 1u : 0u);
+                    L += n;
+                    if (n == 4u) continue;
+                    if (L <= max_len && L < 32u) {
+                        const uint32_t i = (hi >> (32u - L)) + T.base[L];
+                        if (i < kMaxSym) { sy = sorted_at(T, i); len = L; }    // (always, with the lengths of a complete code)
                     }
+                    break;
                 }
                 if (len == 0 && max_len >= 32u) {
                     const uint32_t lo = __builtin_amdgcn_alignbit(wb, wc, npos);
                     const uint64_t v = (((uint64_t)hi) << 32) | lo;
                     for (L = L < 32u ? 32u : L; L <= max_len; ++L) {
                         const uint64_t code = v >> (64 - L);
-                        if (code >= T.first[L] && code - T.first[L] < T.count[L]) {
-                            sy = sorted_at(T, T.offs[L] + (uint32_t)(code - T.first[L]));
+                        if (code >= T.first[L] && code - T.first[L] < codes_of_length(T, L)) {
+                            sy = sorted_at(T, T.base[L] + (uint32_t)code);
                             len = L;
                             break;
                         }

@@ -29,6 +29,8 @@
 // rows in flight) adds them on the fly, de-quantises and stores.  A band with
 // outliers stores plain residuals and patches the outliers in; then its lanes
 // sum their rows in LDS, and the rest is the same.
+// With sub-blocks of 64 or 128 codes the bands of two or four waves are decoded by
+// one wave (a band alone would fill 32 or 16 of its lanes), two barriers per band.
 // Software pipeline: the bit counts of the next band are fetched during the
 // decode of the current one, and its payload during the column pass.
 #include "cmpz_decode_core.h"
@@ -91,6 +93,15 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     constexpr int kNSub = (int)kChunk / SUB;              // sub-blocks per chunk
     constexpr int kPre  = kNSub + kND;                    // bit-count entries looked at per band
     constexpr int kE    = (kPre + kWave - 1) / kWave;     // of which each lane fetches kE consecutive ones
+    // Sub-blocks longer than 32 codes are too few per band to fill a wave: the bands of two (64 codes)
+    // or four waves (128) of the workgroup are decoded by one of them, a lane per sub-block, between
+    // two barriers.  The chain of a lane's dependent steps bounds this, not their number: the loop has
+    // a fixed count, so that it unrolls and the look-ahead word is not waited for in the step that
+    // fetches it.  64x256x56x56 at eb 1e-2: 236 -> 166 us at 128 codes, 147 -> 113 at 64 (pooled with
+    // the loop's count per lane: 226 and 135; a raised wave priority: 172 and 116); at eb 5e-3,
+    // with its longer codes, 261 -> 232 us at 128.
+    constexpr bool kPool = kND < kWave;
+    constexpr int kPoolWaves = kWave / kND;               // bands decoded together
     static_assert(2 * kND <= kStageWords, "the lane records live in the staging buffer");
     static_assert(kStageWords / 4 == 2 * kWave, "two units per lane");
 
@@ -261,7 +272,8 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
         stage_load(sg, s0, s1);
     }
 
-    while (item < pl.nitems) {                       // uniform in the wave; with shared planes, in the workgroup
+    // uniform in the wave; with shared planes and with pooled decoding, in the workgroup
+    for (uint32_t round = 0; (kPool && !coop ? item - wv : item) < pl.nitems; ++round) {
         // ---- next band: geometry now, bit counts in flight while this band is decoded ----
         uint32_t nitem = item, nb = bi + 1;
         if (nb >= nsteps) { nitem = item + item_stride; nb = 0; }
@@ -307,7 +319,91 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
         uint32_t my_reset = 0;
         // (a band with outliers: what the lane needs to sum its rows once the outliers are patched in)
         uint32_t late_klo = 0, late_khi = 0, late_w = 0;
-        if (lane < (int)nsb) {
+        bool pooled = false;                             // this lane's sub-block is decoded by the pool's wave
+        if (kPool) {
+            // What the pool's wave needs to know of a sub-block, in the (still unused) slot that will
+            // take its residuals: its bit position in the staged payload, the elements of it that
+            // belong to the band, the place in its row of the first of them, its stored bit count.
+            if (lane < kND) {
+                uint32_t spos = 0, klo = 0, khi = 0, w_first = 0, flags = 0;
+                if (staged && lane < (int)nsb) {
+                    const uint32_t el0 = (sb0 + lane) << kLog;
+                    const uint32_t n_here = (a.numel - el0 >= (uint32_t)SUB) ? (uint32_t)SUB : a.numel - el0;
+                    klo = (el0 < e0) ? e0 - el0 : 0u;
+                    khi = (el0 + n_here > e0 + n) ? e0 + n - el0 : n_here;
+                    const uint32_t l_first = el0 + klo - e0;
+                    my_reset = klo;
+                    const bool zeros_only = a.zero_blocks && sbits == 0;
+                    const uint32_t nw = (fa.uu0 <= fa.uu1 && fa.uu1 <= payload_units) ? (fa.uu1 - fa.uu0) * 4 : 0u;
+                    bool lbad = !(fa.uu0 <= fa.uu1 && fa.uu1 <= payload_units);
+                    if ((nw == 0 && !zeros_only) || (uint64_t)start + sbits > (uint64_t)nw * 32) lbad = true;
+                    const int64_t rel = ((int64_t)fa.uu0 - (int64_t)sg.q0) * 128 + (int64_t)start;
+                    if (!lbad && (rel < 0 || rel + (int64_t)sbits > (int64_t)sg.nq * 128)) lbad = true;
+                    if (!lbad) {
+                        pooled = true;
+                        spos = (uint32_t)rel;
+                        // a complete sub-block is decoded whole: all its slots are written, and those
+                        // outside the band are never read (elements before it belong to an earlier row,
+                        // so its own first element starts one)
+                        const bool whole = n_here == (uint32_t)SUB;
+                        if (folded) {
+                            w_first = l_first - pl.divW.div(l_first) * W;
+                            const uint32_t k0 = klo + (w_first ? W - w_first : 0u);
+                            my_reset = k0 < khi ? k0 : (uint32_t)SUB;
+                        } else {
+                            late_klo = klo; late_khi = khi; late_w = l_first;
+                        }
+                        flags = 0x8000u | (folded ? 0x4000u : 0u) | (zeros_only ? 0x2000u : 0u) | (whole ? 0x1000u : 0u) |
+                                (khi == n_here ? 0x800u : 0u);
+                    }
+                    bad |= lbad;
+                }
+                RT *rec = R + lane * (SUB + 1);
+                rec[0] = (RT)spos; rec[1] = (RT)(klo | (khi << 8)); rec[2] = (RT)(w_first | flags); rec[3] = (RT)sbits;
+            }
+            __syncthreads();
+            // the pool's wave changes from round to round, so that the four SIMDs share the work
+            const uint32_t turn = round + blockIdx.x + (blockIdx.x >> 8);
+            if (((uint32_t)wv & (kPoolWaves - 1)) == (turn & (kPoolWaves - 1))) {     // uniform in the wave
+                const uint32_t j = ((uint32_t)wv & ~(uint32_t)(kPoolWaves - 1)) + (uint32_t)lane / kND;    // the band's wave
+                RT *my = lds.Rs[j] + ((uint32_t)lane & (kND - 1)) * (SUB + 1);
+                const uint32_t spos = (uint16_t)my[0] + j * (kStageWords * 32u), kk = (uint16_t)my[1],
+                               fl = (uint16_t)my[2], sb = (uint16_t)my[3];
+                const uint32_t klo = kk & 0xffu, khi = kk >> 8, w_first = fl & 0x7ffu;
+                int32_t run = 0;
+                if (fl & 0x8000u) {
+                    // steps to the next row start, counted down; a band with outliers keeps plain
+                    // residuals: every element starts a row
+                    const uint32_t again = (fl & 0x4000u) ? W - 1u : 0u;
+                    uint32_t togo = (fl & 0x1000u) ? klo : 0u;
+                    if (w_first) togo += W - w_first;
+                    auto put = [&](uint32_t k, int32_t d) {
+                        const bool in_row = togo != 0u;
+                        run = (in_row ? run : 0) + d;
+                        togo = in_row ? togo - 1u : again;
+                        my[k] = (RT)run;
+                    };
+                    bool lbad = false;
+                    uint32_t end = spos + sb;
+                    if (fl & 0x2000u) {
+                        for (uint32_t k = klo; k < khi; ++k) put(k, 0);
+                    } else if (fl & 0x1000u) {
+                        end = decode_lds<true>(T, lds.Ss, spos, (uint32_t)SUB, 0u, put, lbad);
+                    } else {                             // the tensor's last sub-block, incomplete
+                        const uint32_t e = decode_lds<false>(T, lds.Ss, spos, khi, klo, put, lbad);
+                        if (fl & 0x800u) end = e;
+                    }
+                    bad |= lbad || end != spos + sb;
+                    run = (fl & 0x4000u) ? (int32_t)my[khi - 1u] : 0;
+                }
+                wave_sync();                             // the staged payload has been read
+                reinterpret_cast<int32_t *>(lds.Ss + j * kStageWords + kStagePad)[(uint32_t)lane & (kND - 1)] = run;
+            }
+            __syncthreads();
+            if (pooled && folded) my_tail = reinterpret_cast<const int32_t *>(S + kStagePad)[lane];
+            wave_sync();
+        }
+        if (lane < (int)nsb && (!kPool || !staged)) {
             const uint32_t g = sb0 + lane;
             const uint32_t uu0 = fa.uu0, uu1 = fa.uu1;
             bool lbad = !(uu0 <= uu1 && uu1 <= payload_units);
@@ -345,7 +441,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                         return start;
                     }
                     if (staged)
-                        return decode_lds(T, S, spos, count, skip, put, lbad) - spos + start;
+                        return decode_lds<false>(T, S, spos, count, skip, put, lbad) - spos + start;
                     return decode_run<false>(T, [&](uint32_t k) -> uint32_t { return gw[k < last ? k : last]; }, start,
                                              count, skip, put, lbad);
                 };

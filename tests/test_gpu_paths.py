@@ -80,3 +80,16 @@ def test_ranges_of_few_chunks(gpu, orc, chunks, extra, zero_blocks):
     n = chunks * 4096 + extra
     check(gpu, orc, [(1, 1, 1, n)], 1e-2, 64, zero_blocks, p_zero=0.8)
     check(gpu, orc, [(2, 3, 37, 41), (1, n, 1, 1), (1, 1, 64, 65)], 1e-3, 32, zero_blocks, p_zero=0.8)
+
+
+# sub-blocks of 64 and 128 codes, bands decoded by another wave than their own: rows that end inside a
+# sub-block, a ragged last sub-block, waves without a band, outliers, planes of every plan, payload
+# beyond the staging buffer, sub-blocks without codes
+@pytest.mark.parametrize("sub", [64, 128])
+@pytest.mark.parametrize("shape,eb,zero_blocks", [
+    ((1, 1, 1, 3), 1e-2, 0), ((3, 7, 13, 11), 1e-2, 0), ((2, 41, 28, 29), 1e-2, 1), ((1, 3, 45, 44), 1e-3, 0),
+    ((2, 2, 101, 99), 1e-2, 0), ((1, 5, 61, 255), 1e-3, 0), ((29, 200, 47, 45), 2e-2, 0), ((1, 3, 200, 64), 2e-4, 0),
+    ((2, 64, 33, 128), 1e-2, 1),
+])
+def test_pooled_decode(gpu, orc, sub, shape, eb, zero_blocks):
+    check(gpu, orc, [shape], eb, sub, zero_blocks, p_zero=0.9 if zero_blocks else 0.5)
