@@ -473,7 +473,7 @@ int cmp_arena_accepts(const cmp_ctx *ctx, const int64_t shape[4])
     std::memset(&t, 0, sizeof(t));
     for (int k = 0; k < 4; ++k) t.shape[k] = (uint32_t)shape[k];
     t.numel = (uint32_t)numel;
-    return plan_decode_fused(&t, ctx->cfg.sub) ? 1 : 0;
+    return plan_decode_fused(&t, ctx->cfg.sub, false) ? 1 : 0;
 }
 
 int cmp_arena_init(cmp_ctx *ctx, void *d_state, uint32_t slots, void *stream)
@@ -537,7 +537,7 @@ int cmp_arena_pop(cmp_ctx *ctx, const void *d_arena, void *d_state, uint32_t slo
     t.s = s;
     // the kernels for shapes outside the fused kernel's plan take their arguments from the host,
     // which does not know where the container lies
-    if (!plan_decode_fused(&t, ctx->cfg.sub)) return CMP_E_ARG;
+    if (!plan_decode_fused(&t, ctx->cfg.sub, false)) return CMP_E_ARG;
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return CMP_E_HIP;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -652,7 +652,7 @@ int cmp_decompress_batch(cmp_ctx *ctx, int n, const void *const *d_buf, const si
         t.numel = (uint32_t)numel;
         std::memcpy(&t.eb_bits, &eb[i], 4);
         t.s = s;
-        if (!plan_decode_fused(&t, ctx->cfg.sub)) t.nitems = 0;
+        if (!plan_decode_fused(&t, ctx->cfg.sub, true)) t.nitems = 0;
     }
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return CMP_E_HIP;

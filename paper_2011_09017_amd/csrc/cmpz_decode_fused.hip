@@ -11,7 +11,8 @@
 // Planes larger than a band are walked band by band with running column sums
 // (needs W <= 256); where a tensor has few such planes, a variant of the kernel
 // gives a plane to a workgroup, whose waves decode four bands side by side and
-// share the column pass by columns.  Shapes that fit neither case take the
+// share the column pass by columns (also for rows of up to 512, where there are enough
+// such planes).  Shapes that fit neither case take the
 // unfused kernels of cmpz_decompress.hip.
 //
 // A band is decoded by one lane per sub-block (the container stores each
@@ -45,6 +46,7 @@ constexpr int kWaves      = kThreads / kWave;
 constexpr int kBandMax    = 2048;                 // elements decoded per band at most
 constexpr int kStageWords = 512;                  // staged payload per band: 2 KB, i.e. 8 bits per code of a full band
 constexpr int kColGroups  = 4;                    // 64-column groups of a big plane (W <= 256)
+constexpr int kWideGroups = 2;                    // 64-column groups of a quarter of a wide row (W <= 512)
 
 template <int SUB> struct Cfg;
 template <> struct Cfg<128> { static constexpr int kLog = 7; };
@@ -82,8 +84,9 @@ struct Stage {
 // One launch decodes all tensors of a call: a workgroup belongs to one tensor (it validates that
 // container and builds that codebook's decode tables for itself, about a microsecond), its waves
 // take every item_stride-th item of the tensor.
-// COOP: the variant for few large planes (plan value big == 2), a launch of its own.
-template <int SUB, bool COOP>
+// COOP: 1 the variant for few large planes (plan value big == 2), 2 the same for rows wider than
+// kColGroups waves (big == 3), each a launch of its own.
+template <int SUB, int COOP>
 __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
 {
     using RT = int16_t;
@@ -255,7 +258,8 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     // four consecutive bands of the same plane, decode them side by side, and then share the column
     // pass by columns, each wave running its quarter of the columns down all four bands, with two
     // workgroup barriers per round.  `bi` then counts rounds of four bands.
-    constexpr bool coop = COOP;
+    constexpr bool coop = COOP != 0;
+    constexpr int kGroups = (COOP == 2) ? kWideGroups : (COOP == 1) ? 1 : kColGroups;   // column groups of a wave
     const uint32_t nbands_big = pl.big ? (H + pl.Rb - 1) / pl.Rb : 1u;
     const uint32_t nsteps = coop ? (nbands_big + kWaves - 1) / kWaves : nbands_big;
     const uint32_t item_stride = coop ? td.nwg : td.nwg * kWaves;
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     auto band_at = [&](uint32_t it, uint32_t step) -> Band { return band_of(it, coop ? step * kWaves + wv : step); };
     Band cur = band_at(item, bi);
     Ahead fa = fetch(cur);
-    int32_t colacc[kColGroups] = {0, 0, 0, 0};               // running column sums (big planes)
+    int32_t colacc[kGroups] = {};                            // running column sums (big planes)
     uint4 s0 = make_uint4(0, 0, 0, 0), s1 = s0;
     Stage sg = {0, 0};
     if (cur.valid) {
@@ -290,7 +294,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
         const uint32_t j0 = sb0 & (kNSub - 1);           // position of sb0 in its chunk
         if (bi == 0) {
 #pragma unroll
-            for (int c = 0; c < kColGroups; ++c) colacc[c] = 0;
+            for (int c = 0; c < kGroups; ++c) colacc[c] = 0;
         }
 
         // this lane's sub-block in its chunk's stream (P is rewritten for the next band below)
@@ -590,25 +594,28 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
             // every wave has decoded its band of this round: now a quarter of the columns each,
             // down the round's bands in their order
             __syncthreads();
-            const uint32_t cw = (W + kWaves - 1) / kWaves;           // <= 64: W <= kColGroups * 64
-            const uint32_t col = (uint32_t)wv * cw + (uint32_t)lane;
-            if ((uint32_t)lane < cw && col < W) {
-                int32_t acc = colacc[0];
-                for (uint32_t j = 0; j < (uint32_t)kWaves; ++j) {
-                    const uint32_t row0 = (bi * kWaves + j) * pl.Rb;
-                    if (row0 >= H) break;                            // uniform
-                    const uint32_t rowsj = (H - row0 < pl.Rb) ? H - row0 : pl.Rb;
-                    const uint32_t ej0 = item * HW + row0 * W;
-                    acc = walk_band(lds.Rs[j], reinterpret_cast<const uint2 *>(lds.Ss + j * kStageWords + kStagePad),
-                                    ej0 - ((ej0 >> kLog) << kLog), rowsj, reinterpret_cast<char *>(a.xout + ej0), col, acc);
+            const uint32_t cw = (W + kWaves - 1) / kWaves;           // <= kGroups * 64
+#pragma unroll
+            for (int c = 0; c < kGroups; ++c) {
+                const uint32_t at = (uint32_t)(c * kWave + lane), col = (uint32_t)wv * cw + at;
+                if (at < cw && col < W) {
+                    int32_t acc = colacc[c];
+                    for (uint32_t j = 0; j < (uint32_t)kWaves; ++j) {
+                        const uint32_t row0 = (bi * kWaves + j) * pl.Rb;
+                        if (row0 >= H) break;                        // uniform
+                        const uint32_t rowsj = (H - row0 < pl.Rb) ? H - row0 : pl.Rb;
+                        const uint32_t ej0 = item * HW + row0 * W;
+                        acc = walk_band(lds.Rs[j], reinterpret_cast<const uint2 *>(lds.Ss + j * kStageWords + kStagePad),
+                                        ej0 - ((ej0 >> kLog) << kLog), rowsj, reinterpret_cast<char *>(a.xout + ej0), col, acc);
+                    }
+                    colacc[c] = acc;
                 }
-                colacc[0] = acc;
             }
             __syncthreads();                              // R and the staging buffers are reused by the next round
         } else {
             if (pl.big) {
 #pragma unroll
-                for (int c = 0; c < kColGroups; ++c) {
+                for (int c = 0; c < kGroups; ++c) {
                     const uint32_t col = c * kWave + lane;
                     if (col < W) colacc[c] = walk(col, colacc[c]);
                 }
@@ -625,10 +632,16 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
 
 }  // namespace
 
-// The fused kernel's plan for one tensor.  Returns false when the shape does not fit it (planes
-// larger than one band with rows wider than kColGroups waves): such tensors take the unfused
-// kernels.
-bool plan_decode_fused(TensorD *t, uint32_t sub)
+// The fused kernel's plan for one tensor.  Returns false when the shape does not fit it: such tensors
+// take the unfused kernels.  Planes larger than one band need rows of at most kColGroups waves, or, if
+// `wide` rows are asked for, rows of up to 512, sub-blocks of 32 codes and no fewer than kWidePlanes
+// planes: such planes are always shared by the waves of a workgroup, which walk down the plane, and
+// with few planes or the longer chains of longer sub-blocks the passes over memory of the unfused
+// kernels, which spread a plane over the chip, are faster.  Measured on planes of 375x500, fused /
+// unfused: 192 of them 213 / 283 us, 256: 215 / 342, 512: 254 / 812; 128 (with more groups) 289 / 236; with
+// 128 codes per sub-block 256 planes 780 / 328; 64 planes of 700x1100 2122 / 429.
+constexpr uint32_t kWidePlanes = 192;
+bool plan_decode_fused(TensorD *t, uint32_t sub, bool wide)
 {
     const uint32_t H = t->shape[2], W = t->shape[3], HW = H * W, planes = t->shape[0] * t->shape[1];
     const uint32_t ndec = kBandMax / sub;
@@ -641,6 +654,9 @@ bool plan_decode_fused(TensorD *t, uint32_t sub)
         t->nitems = (planes + t->G - 1) / t->G;
     } else if (W <= (uint32_t)(kColGroups * kWave) && W <= cap) {
         t->big = 1; t->G = 1; t->Rb = (uint32_t)(cap / W);
+        t->nitems = planes;
+    } else if (wide && sub == 32 && W <= (uint32_t)(kWideGroups * kWave * kWaves) && planes >= kWidePlanes) {
+        t->big = 3; t->G = 1; t->Rb = (uint32_t)(cap / W);
         t->nitems = planes;
     } else {
         return false;
@@ -671,16 +687,17 @@ void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st
         // Measured, shared / a wave per plane: planes of 224x224 (25 bands), 3072 of them 249 / 282 us,
         // 4480: 359 / 356; 160x160 (14), 2304: 108 / 139; 112x112 (7), 2304: 66 / 73, 3072: 81 / 77,
         // 3840: 102 / 86; 56x56 (2), 768: 22 / 25, 1536: 29 / 27, 2624: 42 / 31.
-        if (!t.nitems || !t.big) continue;
+        if (!t.nitems || !t.big || t.big == 3) continue;
         const uint32_t nbands = (t.shape[2] + t.Rb - 1) / t.Rb;
         const uint64_t waves = slots * kWaves;
         const uint64_t limit = nbands >= 12u ? waves : nbands > 4u ? waves / 2u : waves / 4u;
         t.big = (nbands > 1u && t.nitems < limit) ? 2u : 1u;
     }
-    for (uint32_t shared = 0; shared < 2; ++shared) {
+    for (uint32_t shared = 0; shared < 3; ++shared) {
+        auto in_launch = [&](const TensorD &t) { return t.nitems && (t.big < 2u ? 0u : t.big - 1u) == shared; };
         uint64_t total = 0;
         for (uint32_t k = 0; k < b.n; ++k)
-            if (b.t[k].nitems && (b.t[k].big == 2) == (shared == 1)) total += b.t[k].numel;
+            if (in_launch(b.t[k])) total += b.t[k].numel;
         if (!total) continue;
         uint64_t rounds = total / (slots * 16384ull * kWaves);   // at least 16 K elements per wave and round
         rounds = rounds < 1 ? 1 : rounds > 6 ? 6 : rounds;
@@ -690,26 +707,24 @@ void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st
             TensorD &t = b.t[k];
             t.wg_base = grid;
             t.nwg = 0;
-            if (!t.nitems || (t.big == 2) != (shared == 1)) continue;    // not in this launch: no workgroups
+            if (!in_launch(t)) continue;                                 // not in this launch: no workgroups
             const uint64_t share = ((uint64_t)t.numel * deal + total - 1) / total;
             const uint64_t most = shared ? t.nitems : (t.nitems + kWaves - 1) / kWaves;
             t.nwg = (uint32_t)(share < most ? share : most);
             if (t.nwg < 1) t.nwg = 1;
             grid += t.nwg;
         }
-        if (shared) {
+        auto go = [&](auto coop_c) {
+            constexpr int kCoop = decltype(coop_c)::value;
             switch (b.sub) {
-            case 32:  launch(prof, kKDecodeFused, k_decode_fused<32, true>, dim3(grid), dim3(kThreads), st, b); break;
-            case 64:  launch(prof, kKDecodeFused, k_decode_fused<64, true>, dim3(grid), dim3(kThreads), st, b); break;
-            default:  launch(prof, kKDecodeFused, k_decode_fused<128, true>, dim3(grid), dim3(kThreads), st, b); break;
+            case 32:  launch(prof, kKDecodeFused, k_decode_fused<32, kCoop>, dim3(grid), dim3(kThreads), st, b); break;
+            case 64:  launch(prof, kKDecodeFused, k_decode_fused<64, kCoop>, dim3(grid), dim3(kThreads), st, b); break;
+            default:  launch(prof, kKDecodeFused, k_decode_fused<128, kCoop>, dim3(grid), dim3(kThreads), st, b); break;
             }
-        } else {
-            switch (b.sub) {
-            case 32:  launch(prof, kKDecodeFused, k_decode_fused<32, false>, dim3(grid), dim3(kThreads), st, b); break;
-            case 64:  launch(prof, kKDecodeFused, k_decode_fused<64, false>, dim3(grid), dim3(kThreads), st, b); break;
-            default:  launch(prof, kKDecodeFused, k_decode_fused<128, false>, dim3(grid), dim3(kThreads), st, b); break;
-            }
-        }
+        };
+        if (shared == 0) go(std::integral_constant<int, 0>{});
+        else if (shared == 1) go(std::integral_constant<int, 1>{});
+        else launch(prof, kKDecodeFused, k_decode_fused<32, 2>, dim3(grid), dim3(kThreads), st, b);
     }
 }
 

@@ -93,3 +93,14 @@ def test_ranges_of_few_chunks(gpu, orc, chunks, extra, zero_blocks):
 ])
 def test_pooled_decode(gpu, orc, sub, shape, eb, zero_blocks):
     check(gpu, orc, [shape], eb, sub, zero_blocks, p_zero=0.9 if zero_blocks else 0.5)
+
+
+# rows wider than four waves in planes larger than a band: shared by the waves of a workgroup up to 512
+# columns, with sub-blocks of 32 codes and from a number of planes on, the unfused kernels otherwise
+@pytest.mark.parametrize("shape,sub,eb", [
+    ((1, 400, 9, 257), 32, 1e-2), ((4, 100, 8, 500), 32, 1e-3), ((1, 192, 17, 512), 32, 1e-2),
+    ((1, 192, 4, 513), 32, 1e-2), ((1, 191, 5, 512), 32, 1e-2), ((1, 400, 8, 301), 128, 1e-2),
+    ((3, 150, 18, 385), 32, 1e-2), ((1, 3, 40, 700), 32, 1e-2),
+])
+def test_wide_rows(gpu, orc, shape, sub, eb):
+    check(gpu, orc, [shape, (2, 3, 28, 28), (1, 2, 100, 90)], eb, sub, zero_blocks=1 if shape[1] == 150 else 0)
