@@ -5,9 +5,10 @@
 // codeword of at most kLB bits.  Canonical codes grow with their length when
 // left-aligned, so all longer codewords sit above a threshold t32 in the
 // left-aligned code space; level 2 is indexed by (next 32 bits - t32) >> sh and
-// resolves codewords of up to 32 - sh bits.  Whatever is longer still (rare, and
-// impossible unless counts are extremely skewed) is found by the textbook
-// canonical search over first[]/count[].
+// resolves codewords of up to 32 - sh bits.  Whatever is longer still is found by
+// canonical search: decode_lds compares with last32[] for lengths below 32 and from
+// there on with first[], as decode_run does for all of them; base[] then leads to
+// the symbol.
 #pragma once
 #include "cmpz_internal.h"
 
@@ -26,6 +27,8 @@ struct DecodeTables {
                                   // (read only for codewords that neither table level resolves)
     uint64_t first[kMaxCodeLen + 2];   // first canonical code of each length (indexed by the length)
     uint32_t last32[kMaxCodeLen + 2];  // largest left-aligned 32-bit value that belongs to a code of at most that length
+                                  // (exact up to 32 bits, and from the length of the shortest code on; beyond 32
+                                  // bits rounded down: no limit to search by)
     uint32_t base[kMaxCodeLen + 2];    // what turns a code of each length into its index in the ordered symbols (mod 2^32)
     uint32_t t32;                 // left-aligned threshold above which codes are longer than kLB
     uint32_t sh;                  // level-2 shift
@@ -453,7 +456,9 @@ __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint
                 if (len == 0 && max_len >= 32u) {
                     const uint32_t lo = __builtin_amdgcn_alignbit(wb, wc, npos);
                     const uint64_t v = (((uint64_t)hi) << 32) | lo;
-                    for (L = L < 32u ? 32u : L; L <= max_len; ++L) {
+                    // from 32, however far the looks above have counted: past 32 bits last32 is rounded down, and
+                    // a window may lie above it and still hold a codeword of that length
+                    for (L = L < 32u ? L : 32u; L <= max_len; ++L) {
                         const uint64_t code = v >> (64 - L);
                         if (code >= T.first[L] && code - T.first[L] < codes_of_length(T, L)) {
                             sy = sorted_at(T, T.base[L] + (uint32_t)code);
