@@ -495,13 +495,20 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
         if (!folded) {
             // ---- outliers overwrite their residuals; then every lane sums its rows as the other
             //      bands' lanes do while they decode ----
+            uint32_t farthest = 0;                       // largest index met: beyond the tensor it is damage
             for (uint32_t k = olo + lane; k < ohi; k += kWave) {
                 const uint32_t i = oidx[k];
+                farthest = i > farthest ? i : farthest;
                 if (i >= e0 && i - e0 < n) {
                     const uint32_t u = i - base;
                     R[u + (u >> kLog)] = oval[k];
+                } else if (COOP == 2) {
+                    // of another band of these chunks, or of a chunk that the list does not place it in: the
+                    // unfused kernels, which take such shapes too, would patch it wherever it lies
+                    bad |= i / kChunk - e0 / kChunk > (e0 + n - 1) / kChunk - e0 / kChunk;
                 }
             }
+            bad |= farthest >= a.numel;
             wave_sync();
             if (late_klo < late_khi) {
                 RT *my = R + lane * (SUB + 1);
