@@ -6,9 +6,8 @@
 // left-aligned, so all longer codewords sit above a threshold t32 in the
 // left-aligned code space; level 2 is indexed by (next 32 bits - t32) >> sh and
 // resolves codewords of up to 32 - sh bits.  Whatever is longer still is found by
-// canonical search: decode_lds compares with last32[] for lengths below 32 and from
-// there on with first[], as decode_run does for all of them; base[] then leads to
-// the symbol.
+// canonical search: decode_lds compares with the limits in range[] for lengths below
+// 32 and from there on with first[], as decode_run does for all of them.
 #pragma once
 #include "cmpz_internal.h"
 
@@ -26,10 +25,11 @@ struct DecodeTables {
                                   // (symbol - radius) in 10 bits, two's complement, three to a word
                                   // (read only for codewords that neither table level resolves)
     uint64_t first[kMaxCodeLen + 2];   // first canonical code of each length (indexed by the length)
-    uint32_t last32[kMaxCodeLen + 2];  // largest left-aligned 32-bit value that belongs to a code of at most that length
-                                  // (exact up to 32 bits, and from the length of the shortest code on; beyond 32
-                                  // bits rounded down: no limit to search by)
-    uint32_t base[kMaxCodeLen + 2];    // what turns a code of each length into its index in the ordered symbols (mod 2^32)
+    // Per length, side by side so that the search takes both with one access:
+    //   .x  largest left-aligned 32-bit value that belongs to a code of at most that length (exact up to 32
+    //       bits, and from the length of the shortest code on; rounded down beyond: no limit to search by)
+    //   .y  what turns a code of that length into its index in the ordered symbols (mod 2^32)
+    uint2    range[kMaxCodeLen + 2];
     uint32_t t32;                 // left-aligned threshold above which codes are longer than kLB
     uint32_t sh;                  // level-2 shift
     uint32_t has_long;            // any code longer than kLB bits
@@ -197,8 +197,7 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
         const uint64_t first = (lane >= 1 && lane <= (int)kMaxCodeLen) ? (excl >> (kMaxCodeLen - lane)) : 0ull;
         if (lane <= (int)kMaxCodeLen) {
             T.first[lane] = first;
-            T.last32[lane] = (uint32_t)(incl >> (kMaxCodeLen - 32)) - 1u;
-            T.base[lane] = offs - (uint32_t)first;
+            T.range[lane] = make_uint2((uint32_t)(incl >> (kMaxCodeLen - 32)) - 1u, offs - (uint32_t)first);
         }
         if (lane == (int)kMaxCodeLen) T.first[lane + 1] = (first + cnt) << 1;
         lim[lane] = incl;
@@ -229,7 +228,7 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
     // symbols ordered by (length, symbol)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        if (L[q]) sorted[T.base[L[q]] + (uint32_t)T.first[L[q]] + wave_cnt[q * 4 + wv][L[q]] + in_wave[q]] = (uint16_t)((q * 256 + tid - a.radius) & 1023u);
+        if (L[q]) sorted[T.range[L[q]].y + (uint32_t)T.first[L[q]] + wave_cnt[q * 4 + wv][L[q]] + in_wave[q]] = (uint16_t)((q * 256 + tid - a.radius) & 1023u);
     __syncthreads();
 
     // level 1: entry idx is the codeword (if any, of at most kLB bits) that prefixes idx
@@ -246,7 +245,7 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
 #pragma unroll
             for (uint32_t k = 1; k <= kLB; ++k) l += (idx >= l1[k]) ? 1u : 0u;
             uint32_t e = 0;
-            if (l <= kLB) e = sorted[T.base[l] + (idx >> (kLB - l))] | (l << 10);
+            if (l <= kLB) e = sorted[T.range[l].y + (idx >> (kLB - l))] | (l << 10);
             T.t1[idx] = (uint16_t)e;
         }
     }
@@ -270,7 +269,7 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
         for (int k = 0; k < kPer; ++k) {
             uint32_t e = 0;
             if (has_long && v[k] < (1ull << 32) && l[k] <= lmax)
-                e = sorted[T.base[l[k]] + (uint32_t)(v[k] >> (32 - l[k]))] | (l[k] << 10);
+                e = sorted[T.range[l[k]].y + (uint32_t)(v[k] >> (32 - l[k]))] | (l[k] << 10);
             T.t2[tid + 256 * k] = (uint16_t)e;
         }
     }
@@ -358,7 +357,7 @@ __device__ __forceinline__ uint32_t decode_run(const DecodeTables &T, RD rd, uin
                 for (uint32_t L = has_long ? first_unresolved_length(sh) : kLB + 1; L <= T.max_len; ++L) {
                     const uint64_t code = w64 >> (64 - L);
                     if (code >= T.first[L] && code - T.first[L] < codes_of_length(T, L)) {
-                        sy = sorted_at(T, T.base[L] + (uint32_t)code);
+                        sy = sorted_at(T, T.range[L].y + (uint32_t)code);
                         len = L;
                         break;
                     }
@@ -436,32 +435,32 @@ __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint
             }
             if (__builtin_expect(e == 0, 0)) {
                 // canonical search over the lengths the second level does not resolve.  Up to 31 bits the
-                // length is the first one whose largest value is not below the window: four lengths per
-                // look at the table, so that an LDS round trip or two settle what took two per length
-                // (64x256x56x56 at eb 5e-3 and 128 codes per sub-block: 243 -> 232 us).
+                // length is the first one whose limit is not below the window; the next length's limit is
+                // fetched beside the present one's.  Latency of LDS accesses bounds this: four limits per
+                // look, and the way to the symbol behind them, took longer where the first length or two
+                // hit: 64x256x56x56 at eb 5e-3 and 128 codes per sub-block 227 -> 213 us, 16x112x112 at
+                // eb 1e-3 and 32 codes 61.9 -> 59.3 (one length per look: 219 and 60.2).
                 uint32_t len = 0, sy = 0;                     // no match: residual 0
                 const uint32_t max_len = T.max_len;
                 uint32_t L = first_unresolved_length(sh);
-                while (L <= max_len && L < 32u) {
-                    const uint32_t n = ((hi > T.last32[L]) ? 1u : 0u) + ((hi > T.last32[L + 1]) ? 1u : 0u) +
-                                       ((hi > T.last32[L + 2]) ? 1u : 0u) + ((hi > T.last32[L + 3]) ? 1u : 0u);
-                    L += n;
-                    if (n == 4u) continue;
-                    if (L <= max_len && L < 32u) {
-                        const uint32_t i = (hi >> (32u - L)) + T.base[L];
-                        if (i < kMaxSym) { sy = sorted_at(T, i); len = L; }    // (always, with the lengths of a complete code)
-                    }
-                    break;
+                uint2 r = T.range[L], next = T.range[L + 1];
+                while (L < 32u && hi > r.x) {
+                    ++L; r = next;
+                    if (L < 32u && hi > r.x) { ++L; r = T.range[L]; next = T.range[L + 1]; }
+                }
+                if (L <= max_len && L < 32u) {
+                    const uint32_t i = (hi >> (32u - L)) + r.y;
+                    if (i < kMaxSym) { sy = sorted_at(T, i); len = L; }    // (always, with the lengths of a complete code)
                 }
                 if (len == 0 && max_len >= 32u) {
                     const uint32_t lo = __builtin_amdgcn_alignbit(wb, wc, npos);
                     const uint64_t v = (((uint64_t)hi) << 32) | lo;
-                    // from 32, however far the looks above have counted: past 32 bits last32 is rounded down, and
-                    // a window may lie above it and still hold a codeword of that length
-                    for (L = L < 32u ? L : 32u; L <= max_len; ++L) {
+                    // (past 32 bits a limit is rounded down, and a window above it may still hold a codeword of
+                    // that length: from here on by first codes)
+                    for (; L <= max_len; ++L) {
                         const uint64_t code = v >> (64 - L);
                         if (code >= T.first[L] && code - T.first[L] < codes_of_length(T, L)) {
-                            sy = sorted_at(T, T.base[L] + (uint32_t)code);
+                            sy = sorted_at(T, T.range[L].y + (uint32_t)code);
                             len = L;
                             break;
                         }
