@@ -33,6 +33,7 @@ struct DecodeTables {
     uint32_t t32;                 // left-aligned threshold above which codes are longer than kLB
     uint32_t sh;                  // level-2 shift
     uint32_t has_long;            // any code longer than kLB bits
+    uint32_t searched;            // share of the code space that neither level resolves, in units of 2^-32
     uint32_t max_len;
     uint32_t payload_units;
     uint32_t n_outliers;
@@ -219,7 +220,9 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
             const uint64_t span = (1ull << 32) - (t < (1ull << 32) ? t : (1ull << 32));
             uint32_t sh = 0;
             while ((span >> sh) > kT2Size) ++sh;
-            T.t32 = (uint32_t)t; T.sh = sh; T.has_long = (max_len > kLB && span > 0) ? 1u : 0u;
+            const uint32_t has_long = (max_len > kLB && span > 0) ? 1u : 0u;
+            T.t32 = (uint32_t)t; T.sh = sh; T.has_long = has_long;
+            T.searched = has_long ? (uint32_t)((1ull << 32) - (lim[32 - sh > kLB ? 32 - sh : kLB] >> (kMaxCodeLen - 32))) : 0u;
         }
     }
     __syncthreads();

@@ -31,7 +31,8 @@
 // outliers stores plain residuals and patches the outliers in; then its lanes
 // sum their rows in LDS, and the rest is the same.
 // With sub-blocks of 64 or 128 codes the bands of two or four waves are decoded by
-// one wave (a band alone would fill 32 or 16 of its lanes), two barriers per band.
+// one wave (a band alone would fill 32 or 16 of its lanes), two barriers per band,
+// unless the codebook sends too many codes past the tables.
 // Software pipeline: the bit counts of the next band are fetched during the
 // decode of the current one, and its payload during the column pass.
 #include "cmpz_decode_core.h"
@@ -105,6 +106,14 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     // with its longer codes, 261 -> 232 us at 128.
     constexpr bool kPool = kND < kWave;
     constexpr int kPoolWaves = kWave / kND;               // bands decoded together
+    // But a step waits for the canonical search as soon as one of its lanes needs it, and a pooled wave
+    // has two or four times the lanes.  So a codebook pools only if a sub-block is expected to search
+    // less than 0.64 times (the code space that the tables leave open is the share of codes that land
+    // there).  Pooled / each band by its own wave, with 128 codes: share 0.0013 2048 planes of 55x55
+    // 60 / 69 us, 512 of 112x112 66 / 75; 0.0035 64x256x56x56 213 / 264; 0.0064 100 / 83 and 105 / 92;
+    // 0.022 182 / 126 and 224 / 150.  With 64 codes: 0.0064 67 / 59 and 63 / 65; 0.011 103 / 81 and 101 / 82;
+    // 0.022 116 / 90 and 121 / 95.
+    constexpr uint32_t kPoolSearched = (uint32_t)(0.64 / SUB * 4294967296.0);
     static_assert(2 * kND <= kStageWords, "the lane records live in the staging buffer");
     static_assert(kStageWords / 4 == 2 * kWave, "two units per lane");
 
@@ -158,6 +167,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     // it lack the carry), .y = the carry
     uint2 *RC = reinterpret_cast<uint2 *>(S + kStagePad);
     const uint32_t payload_units = T.payload_units, n_outl = T.n_outliers;
+    const bool pool = kPool && (uint32_t)__builtin_amdgcn_readfirstlane((int)T.searched) < kPoolSearched;   // uniform in the workgroup
 
     const uint32_t W = a.W, H = a.H, HW = a.HW;
     const uint32_t *__restrict__ chunk_off = reinterpret_cast<const uint32_t *>(a.buf + a.lay.off_chunk_off);
@@ -277,7 +287,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     }
 
     // uniform in the wave; with shared planes and with pooled decoding, in the workgroup
-    for (uint32_t round = 0; (kPool && !coop ? item - wv : item) < pl.nitems; ++round) {
+    for (uint32_t round = 0; (pool && !coop ? item - wv : item) < pl.nitems; ++round) {
         // ---- next band: geometry now, bit counts in flight while this band is decoded ----
         uint32_t nitem = item, nb = bi + 1;
         if (nb >= nsteps) { nitem = item + item_stride; nb = 0; }
@@ -323,13 +333,15 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
         uint32_t my_reset = 0;
         // (a band with outliers: what the lane needs to sum its rows once the outliers are patched in)
         uint32_t late_klo = 0, late_khi = 0, late_w = 0;
-        bool pooled = false;                             // this lane's sub-block is decoded by the pool's wave
-        if (kPool) {
-            // What the pool's wave needs to know of a sub-block, in the (still unused) slot that will
+        if (pool) {
+            // What the pool's waves need to know of a sub-block, in the (still unused) slot that will
             // take its residuals: its bit position in the staged payload, the elements of it that
-            // belong to the band, the place in its row of the first of them, its stored bit count.
+            // belong to the band, its stored bit count; and in the pad slot behind, which outlasts the
+            // decode (two waves look at it), how to decode it and the place in its row of its first element.
+            uint32_t khi = 0;
+            bool pooled = false;                         // this lane's sub-block is decoded by the pool's waves
             if (lane < kND) {
-                uint32_t spos = 0, klo = 0, khi = 0, w_first = 0, flags = 0;
+                uint32_t spos = 0, klo = 0, w_first = 0, flags = 0;
                 if (staged && lane < (int)nsb) {
                     const uint32_t el0 = (sb0 + lane) << kLog;
                     const uint32_t n_here = (a.numel - el0 >= (uint32_t)SUB) ? (uint32_t)SUB : a.numel - el0;
@@ -363,51 +375,50 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                     bad |= lbad;
                 }
                 RT *rec = R + lane * (SUB + 1);
-                rec[0] = (RT)spos; rec[1] = (RT)(klo | (khi << 8)); rec[2] = (RT)(w_first | flags); rec[3] = (RT)sbits;
+                rec[0] = (RT)spos; rec[1] = (RT)(klo | (khi << 8)); rec[2] = (RT)sbits; rec[SUB] = (RT)(w_first | flags);
             }
             __syncthreads();
-            // the pool's wave changes from round to round, so that the four SIMDs share the work
+            // The pool's wave changes from round to round, so that the four SIMDs share the work.  The
+            // tensor's last sub-block, if incomplete, is left to the wave behind it, which would wait: in
+            // the same wave its steps would come on top (4 planes of 28x28, 128 codes: 36 -> 25 us).
             const uint32_t turn = round + blockIdx.x + (blockIdx.x >> 8);
-            if (((uint32_t)wv & (kPoolWaves - 1)) == (turn & (kPoolWaves - 1))) {     // uniform in the wave
+            const uint32_t role = ((uint32_t)wv - turn) & (uint32_t)(kPoolWaves - 1);
+            if (role < 2u) {                                                          // uniform in the wave
                 const uint32_t j = ((uint32_t)wv & ~(uint32_t)(kPoolWaves - 1)) + (uint32_t)lane / kND;    // the band's wave
                 RT *my = lds.Rs[j] + ((uint32_t)lane & (kND - 1)) * (SUB + 1);
                 const uint32_t spos = (uint16_t)my[0] + j * (kStageWords * 32u), kk = (uint16_t)my[1],
-                               fl = (uint16_t)my[2], sb = (uint16_t)my[3];
-                const uint32_t klo = kk & 0xffu, khi = kk >> 8, w_first = fl & 0x7ffu;
+                               sb = (uint16_t)my[2], fl = (uint16_t)my[SUB];
+                const uint32_t from = kk & 0xffu, to = kk >> 8, w_first = fl & 0x7ffu;
                 int32_t run = 0;
-                if (fl & 0x8000u) {
-                    // steps to the next row start, counted down; a band with outliers keeps plain
-                    // residuals: every element starts a row
-                    const uint32_t again = (fl & 0x4000u) ? W - 1u : 0u;
-                    uint32_t togo = (fl & 0x1000u) ? klo : 0u;
-                    if (w_first) togo += W - w_first;
-                    auto put = [&](uint32_t k, int32_t d) {
-                        const bool in_row = togo != 0u;
-                        run = (in_row ? run : 0) + d;
-                        togo = in_row ? togo - 1u : again;
-                        my[k] = (RT)run;
-                    };
-                    bool lbad = false;
-                    uint32_t end = spos + sb;
-                    if (fl & 0x2000u) {
-                        for (uint32_t k = klo; k < khi; ++k) put(k, 0);
-                    } else if (fl & 0x1000u) {
+                // steps to the next row start, counted down; a band with outliers keeps plain
+                // residuals: every element starts a row
+                const uint32_t again = (fl & 0x4000u) ? W - 1u : 0u;
+                uint32_t togo = (fl & 0x1000u) ? from : 0u;
+                if (w_first) togo += W - w_first;
+                auto put = [&](uint32_t k, int32_t d) {
+                    const bool in_row = togo != 0u;
+                    run = (in_row ? run : 0) + d;
+                    togo = in_row ? togo - 1u : again;
+                    my[k] = (RT)run;
+                };
+                bool lbad = false;
+                uint32_t end = spos + sb;
+                if (role == 0u) {
+                    if ((fl & 0xa000u) == 0xa000u) {
+                        for (uint32_t k = from; k < to; ++k) put(k, 0);
+                    } else if ((fl & 0x9000u) == 0x9000u) {
                         end = decode_lds<true>(T, lds.Ss, spos, (uint32_t)SUB, 0u, put, lbad);
-                    } else {                             // the tensor's last sub-block, incomplete
-                        const uint32_t e = decode_lds<false>(T, lds.Ss, spos, khi, klo, put, lbad);
-                        if (fl & 0x800u) end = e;
                     }
-                    bad |= lbad || end != spos + sb;
-                    run = (fl & 0x4000u) ? (int32_t)my[khi - 1u] : 0;
+                } else if ((fl & 0xb000u) == 0x8000u) {
+                    const uint32_t e = decode_lds<false>(T, lds.Ss, spos, to, from, put, lbad);
+                    if (fl & 0x800u) end = e;
                 }
-                wave_sync();                             // the staged payload has been read
-                reinterpret_cast<int32_t *>(lds.Ss + j * kStageWords + kStagePad)[(uint32_t)lane & (kND - 1)] = run;
+                bad |= lbad || end != spos + sb;
             }
             __syncthreads();
-            if (pooled && folded) my_tail = reinterpret_cast<const int32_t *>(S + kStagePad)[lane];
-            wave_sync();
+            if (pooled && folded) my_tail = R[lane * (SUB + 1) + khi - 1u];
         }
-        if (lane < (int)nsb && (!kPool || !staged)) {
+        if (lane < (int)nsb && (!pool || !staged)) {
             const uint32_t g = sb0 + lane;
             const uint32_t uu0 = fa.uu0, uu1 = fa.uu1;
             bool lbad = !(uu0 <= uu1 && uu1 <= payload_units);

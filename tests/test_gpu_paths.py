@@ -104,3 +104,13 @@ def test_pooled_decode(gpu, orc, sub, shape, eb, zero_blocks):
 ])
 def test_wide_rows(gpu, orc, shape, sub, eb):
     check(gpu, orc, [shape, (2, 3, 28, 28), (1, 2, 100, 90)], eb, sub, zero_blocks=1 if shape[1] == 150 else 0)
+
+
+# codebooks on either side of the share of codes past the tables from which every wave decodes its own
+# bands (from 2 % of the codes at eb 1e-3 to 0.03 % at 1e-2), and last sub-blocks that another wave than
+# the pool's decodes beside it: in the last of two bands, in a band of its own, behind planes of two bands
+@pytest.mark.parametrize("sub", [64, 128])
+@pytest.mark.parametrize("eb", [1e-3, 1.8e-3, 2.5e-3, 1e-2])
+@pytest.mark.parametrize("shape", [(1, 4, 28, 28), (1, 64, 55, 55), (2, 3, 101, 99), (1, 40, 31, 62), (1, 1, 1, 1930)])
+def test_pooled_or_a_wave_each(gpu, orc, shape, eb, sub):
+    check(gpu, orc, [shape, (1, 128, 28, 28)], eb, sub)
