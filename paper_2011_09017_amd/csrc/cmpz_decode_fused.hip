@@ -652,13 +652,25 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
 
 // The fused kernel's plan for one tensor.  Returns false when the shape does not fit it: such tensors
 // take the unfused kernels.  Planes larger than one band need rows of at most kColGroups waves, or, if
-// `wide` rows are asked for, rows of up to 512, sub-blocks of 32 codes and no fewer than kWidePlanes
-// planes: such planes are always shared by the waves of a workgroup, which walk down the plane, and
-// with few planes or the longer chains of longer sub-blocks the passes over memory of the unfused
-// kernels, which spread a plane over the chip, are faster.  Measured on planes of 375x500, fused /
-// unfused: 192 of them 213 / 283 us, 256: 215 / 342, 512: 254 / 812; 128 (with more groups) 289 / 236; with
-// 128 codes per sub-block 256 planes 780 / 328; 64 planes of 700x1100 2122 / 429.
-constexpr uint32_t kWidePlanes = 192;
+// `wide` rows are asked for, rows of up to 512, sub-blocks of 32 codes and enough planes
+// (enough_wide_planes).
+//
+// Wide planes are always shared by the waves of a workgroup, which walk down the plane: with few
+// planes, or the longer chains of longer sub-blocks, the passes over memory of the unfused kernels,
+// which spread a plane over the chip, are faster.  How many planes it takes depends on the bound: with
+// outliers in every band the walk takes three times as long, and the host does not know of them.  So
+// the lines lie where a tight bound loses nothing.  Fused / unfused in us, planes of 375x500 at eb 1e-2,
+// 192 of them: 211 / 284, 512: 252 / 811; at eb 1e-3, 192: 614 / 364, 320: 665 / 570, 448: 673 / 905; planes of
+// 64x384 at eb 1e-3, 320: 108 / 100, 448: 108 / 135.  In planes of one or two rounds of bands the unfused
+// kernels' five launches weigh more: 20x512 at eb 1e-3, 192: 53 / 68, 40x300: 56 / 75.  Tensors larger than
+// the memory-side cache (256 MB) are slower for the unfused kernels: at eb 1e-3 320 planes of 1500x300
+// 1546 / 1904, of 2000x512 3697 / 3648, 256 of them 3567 / 3053.  With 128 codes per sub-block 256 planes of
+// 375x500 take 780 / 328; 64 planes of 700x1100, which need more column groups, 2122 / 429.
+static bool enough_wide_planes(uint32_t planes, uint32_t nbands, uint32_t numel)
+{
+    return planes >= (nbands <= 2u * kWaves ? 192u : numel > (1u << 26) ? 320u : 448u);
+}
+
 bool plan_decode_fused(TensorD *t, uint32_t sub, bool wide)
 {
     const uint32_t H = t->shape[2], W = t->shape[3], HW = H * W, planes = t->shape[0] * t->shape[1];
@@ -673,7 +685,8 @@ bool plan_decode_fused(TensorD *t, uint32_t sub, bool wide)
     } else if (W <= (uint32_t)(kColGroups * kWave) && W <= cap) {
         t->big = 1; t->G = 1; t->Rb = (uint32_t)(cap / W);
         t->nitems = planes;
-    } else if (wide && sub == 32 && W <= (uint32_t)(kWideGroups * kWave * kWaves) && planes >= kWidePlanes) {
+    } else if (wide && sub == 32 && W <= (uint32_t)(kWideGroups * kWave * kWaves) &&
+               enough_wide_planes(planes, (uint32_t)((H + cap / W - 1) / (cap / W)), t->numel)) {
         t->big = 3; t->G = 1; t->Rb = (uint32_t)(cap / W);
         t->nitems = planes;
     } else {

@@ -114,3 +114,13 @@ def test_wide_rows(gpu, orc, shape, sub, eb):
 @pytest.mark.parametrize("shape", [(1, 4, 28, 28), (1, 64, 55, 55), (2, 3, 101, 99), (1, 40, 31, 62), (1, 1, 1, 1930)])
 def test_pooled_or_a_wave_each(gpu, orc, shape, eb, sub):
     check(gpu, orc, [shape, (1, 128, 28, 28)], eb, sub)
+
+
+# the same on either side of the counts of planes from which a workgroup takes them: planes of two rounds of
+# bands, of more, and tensors larger than the memory-side cache
+@pytest.mark.parametrize("shape,eb", [
+    ((1, 191, 24, 512), 1e-2), ((1, 192, 24, 512), 1e-3), ((1, 447, 45, 400), 1e-2), ((1, 448, 45, 400), 1e-3),
+    ((1, 320, 461, 456), 1e-2),
+])
+def test_wide_rows_from_a_count_of_planes_on(gpu, orc, shape, eb):
+    check(gpu, orc, [shape], eb, 32)
