@@ -298,7 +298,7 @@ void group_plan_sweep(BatchC *b, uint32_t cus)
 // Chunks per workgroup of the bit-count and packing kernels, once all tensors of the group are known.
 // Their waves take whole chunks one after the other, so a call of few chunks wants them spread over
 // the chip, one per wave; a workgroup also loads the code table and the offsets, so a large call wants
-// sixteen.  The line is where the next smaller range still gives every compute unit four workgroups.
+// sixteen: the largest of 16, 8 and 4 that gives every compute unit four workgroups, and 4 if none does.
 // Whole compressions with 16 / with 4 or 8 chunks: 49 chunks 55.9 / 38.9 us, 784: 63.1 / 44.1, 3136
 // (4 chunks): 75.7 / 61.2, 9075 (8): 105.4 / 96.5, 12544 (8): 131.0 / 125.2; 25088: 218.0 / 216.5 with 8,
 // and 144 256 chunks are slower with 8 (packing 241 / 254 us).

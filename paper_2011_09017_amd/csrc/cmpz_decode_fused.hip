@@ -56,7 +56,8 @@ template <> struct Cfg<32>  { static constexpr int kLog = 5; };
 
 struct FusedPlan {
     uint32_t big;          // 0: groups of whole planes; 1: one plane per item, bands of rows; 2: the same,
-                           // the four waves of a workgroup on four consecutive bands of one plane
+                           // the four waves of a workgroup on four consecutive bands of one plane; 3: as 2,
+                           // with rows wider than 256
     uint32_t G;            // planes per group (big == 0)
     uint32_t Rb;           // rows per band (big == 1)
     uint32_t nitems;
@@ -695,15 +696,15 @@ bool plan_decode_fused(TensorD *t, uint32_t sub, bool wide)
     return true;
 }
 
-// One launch over the tensors of the group that have a plan (and a second one, of the variant
-// that shares planes between waves, over those with few large planes).  Five workgroups are
+// One launch over the tensors of the group that have a plan (and one each, of the variants that share
+// planes between waves, over those with few large planes and over those with wide rows).  Five workgroups are
 // resident per compute unit.  A small launch gets one round of them (a second round would build its
 // decode tables for little work); a large one up to six rounds, dealt to its tensors in proportion
 // to their elements, so that workgroups of different cost (small planes cost more per element than
 // large ones) even out and the chip does not idle while the last round's slowest workgroup
 // finishes.  Measured on the ResNet-18-shaped stream (17 tensors, 591 M elements): 1.00 / 0.96 /
 // 0.93 / 0.94 / 0.94 / 0.94 ms for 3 / 4 / 5 / 6 / 8 / 12 rounds.  No more than a tensor has items
-// for, at least one.  The two launches run one after the other: each deals its own rounds (dealt
+// for, at least one.  The launches run one after the other: each deals its own rounds (dealt
 // from a common count, the 4096 shared planes of that stream at batch 64 got 448 workgroups of the
 // 1280 that fit and took 366 us, with 1280 about 240; as plain items of the other launch about 150).
 void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st)
@@ -715,9 +716,13 @@ void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st
         // plane, its waves side by side on the plane's bands.  It has to pay for its barriers, for
         // waves without a band in the plane's last round and for columns that do not fill four
         // waves, so the fewer bands a plane has the sooner a wave per plane is the better one.
-        // Measured, shared / a wave per plane: planes of 224x224 (25 bands), 3072 of them 249 / 282 us,
-        // 4480: 359 / 356; 160x160 (14), 2304: 108 / 139; 112x112 (7), 2304: 66 / 73, 3072: 81 / 77,
-        // 3840: 102 / 86; 56x56 (2), 768: 22 / 25, 1536: 29 / 27, 2624: 42 / 31.
+        // Measured in us, shared / a wave per plane, 32 codes per sub-block: planes of 224x224 (25 bands),
+        // 3072 of them 242 / 280, 4096: 322 / 320, 4864: 378 / 360, 5120, a wave for each: 396 / 363, 5632, more than
+        // that: 436 / 518; 160x160 (14), 3072: 141 / 151, 4096: 184 / 175; 112x112 (7), 2304: 63 / 73,
+        // 2560: 71 / 73, 3072: 76 / 74; 56x56 (2), 1024: 23 / 24, 1280: 26 / 26, 2624: 40 / 29.
+        // The lines were drawn for 32 codes.  With the longer chains of 64 and 128 they could lie higher:
+        // 224x224, 4480: 458 / 495 and 631 / 664; 112x112, 2560: 93 / 109 and 120 / 162, 3840: 134 / 119 and 169 / 168;
+        // 56x56, 1280: 32 / 37 and 41 / 50, 1792: 39 / 38 and 53 / 51.
         if (!t.nitems || !t.big || t.big == 3) continue;
         const uint32_t nbands = (t.shape[2] + t.Rb - 1) / t.Rb;
         const uint64_t waves = slots * kWaves;

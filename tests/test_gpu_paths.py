@@ -76,10 +76,38 @@ def test_codebook_around_its_window(gpu, orc, nsym, weights):
 @pytest.mark.parametrize("zero_blocks", [0, 1])
 def test_ranges_of_few_chunks(gpu, orc, chunks, extra, zero_blocks):
     """Tensors that end at or beside the end of a chunk and of a workgroup's range of chunks, alone in a
-    call and after another tensor."""
+    call and after another tensor.  Calls as small as these have ranges of four chunks."""
     n = chunks * 4096 + extra
     check(gpu, orc, [(1, 1, 1, n)], 1e-2, 64, zero_blocks, p_zero=0.8)
     check(gpu, orc, [(2, 3, 37, 41), (1, n, 1, 1), (1, 1, 64, 65)], 1e-3, 32, zero_blocks, p_zero=0.8)
+
+
+@pytest.mark.parametrize("per_range,zero_blocks", [(8, 0), (8, 1), (16, 0), (16, 1)])
+def test_ranges_of_8_and_16_chunks(gpu, orc, per_range, zero_blocks):
+    """Calls of so many chunks that a range holds 8 or 16 of them: one large tensor, and small ones behind it
+    that end inside, at and beside the end of a range."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    fill = 4 * cus * per_range                          # chunks from which on the ranges are that long
+    sizes = [4096 * c + extra for c in (1, 3, per_range - 1, per_range, per_range + 1, 2 * per_range) for extra in (-1, 0, 1)]
+    xs = [torch.zeros((fill, 64, 8, 8), device="cuda")]         # a chunk per sample
+    xs += [activation((1, 1, 1, n), 5, 0.8, seed=n).cuda() for n in sizes]
+    xs[0][..., ::7] = 0.3
+    ebs = [1e-2] * len(xs)
+    ctx = gpu.Context(sub=32, max_numel=sum(x.numel() for x in xs), zero_blocks=zero_blocks)
+    bufs, lens, rc = ctx.compress_batch(xs, ebs)
+    assert rc == 0
+    outs = [torch.full(x.shape, float("nan"), device="cuda") for x in xs]
+    ctx.decompress_batch(bufs, lens, [x.shape for x in xs], ebs, outs=outs)
+    assert ctx.last_status() == 0
+    assert bool(((outs[0] - xs[0]).abs() <= 1e-2).all())
+    cfg = orc.Config(sub=32, zero_blocks=zero_blocks)
+    for x, buf, size in zip(xs[1:], bufs[1:], lens[1:]):
+        orc_rc, obuf, osize, _ = orc.compress(x.cpu().numpy(), 1e-2, cfg)
+        assert orc_rc == 0 and size == osize
+        assert np.array_equal(buf[:size].cpu().numpy(), obuf), x.shape
+    for x, y, buf, size in zip(xs[1:], outs[1:], bufs[1:], lens[1:]):
+        orc_rc, oy = orc.decompress(buf[:size].cpu().numpy(), x.shape, 1e-2, cfg)
+        assert orc_rc == 0 and np.array_equal(y.cpu().numpy().view(np.uint32), oy.view(np.uint32))
 
 
 # sub-blocks of 64 and 128 codes, bands decoded by another wave than their own: rows that end inside a
@@ -116,8 +144,8 @@ def test_pooled_or_a_wave_each(gpu, orc, shape, eb, sub):
     check(gpu, orc, [shape, (1, 128, 28, 28)], eb, sub)
 
 
-# the same on either side of the counts of planes from which a workgroup takes them: planes of two rounds of
-# bands, of more, and tensors larger than the memory-side cache
+# wide rows on either side of the counts of planes from which the fused kernel takes them: planes of two rounds
+# of bands, of more, and a tensor larger than the memory-side cache
 @pytest.mark.parametrize("shape,eb", [
     ((1, 191, 24, 512), 1e-2), ((1, 192, 24, 512), 1e-3), ((1, 447, 45, 400), 1e-2), ((1, 448, 45, 400), 1e-3),
     ((1, 320, 461, 456), 1e-2),
