@@ -61,18 +61,18 @@ MEASURED_TRAFFIC = {
     ("cfg5_resnet18_stream", 32, 1e-2): {
         "profile": "profiles/hbm_traffic_cfg5_resnet18_stream.txt",
         "per_elem": {
-            "k_quant_lorenzo_split_hist": 4.0178 + 1.0509,     # 8-bit symbols in the scratch
+            "k_quant_lorenzo_split_hist": 4.0177 + 1.0509,     # 8-bit symbols in the scratch
             "k_lengths": 1.0088 + 0.0672,
-            "k_pack": 1.0138 + 0.6639,
-            "k_decode_fused": 0.8330 + 4.0086,
+            "k_pack": 1.0140 + 0.6639,
+            "k_decode_fused": 0.8347 + 4.0091,
         },
         # vector instructions per element and the fraction of the kernel's time its vector units are busy
         # (profiles/instruction_counters_cfg5_resnet18_stream.txt)
         "valu": {
-            "k_quant_lorenzo_split_hist": (26.48, 0.688),
+            "k_quant_lorenzo_split_hist": (26.48, 0.680),
             "k_lengths": (2.98, 0.355),
-            "k_pack": (12.27, 0.831),
-            "k_decode_fused": (46.83, 0.829),
+            "k_pack": (12.27, 0.828),
+            "k_decode_fused": (46.02, 0.811),
         },
     },
 }

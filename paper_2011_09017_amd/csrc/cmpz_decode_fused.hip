@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     // a fixed count, so that it unrolls and the look-ahead word is not waited for in the step that
     // fetches it.  64x256x56x56 at eb 1e-2: 236 -> 166 us at 128 codes, 147 -> 113 at 64 (pooled with
     // the loop's count per lane: 226 and 135; a raised wave priority: 172 and 116); at eb 5e-3,
-    // with its longer codes, 261 -> 232 us at 128.
+    // with its longer codes, 261 -> 232 us at 128 (217 with the search in decode_lds as it is).
     constexpr bool kPool = kND < kWave;
     constexpr int kPoolWaves = kWave / kND;               // bands decoded together
     // But a step waits for the canonical search as soon as one of its lanes needs it, and a pooled wave
