@@ -710,24 +710,30 @@ bool plan_decode_fused(TensorD *t, uint32_t sub, bool wide)
 void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st)
 {
     const uint64_t slots = 5ull * cus;
+    const uint64_t waves = slots * kWaves;
     for (uint32_t k = 0; k < b.n; ++k) {
         TensorD &t = b.t[k];
         // Few large planes (one wave per plane would leave the chip half empty): a workgroup per
         // plane, its waves side by side on the plane's bands.  It has to pay for its barriers, for
         // waves without a band in the plane's last round and for columns that do not fill four
-        // waves, so the fewer bands a plane has the sooner a wave per plane is the better one.
-        // Measured in us, shared / a wave per plane, 32 codes per sub-block: planes of 224x224 (25 bands),
-        // 3072 of them 242 / 280, 4096: 322 / 320, 4864: 378 / 360, 5120, a wave for each: 396 / 363, 5632, more than
-        // that: 436 / 518; 160x160 (14), 3072: 141 / 151, 4096: 184 / 175; 112x112 (7), 2304: 63 / 73,
-        // 2560: 71 / 73, 3072: 76 / 74; 56x56 (2), 1024: 23 / 24, 1280: 26 / 26, 2624: 40 / 29.
-        // The lines were drawn for 32 codes.  With the longer chains of 64 and 128 they could lie higher:
-        // 224x224, 4480: 458 / 495 and 631 / 664; 112x112, 2560: 93 / 109 and 120 / 162, 3840: 134 / 119 and 169 / 168;
-        // 56x56, 1280: 32 / 37 and 41 / 50, 1792: 39 / 38 and 53 / 51.
+        // waves: with two or three bands a plane the most.  Shared up to the count of planes from which
+        // a wave each is no slower at either of two bounds.  In us, shared / a wave each (eb 1e-2; eb 1e-3):
+        //   2 bands (56x56), 32 codes: 1280 planes 26 / 26; 48 / 59, 1536: 27 / 26; 62 / 59; 128 codes,
+        //     1280: 41 / 51; 85 / 125, 1536: 50 / 51; 134 / 123
+        //   3 bands (64x64), 32 codes: 1792: 32 / 33; 69 / 71, 2048: 36 / 33; 72 / 72; 128 codes,
+        //     2560: 71 / 78; 147 / 160, 3072: 77 / 78; 172 / 161
+        //   4 bands (80x80), 32 codes: 3584: 58 / 56; 125 / 128, 4096: 67 / 56; 138 / 128; 128 codes,
+        //     4608: 112 / 110; 248 / 273, 5056: 128 / 111; 297 / 271
+        //   7 bands (112x112), 32 codes: 3584: 88 / 82; 206 / 217, 4096: 102 / 83; 236 / 218; 128 codes,
+        //     3584: 160 / 168; 426 / 457, 4096: 174 / 169; 514 / 464
+        //   25 bands (224x224), 32 codes: 3584: 284 / 311; 669 / 757, 4096: 322 / 320; 770 / 774; 28 bands,
+        //     128 codes, 4608: 634 / 668; 1450 / 1667, 5056: 707 / 673; 1624 / 1665
+        // (of 5120 waves; between them 5 and 9 bands would do with fewer planes, 3072 and 3584)
         if (!t.nitems || !t.big || t.big == 3) continue;
         const uint32_t nbands = (t.shape[2] + t.Rb - 1) / t.Rb;
-        const uint64_t waves = slots * kWaves;
-        const uint64_t limit = nbands >= 12u ? waves : nbands > 4u ? waves / 2u : waves / 4u;
-        t.big = (nbands > 1u && t.nitems < limit) ? 2u : 1u;
+        const uint64_t tenths = nbands <= 2u ? 3u : nbands == 3u ? (b.sub == 32u ? 4u : 6u) :
+                                b.sub == 32u || (nbands > 4u && nbands <= 16u) ? 8u : 10u;
+        t.big = (nbands > 1u && 10ull * t.nitems < tenths * waves) ? 2u : 1u;
     }
     for (uint32_t shared = 0; shared < 3; ++shared) {
         auto in_launch = [&](const TensorD &t) { return t.nitems && (t.big < 2u ? 0u : t.big - 1u) == shared; };

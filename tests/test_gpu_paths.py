@@ -49,6 +49,14 @@ def test_shared_planes_or_one_wave_each(gpu, orc, shapes):
     check(gpu, orc, shapes, 1e-2, 32)
 
 
+# the same at the lines as they depend on the number of bands: two bands, three, four (a full round), five
+@pytest.mark.parametrize("sub", [32, 128])
+@pytest.mark.parametrize("shape", [(5, 307, 46, 45), (3, 512, 46, 45), (23, 89, 70, 64), (4, 512, 70, 64), (6, 512, 70, 64),
+                                   (8, 512, 70, 90), (8, 512, 86, 70)])
+def test_shared_planes_by_their_bands(gpu, orc, shape, sub):
+    check(gpu, orc, [shape], 1e-2, sub)
+
+
 @pytest.mark.parametrize("nsym", [4, 62, 64, 66, 126, 128, 130, 500])
 @pytest.mark.parametrize("weights", [(1,), (1, 2, 3, 4, 8), (1, 1, 50, 2000)])
 def test_codebook_around_its_window(gpu, orc, nsym, weights):
