@@ -735,6 +735,25 @@ void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st
                                 b.sub == 32u || (nbands > 4u && nbands <= 16u) ? 8u : 10u;
         t.big = (nbands > 1u && 10ull * t.nitems < tenths * waves) ? 2u : 1u;
     }
+    // A workgroup that walks down a tall plane keeps its launch going while most of the chip idles, if
+    // there is little else in it.  Large planes of a count between the lines above and the chip's waves go
+    // into that launch then, rather than into one of their own that it would add to.  Counted in rounds
+    // of bands: at most a quarter of the walk's time on all slots taken without them, and one and a half
+    // times that time with them.  In us, together / apart: 16 planes of 224x224 (7 rounds) beside 2048 of
+    // 56x56 (1) 64 / 90, with 128 codes at eb 1e-3 389 / 555; beside 3 x 4096 of them 137 / 144 and 584 / 813; 256 of
+    // 112x112 (2) beside 2048 of 56x56 42 / 55, but 512 of them 71 / 59; 64 of 56x56 beside 4096 72 / 50.
+    uint64_t walk = 0, load = 0, between = 0;
+    auto undecided = [&](const TensorD &t) { return t.nitems && t.big == 1u && t.shape[2] > t.Rb && t.nitems < waves; };
+    for (uint32_t k = 0; k < b.n; ++k) {
+        const TensorD &t = b.t[k];
+        if (!t.nitems || !t.big || t.big == 3u) continue;
+        const uint64_t rounds = ((uint64_t)t.shape[2] + t.Rb * kWaves - 1) / (t.Rb * kWaves);
+        if (t.big == 2u) { load += rounds * t.nitems; walk = rounds > walk ? rounds : walk; }
+        else if (undecided(t)) between += rounds * t.nitems;
+    }
+    if (4u * load <= walk * slots && 2u * between <= 3u * walk * slots)
+        for (uint32_t k = 0; k < b.n; ++k)
+            if (undecided(b.t[k])) b.t[k].big = 2u;
     for (uint32_t shared = 0; shared < 3; ++shared) {
         auto in_launch = [&](const TensorD &t) { return t.nitems && (t.big < 2u ? 0u : t.big - 1u) == shared; };
         uint64_t total = 0;

@@ -57,6 +57,13 @@ def test_shared_planes_by_their_bands(gpu, orc, shape, sub):
     check(gpu, orc, [shape], 1e-2, sub)
 
 
+# a few tall planes beside large planes that they take into their launch, and beside more of them than they take
+@pytest.mark.parametrize("sub", [32, 128])
+@pytest.mark.parametrize("count", [1, 6])
+def test_tall_planes_beside_large_ones(gpu, orc, count, sub):
+    check(gpu, orc, [(1, 5, 150, 130)] + [(4, 512, 46, 45)] * count + [(3, 50, 14, 14)], 1e-2, sub)
+
+
 @pytest.mark.parametrize("nsym", [4, 62, 64, 66, 126, 128, 130, 500])
 @pytest.mark.parametrize("weights", [(1,), (1, 2, 3, 4, 8), (1, 1, 50, 2000)])
 def test_codebook_around_its_window(gpu, orc, nsym, weights):
