@@ -404,15 +404,26 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                 };
                 bool lbad = false;
                 uint32_t end = spos + sb;
-                if (role == 0u) {
+                if (role != 0u) {
+                    // seldom more than one lane, so one after the other with uniform counts: the loop unrolls then
+                    // (2 planes of 38x37, 128 codes at eb 1e-3: 42.6 -> 39.6 us)
+                    unsigned long long rest = __ballot((fl & 0xb000u) == 0x8000u);
+                    while (rest) {
+                        const int l = __ffsll((long long)rest) - 1;
+                        rest &= rest - 1;
+                        const uint32_t to_l = (uint32_t)__builtin_amdgcn_readlane((int)to, l),
+                                       from_l = (uint32_t)__builtin_amdgcn_readlane((int)from, l);
+                        if (lane == l) {
+                            const uint32_t e = decode_lds<false>(T, lds.Ss, spos, to_l, from_l, put, lbad);
+                            if (fl & 0x800u) end = e;
+                        }
+                    }
+                } else {
                     if ((fl & 0xa000u) == 0xa000u) {
                         for (uint32_t k = from; k < to; ++k) put(k, 0);
                     } else if ((fl & 0x9000u) == 0x9000u) {
                         end = decode_lds<true>(T, lds.Ss, spos, (uint32_t)SUB, 0u, put, lbad);
                     }
-                } else if ((fl & 0xb000u) == 0x8000u) {
-                    const uint32_t e = decode_lds<false>(T, lds.Ss, spos, to, from, put, lbad);
-                    if (fl & 0x800u) end = e;
                 }
                 bad |= lbad || end != spos + sb;
             }

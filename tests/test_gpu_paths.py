@@ -154,7 +154,8 @@ def test_wide_rows(gpu, orc, shape, sub, eb):
 # the pool's decodes beside it: in the last of two bands, in a band of its own, behind planes of two bands
 @pytest.mark.parametrize("sub", [64, 128])
 @pytest.mark.parametrize("eb", [1e-3, 1.8e-3, 2.5e-3, 1e-2])
-@pytest.mark.parametrize("shape", [(1, 4, 28, 28), (1, 64, 55, 55), (2, 3, 101, 99), (1, 40, 31, 62), (1, 1, 1, 1930)])
+@pytest.mark.parametrize("shape", [(1, 4, 28, 28), (1, 64, 55, 55), (2, 3, 101, 99), (1, 40, 31, 62), (1, 1, 1, 1930),
+                                   (1, 2, 9, 7), (1, 2, 38, 37)])
 def test_pooled_or_a_wave_each(gpu, orc, shape, eb, sub):
     check(gpu, orc, [shape, (1, 128, 28, 28)], eb, sub)
 
