@@ -168,7 +168,10 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     // it lack the carry), .y = the carry
     uint2 *RC = reinterpret_cast<uint2 *>(S + kStagePad);
     const uint32_t payload_units = T.payload_units, n_outl = T.n_outliers;
-    const bool pool = kPool && (uint32_t)__builtin_amdgcn_readfirstlane((int)T.searched) < kPoolSearched;   // uniform in the workgroup
+    // (uniform in the workgroup; nor where a band's share of the payload does not fit the staging buffer)
+    const uint32_t band_n = pl.big ? pl.Rb * a.W : pl.G * a.HW;
+    const bool pool = kPool && (uint32_t)__builtin_amdgcn_readfirstlane((int)T.searched) < kPoolSearched &&
+                      (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)T.payload_units) * 128u * band_n <= (uint64_t)a.numel * (kStageWords * 32u);
 
     const uint32_t W = a.W, H = a.H, HW = a.HW;
     const uint32_t *__restrict__ chunk_off = reinterpret_cast<const uint32_t *>(a.buf + a.lay.off_chunk_off);
@@ -334,6 +337,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
         uint32_t my_reset = 0;
         // (a band with outliers: what the lane needs to sum its rows once the outliers are patched in)
         uint32_t late_klo = 0, late_khi = 0, late_w = 0;
+        bool together = false;                           // the bands of this round are decoded by the pool's waves
         if (pool) {
             // What the pool's waves need to know of a sub-block, in the (still unused) slot that will
             // take its residuals: its bit position in the staged payload, the elements of it that
@@ -376,15 +380,22 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                     bad |= lbad;
                 }
                 RT *rec = R + lane * (SUB + 1);
+                // (a band that is not staged says so in its first lane's pad)
+                if (lane == 0 && cur.valid && !staged) flags = 1u;
                 rec[0] = (RT)spos; rec[1] = (RT)(klo | (khi << 8)); rec[2] = (RT)sbits; rec[SUB] = (RT)(w_first | flags);
             }
             __syncthreads();
+            // A band that did not fit the staging buffer is decoded from memory, which takes longest and would
+            // come on top: then every wave of the workgroup decodes its own band, side by side.
+            together = true;
+#pragma unroll
+            for (int j = 0; j < kWaves; ++j) together &= (uint16_t)lds.Rs[j][SUB] != 1u;      // uniform in the workgroup
             // The pool's wave changes from round to round, so that the four SIMDs share the work.  The
             // tensor's last sub-block, if incomplete, is left to the wave behind it, which would wait: in
             // the same wave its steps would come on top (4 planes of 28x28, 128 codes: 36 -> 25 us).
             const uint32_t turn = round + blockIdx.x + (blockIdx.x >> 8);
             const uint32_t role = ((uint32_t)wv - turn) & (uint32_t)(kPoolWaves - 1);
-            if (role < 2u) {                                                          // uniform in the wave
+            if (together && role < 2u) {                                              // uniform in the wave
                 const uint32_t j = ((uint32_t)wv & ~(uint32_t)(kPoolWaves - 1)) + (uint32_t)lane / kND;    // the band's wave
                 RT *my = lds.Rs[j] + ((uint32_t)lane & (kND - 1)) * (SUB + 1);
                 const uint32_t spos = (uint16_t)my[0] + j * (kStageWords * 32u), kk = (uint16_t)my[1],
@@ -427,10 +438,10 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                 }
                 bad |= lbad || end != spos + sb;
             }
-            __syncthreads();
-            if (pooled && folded) my_tail = R[lane * (SUB + 1) + khi - 1u];
+            __syncthreads();                             // (also before the next round's records: all have seen these)
+            if (together && pooled && folded) my_tail = R[lane * (SUB + 1) + khi - 1u];
         }
-        if (lane < (int)nsb && (!pool || !staged)) {
+        if (lane < (int)nsb && !together) {
             const uint32_t g = sb0 + lane;
             const uint32_t uu0 = fa.uu0, uu1 = fa.uu1;
             bool lbad = !(uu0 <= uu1 && uu1 <= payload_units);

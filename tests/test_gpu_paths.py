@@ -20,9 +20,10 @@ def gpu():
     return binding
 
 
-def check(gpu, orc, shapes, eb, sub, zero_blocks=0, k=5, p_zero=0.6):
+def check(gpu, orc, shapes, eb, sub, zero_blocks=0, k=5, p_zero=0.6, xs=None):
     """One batch call over `shapes`, both directions."""
-    xs = [activation(s, k, p_zero, seed=sum(s) + i) for i, s in enumerate(shapes)]
+    if xs is None:
+        xs = [activation(s, k, p_zero, seed=sum(s) + i) for i, s in enumerate(shapes)]
     ctx = gpu.Context(sub=sub, max_numel=sum(x.numel() for x in xs), zero_blocks=zero_blocks)
     bufs, sizes, rc = ctx.compress_batch([x.cuda() for x in xs], [eb] * len(xs))
     assert rc == 0
@@ -158,6 +159,19 @@ def test_wide_rows(gpu, orc, shape, sub, eb):
                                    (1, 2, 9, 7), (1, 2, 38, 37)])
 def test_pooled_or_a_wave_each(gpu, orc, shape, eb, sub):
     check(gpu, orc, [shape, (1, 128, 28, 28)], eb, sub)
+
+
+# bands whose payload exceeds the staging buffer beside bands that fit it, in one workgroup: blocks of rows
+# without structure (about ten bits a code) among zeros, in a quarter, a half and three quarters of the tensor
+@pytest.mark.parametrize("sub", [32, 64, 128])
+@pytest.mark.parametrize("dense", [1, 2, 3])
+@pytest.mark.parametrize("shape,block", [((1, 24, 40, 48), 40), ((2, 5, 90, 60), 11), ((1, 50, 17, 13), 150), ((6, 400, 50, 45), 23)])
+def test_bands_beyond_the_staging_buffer(gpu, orc, shape, block, dense, sub):
+    rng = np.random.default_rng(dense)
+    rows = np.arange(int(np.prod(shape[:3])))
+    x = rng.uniform(0, 4.5, (rows.size, shape[3])).astype(np.float32)
+    x[(rows // block) % 4 >= dense] = 0
+    check(gpu, orc, [shape], 1e-2, sub, xs=[torch.from_numpy(x.reshape(shape))])
 
 
 # wide rows on either side of the counts of planes from which the fused kernel takes them: planes of two rounds
