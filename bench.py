@@ -63,16 +63,16 @@ MEASURED_TRAFFIC = {
         "per_elem": {
             "k_quant_lorenzo_split_hist": 4.0177 + 1.0509,     # 8-bit symbols in the scratch
             "k_lengths": 1.0088 + 0.0672,
-            "k_pack": 1.0140 + 0.6639,
-            "k_decode_fused": 0.8347 + 4.0091,
+            "k_pack": 1.0138 + 0.6639,
+            "k_decode_fused": 0.8349 + 4.0088,
         },
         # vector instructions per element and the fraction of the kernel's time its vector units are busy
         # (profiles/instruction_counters_cfg5_resnet18_stream.txt)
         "valu": {
-            "k_quant_lorenzo_split_hist": (26.48, 0.680),
+            "k_quant_lorenzo_split_hist": (26.48, 0.684),
             "k_lengths": (2.98, 0.355),
-            "k_pack": (12.27, 0.828),
-            "k_decode_fused": (46.02, 0.811),
+            "k_pack": (12.27, 0.830),
+            "k_decode_fused": (46.02, 0.814),
         },
     },
 }

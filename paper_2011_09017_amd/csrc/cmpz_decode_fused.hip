@@ -32,7 +32,7 @@
 // sum their rows in LDS, and the rest is the same.
 // With sub-blocks of 64 or 128 codes the bands of two or four waves are decoded by
 // one wave (a band alone would fill 32 or 16 of its lanes), two barriers per band,
-// unless the codebook sends too many codes past the tables.
+// unless the codebook sends too many codes past the tables or a band does not fit the staging buffer.
 // Software pipeline: the bit counts of the next band are fetched during the
 // decode of the current one, and its payload during the column pass.
 #include "cmpz_decode_core.h"
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     // a fixed count, so that it unrolls and the look-ahead word is not waited for in the step that
     // fetches it.  64x256x56x56 at eb 1e-2: 236 -> 166 us at 128 codes, 147 -> 113 at 64 (pooled with
     // the loop's count per lane: 226 and 135; a raised wave priority: 172 and 116); at eb 5e-3,
-    // with its longer codes, 261 -> 232 us at 128 (217 with the search in decode_lds as it is).
+    // with its longer codes, 261 -> 232 us at 128 (220 with the search in decode_lds as it is).
     constexpr bool kPool = kND < kWave;
     constexpr int kPoolWaves = kWave / kND;               // bands decoded together
     // But a step waits for the canonical search as soon as one of its lanes needs it, and a pooled wave
