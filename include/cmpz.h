@@ -143,7 +143,7 @@ int cmp_compress_batch(cmp_ctx *ctx, int n, const float *const *d_x, const int64
 /* cmp_compress for callers that cannot allocate device memory and therefore cannot hold a
  * context: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * It runs the same kernels as cmp_compress and gives the same container, with its scratch in an
- * array that is part of the library's device image: about 11.7 MB on every GPU the library is
+ * array that is part of the library's device image: about 14.4 MB on every GPU the library is
  * loaded on, held until the process ends.  The call allocates nothing (no hipMalloc, no
  * hipFree, no pinned memory) and does not synchronise.
  *   device   the GPU of d_x and d_out;

@@ -21,8 +21,8 @@ using namespace cmpz;
 // Device memory of a context, carved out of one block (from hipMalloc in cmp_create).
 struct Scratch {
     // compression (see BatchC)
-    uint16_t   *sym;
-    uint32_t   *hist, *hist_copy, *enc32, *outl_cnt, *wide, *chunk_bits, *range_units, *range_outl, *range_bits, *status;
+    uint16_t   *sym, *chunk_hist, *chunk_hist_all;
+    uint32_t   *hist, *hist_copy, *enc32, *outl_cnt, *has_all, *wide, *chunk_bits, *range_units, *range_outl, *range_bits, *status;
     uint8_t    *lens;
     uint64_t   *codes;
     TensorMeta *tmeta;
@@ -93,7 +93,7 @@ Layout make_layout(uint64_t numel, const cmp_config &c) { return cmpz::make_layo
 
 // Carves the scratch of a context for `max_numel` elements per call out of a block starting at
 // `base` (NULL: only the size is wanted).  Returns the bytes needed; *zero_from is the offset
-// from which the block must start out as zeros (everything but the symbols).
+// from which the block must start out as zeros (everything but the symbols and the chunks' histograms).
 uint64_t carve_scratch(Scratch *sc, uint8_t *base, uint64_t max_numel, uint64_t *zero_from)
 {
     Scratch s;
@@ -102,6 +102,8 @@ uint64_t carve_scratch(Scratch *sc, uint8_t *base, uint64_t max_numel, uint64_t 
     uint64_t off = 0;
     auto carve = [&](uint64_t bytes) { uint64_t o = off; off = align_up(off + bytes, 256); return base + o; };
     s.sym = reinterpret_cast<uint16_t *>(carve(2 * (s.max_chunks * kChunk + 16)));   // whole chunks: readable past numel
+    s.chunk_hist = reinterpret_cast<uint16_t *>(carve(2ull * 256 * s.max_chunks));
+    s.chunk_hist_all = reinterpret_cast<uint16_t *>(carve(2ull * kMaxSym * s.max_chunks));
     if (zero_from) *zero_from = off;
     s.hist = reinterpret_cast<uint32_t *>(carve(4ull * kMaxSym * kHistCopies * kBatchMax));
     s.hist_copy = reinterpret_cast<uint32_t *>(carve(4ull * kMaxSym * kBatchMax));
@@ -109,6 +111,7 @@ uint64_t carve_scratch(Scratch *sc, uint8_t *base, uint64_t max_numel, uint64_t 
     s.codes = reinterpret_cast<uint64_t *>(carve(8ull * kMaxSym * kBatchMax));
     s.enc32 = reinterpret_cast<uint32_t *>(carve(4ull * kMaxSym * kBatchMax));
     s.outl_cnt = reinterpret_cast<uint32_t *>(carve(4 * s.max_chunks));
+    s.has_all = reinterpret_cast<uint32_t *>(carve(4 * s.max_chunks));
     s.wide = reinterpret_cast<uint32_t *>(carve(16 * s.max_chunks));
     s.chunk_bits = reinterpret_cast<uint32_t *>(carve(4 * s.max_chunks));
     s.range_units = reinterpret_cast<uint32_t *>(carve(4 * s.max_ranges));
@@ -252,9 +255,9 @@ void group_begin(BatchC *b, const cmp_config &cfg, const Scratch &s)
     std::memset(b, 0, sizeof(*b));
     b->radius = cfg.radius; b->sub = cfg.sub; b->guard_shift = cfg.guard_shift;
     b->zero_blocks = (cfg.flags & CMP_F_ZERO_BLOCKS) ? 1u : 0u;
-    b->sym = s.sym; b->hist = s.hist; b->hist_copy = s.hist_copy; b->lens = s.lens; b->codes = s.codes;
+    b->sym = s.sym; b->chunk_hist = s.chunk_hist; b->chunk_hist_all = s.chunk_hist_all; b->has_all = s.has_all; b->hist = s.hist; b->hist_copy = s.hist_copy; b->lens = s.lens; b->codes = s.codes;
     b->enc32 = s.enc32; b->outl_cnt = s.outl_cnt; b->wide = s.wide; b->chunk_bits = s.chunk_bits;
-    b->sym_off = cfg.radius > 128 ? cfg.radius - 128 : 0;
+    b->sym_off = byte_form_base(cfg.radius);
     b->range_units = s.range_units; b->range_outl = s.range_outl; b->range_bits = s.range_bits;
     b->tmeta = s.tmeta; b->status = s.status;
 }
@@ -287,31 +290,45 @@ void group_plan_sweep(BatchC *b, uint32_t cus)
     const uint32_t want = slots * rounds;
     b->sweep_chunks = (b->total_chunks + want - 1) / want;
     if (b->sweep_chunks < 1) b->sweep_chunks = 1;
+    if (b->sweep_chunks > kRunMax) b->sweep_chunks = kRunMax;
     b->sweep_wgs = 0;
     for (uint32_t k = 0; k < b->n; ++k) {
         TensorC &t = b->t[k];
         t.sweep_base = b->sweep_wgs;
+        t.run = sweep1_tiled_fits(t.shape[3]) ? b->sweep_chunks : kUntiledChunks;
         if (sweep1_tiled_fits(t.shape[3])) b->sweep_wgs += (t.nchunks + b->sweep_chunks - 1) / b->sweep_chunks;
     }
 }
 
-// Chunks per workgroup of the bit-count and packing kernels, once all tensors of the group are known.
-// Their waves take whole chunks one after the other, so a call of few chunks wants them spread over
-// the chip, one per wave; a workgroup also loads the code table and the offsets, so a large call wants
-// sixteen: the largest of 16, 8 and 4 that gives every compute unit four workgroups, and 4 if none does.
-// Whole compressions with 16 / with 4 or 8 chunks: 49 chunks 55.9 / 38.9 us, 784: 63.1 / 44.1, 3136
-// (4 chunks): 75.7 / 61.2, 9075 (8): 105.4 / 96.5, 12544 (8): 131.0 / 125.2; 25088: 218.0 / 216.5 with 8,
-// and 144 256 chunks are slower with 8 (packing 241 / 254 us).
+// Chunks per workgroup of the bit-count and packing kernels, once all tensors of the group are known:
+// a multiple of four, one for each wave.  Five workgroups are resident per compute unit, and a launch
+// takes as many rounds of them as it has workgroups for, each as long as a wave's chunks and what a
+// workgroup needs for the code table and the offsets (about a quarter of a chunk of a wave): of 4 to 28 chunks
+// the number with the least of that.  Both kernels together, with 4 / 8 / 12 / 16 / 20 / 24 / 28 / 32 chunks:
+//   49 chunks       19 / 24 / 28 / 31 / 35 / 39 / 43 / 46 us
+//   12544 (sub 128) 53 / 54 / 54 / 60 / 65 / 68 / 71 / 79
+//   25088           76 / 70 / 70 / 71 / 64 / 71 / 74 / 79
+//   31360           91 / 84 / 83 / 81 / 84 / 90 / 79 / 80
+//   36064           132 / 117 / 113 / 111 / 120 / 119 / 128 / 114
+//   144 256         418 / 342 / 317 / 306 / 301 / 299 / 301 / 297
 void group_plan_pack(BatchC *b, uint32_t cus)
 {
-    uint32_t pc = kPackChunks;
-    while (pc > kPackChunksMin && b->total_chunks < 4u * cus * pc) pc /= 2;
-    b->pack_chunks = pc;
+    const uint32_t slots = 5u * cus;
+    auto workgroups = [&](uint32_t pc) -> uint64_t {
+        uint64_t n = 0;
+        for (uint32_t k = 0; k < b->n; ++k) n += (b->t[k].nchunks + pc - 1) / pc;
+        return n;
+    };
+    uint64_t least = ~0ull;
+    for (uint32_t pc = kPackChunksMin; pc <= kPackChunks; pc += kPackChunksMin) {
+        const uint64_t cost = (workgroups(pc) + slots - 1) / slots * (pc + 1u);
+        if (cost <= least) { least = cost; b->pack_chunks = pc; }
+    }
     b->pack_wgs = 0;
     for (uint32_t k = 0; k < b->n; ++k) {
         TensorC &t = b->t[k];
         t.pack_base = b->pack_wgs;
-        b->pack_wgs += (t.nchunks + pc - 1) / pc;
+        b->pack_wgs += (t.nchunks + b->pack_chunks - 1) / b->pack_chunks;
     }
 }
 
@@ -398,7 +415,8 @@ int cmp_compress(cmp_ctx *ctx, const float *d_x, const int64_t shape[4], float e
 // the process ends.  Host code never uses the array's name as an address: every device has its
 // own copy at its own address, looked up once (static_scratch_of) and kept.
 constexpr uint64_t kStaticMaxNumel = CMP_STATIC_MAX_NUMEL;
-constexpr uint64_t kStaticBytes    = 2 * (kStaticMaxNumel + (uint64_t)(kBatchMax + 1) * kChunk) + (3ull << 20);
+constexpr uint64_t kStaticChunks   = kStaticMaxNumel / kChunk + kBatchMax + 1;
+constexpr uint64_t kStaticBytes    = 2 * kStaticChunks * (kChunk + 256 + kMaxSym) + (3ull << 20);
 static __device__ __align__(256) __attribute__((used)) unsigned char scratch[kStaticBytes];
 
 namespace {
@@ -709,7 +727,7 @@ int cmp_debug_stage(cmp_ctx *ctx, int which, const void **d_ptr, size_t *bytes)
         DeviceGuard guard(ctx->device);
         if (!guard.ok) return CMP_E_HIP;
         if (hipDeviceSynchronize() != hipSuccess) return CMP_E_HIP;
-        launch_widen(ctx->s.sym, ctx->s.wide, ctx->cfg.radius > 128 ? ctx->cfg.radius - 128 : 0,
+        launch_widen(ctx->s.sym, ctx->s.wide, byte_form_base(ctx->cfg.radius),
                      (uint32_t)((ctx->last_numel + kChunk - 1) / kChunk), nullptr);
         if (hipDeviceSynchronize() != hipSuccess) return CMP_E_HIP;
         *d_ptr = ctx->s.sym; *bytes = 2 * (size_t)ctx->last_numel; return CMP_OK;

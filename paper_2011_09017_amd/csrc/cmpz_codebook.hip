@@ -246,15 +246,16 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
         const uint64_t excl = (uint64_t)i0 + ((uint64_t)i1 << 24) + ((uint64_t)i2 << 48) - sl;
         first_code[lane] = real ? (excl >> (kMaxCodeLen - lane)) : 0ull;
         if (lane == 0) b.tmeta[ti].max_len = max_len;
+        if (lane == (int)kEncBits + 1) b.tmeta[ti].long_from = (uint32_t)(excl >> (kMaxCodeLen - 32));
     }
     __syncthreads();
     const uint32_t rank = wave_cnt[wv][L] + in_wave;
     const uint64_t entry = L ? (((uint64_t)L << 56) | (first_code[L] + rank)) : 0ull;
     b.codes[ti * kMaxSym + tid] = entry;
     b.lens[ti * kMaxSym + tid] = (uint8_t)L;
-    // what the packing kernel looks up while no codeword is longer than 27 bits: the codeword
-    // left-aligned in 32 bits with its length in the low five
-    b.enc32[ti * kMaxSym + tid] = (L && L <= 27u) ? (((uint32_t)entry << (32u - L)) | L) : 0u;
+    // what the packing kernel looks up: the first 24 bits of the codeword, left-aligned, above its length
+    const uint64_t left = L ? (first_code[L] + rank) << (64u - L) : 0ull;
+    b.enc32[ti * kMaxSym + tid] = ((uint32_t)(left >> 32) & ~0xffu) | L;
     // container section `lens`: 2*radius bytes, zero padded to a multiple of 16
     const uint32_t padded = (nsym + 15u) & ~15u;
     if ((uint32_t)tid < padded && oref.cap >= kHeaderBytes + padded) out[kHeaderBytes + tid] = ((uint32_t)tid < nsym) ? (uint8_t)L : 0;

@@ -11,7 +11,7 @@ namespace cmpz {
 namespace {
 
 constexpr int kThreads    = 256;
-constexpr int kTileChunks = 4;                       // chunks per workgroup
+constexpr int kTileChunks = (int)kUntiledChunks;                       // chunks per workgroup
 constexpr int kTile       = kTileChunks * kChunk;    // 16384 elements
 
 // ---------------------------------------------------------------------------
@@ -20,7 +20,7 @@ constexpr int kTile       = kTileChunks * kChunk;    // 16384 elements
 __global__ __launch_bounds__(kThreads) void k_quant_lorenzo_split_hist(BatchC b, uint32_t ti)
 {
     const TensorC &tc = b.t[ti];
-    __shared__ uint32_t hist[kMaxSym];
+    __shared__ __align__(16) uint32_t hist[kMaxSym];
     __shared__ uint32_t ocnt[kTileChunks];
     const int tid = threadIdx.x;
     for (int k = tid; k < (int)kMaxSym; k += kThreads) hist[k] = 0;
@@ -35,7 +35,9 @@ __global__ __launch_bounds__(kThreads) void k_quant_lorenzo_split_hist(BatchC b,
     const uint64_t tile0 = (uint64_t)blockIdx.x * kTile;
     uint32_t events = 0;
 
-    for (int it = 0; it < kTile / (kThreads * 4); ++it) {
+    constexpr int kSteps = (int)kChunk / (kThreads * 4);          // per chunk
+    for (int ch = 0; ch < kTileChunks && tile0 + (uint64_t)ch * kChunk < numel; ++ch) {     // uniform
+    for (int it = ch * kSteps; it < (ch + 1) * kSteps; ++it) {
         const uint64_t i64 = tile0 + (uint64_t)it * (kThreads * 4) + (uint64_t)tid * 4;
         if (i64 >= numel) continue;
         const uint32_t i0 = (uint32_t)i64;
@@ -119,9 +121,17 @@ __global__ __launch_bounds__(kThreads) void k_quant_lorenzo_split_hist(BatchC b,
             }
             if (s[3] != 0xffffffffu) atomicAdd(&hist[s[3]], run);
         }
-        if (nout) atomicAdd(&ocnt[it / 4], nout);
+        if (nout) atomicAdd(&ocnt[ch], nout);
     }
     __syncthreads();
+    // the counts so far to the chunk's rows
+    const uint64_t g = (uint64_t)tc.chunk_base + (uint64_t)blockIdx.x * kTileChunks + ch;
+    for (int k = tid; k < (int)kMaxSym; k += kThreads) b.chunk_hist_all[g * kMaxSym + k] = (uint16_t)hist[k];
+    static_assert(kThreads == 256, "one symbol with a byte form per thread");
+    b.chunk_hist[g * 256 + tid] = (uint16_t)hist[b.sym_off + tid];
+    if (tid == 0) b.has_all[g] = 1;
+    __syncthreads();
+    }
     for (int k = tid; k < (int)kMaxSym; k += kThreads) {
         const uint32_t c = hist[k];
         if (c) atomicAdd(&b.hist[((uint64_t)ti * kHistCopies + blockIdx.x % kHistCopies) * kMaxSym + k], c);

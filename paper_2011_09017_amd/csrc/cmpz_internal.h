@@ -18,9 +18,20 @@ constexpr uint32_t kHeaderBytes = 256;
 // last element before they compare, so the bound stays two such steps below 2^32.
 constexpr uint64_t kMaxNumel    = (1ull << 32) - 8192;
 constexpr uint32_t kMaxCodeLen  = 48;       // counts below 2^32 bound a Huffman depth by 45
+constexpr uint32_t kEncBits     = 24;       // bits of a codeword in its 32-bit packing entry; the low eight are its length
 constexpr uint32_t kVersion     = 1;        // every code is in the bit stream
 constexpr uint32_t kVersionZB   = 2;        // sub-blocks of zero residuals are left out of it
 constexpr uint32_t kHistCopies  = 8;        // global histogram replicas that workgroups flush into (less contention)
+// Every chunk leaves 16-bit counts: the histogram of the chunks that its workgroup of the first sweep
+// has taken so far, this one included (a run of at most kRunMax chunks, so that the counts fit).
+// With the code lengths, these counts less those of the chunk before give the chunk's bit count without a
+// second look at its symbols.  Those of the 256 symbols with a byte form have a row of their own; from the
+// first chunk of a run on that is not all bytes, there is a row of all symbols too.
+constexpr uint32_t kRunMax      = 15;
+constexpr uint32_t kUntiledChunks = 4;      // run of the first sweep's kernel for wide rows
+// First symbol with a byte form: 128 below the zero residual, rounded down to a multiple of four entries of
+// a row (radii up to 128: all symbols have one).
+__host__ __device__ inline uint32_t byte_form_base(uint32_t radius) { return radius > 128u ? (radius - 128u) & ~3u : 0u; }
 
 // Container header, little-endian, 256 bytes; bytes 144..255 are zero.
 struct Header {
@@ -103,8 +114,8 @@ enum MetaWord : int {
 // a range of pack_chunks consecutive chunks of one tensor; those ranges are numbered
 // consecutively too (tensor t owns pack_base .. ).
 constexpr int      kBatchMax   = 24;        // tensors per launch group (kernel arguments hold their descriptors)
-constexpr uint32_t kPackChunks = 16;        // chunks per workgroup of the bit-count and packing kernels: at most,
-constexpr uint32_t kPackChunksMin = 4;      // and at least (one per wave)
+constexpr uint32_t kPackChunks = 28;        // chunks per workgroup of the bit-count and packing kernels: at most,
+constexpr uint32_t kPackChunksMin = 4;      // and at least (one per wave); always a multiple of that
 
 // A stack of containers in one device buffer whose bookkeeping lives on the device: where the
 // next container goes is known to the GPU only (it depends on the sizes of the containers before
@@ -129,6 +140,7 @@ struct TensorC {
     uint32_t     numel, nchunks, chunk_base, eb_bits;
     float        r;
     uint32_t     sweep_base;    // first workgroup of this tensor in the first sweep
+    uint32_t     run;           // consecutive chunks that a workgroup of the first sweep takes
     uint32_t     pack_base;     // first chunk range of this tensor
     FastDiv      divW, divHW;
 };
@@ -140,16 +152,24 @@ struct TensorMeta {
     uint32_t skip;              // the container does not fit: nothing but the header is written
     uint32_t n_outliers;
     uint32_t total_units;       // payload size in 16-byte units
-    uint32_t pad;
+    uint32_t long_from;         // smallest left-aligned 32 bits of a code longer than kEncBits (max_len says if any is)
     uint64_t total_bits;
     uint64_t total_size;        // container bytes
 };
+
+// A value that is the same in all lanes, in a scalar register (a load from memory that the kernel may
+// write leaves it in a vector register).
+__device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
+{
+    return ((uint64_t)uniform_u32((uint32_t)(v >> 32)) << 32) | uniform_u32((uint32_t)v);
+}
 
 // Where the container of a tensor goes and how much room there is.
 struct OutRef { uint8_t *out; uint64_t cap; };
 __device__ __forceinline__ OutRef resolve_out(const TensorC &tc)
 {
-    uint64_t at = tc.arena ? tc.arena->top : 0;
+    uint64_t at = tc.arena ? uniform_u64(tc.arena->top) : 0;
     if (at > tc.out_cap) at = tc.out_cap;
     OutRef o = {tc.out + at, tc.out_cap - at};
     return o;
@@ -167,12 +187,17 @@ struct BatchC {
                                 // symbols, 2048 bytes apart) holds 16 bits per symbol or, if not marked wide,
                                 // 8 bits (symbol - sym_off) in its first 1024 bytes
     uint32_t   *wide;           // [global chunk][quarter]: nonzero = 16-bit symbols
-    uint32_t    sym_off;        // radius - 128 (0 for radii up to 128): byte b stands for symbol b + sym_off
+    uint32_t    sym_off;        // byte_form_base(radius): byte b stands for symbol b + sym_off
     uint32_t   *hist;           // [slot][kHistCopies][kMaxSym], zero between calls
     uint32_t   *hist_copy;      // [slot][kMaxSym]
     uint8_t    *lens;           // [slot][kMaxSym]
     uint64_t   *codes;          // [slot][kMaxSym]: len << 56 | code
-    uint32_t   *enc32;          // [slot][kMaxSym]: code << (32 - len) | len, valid while max_len <= 27
+    uint32_t   *enc32;          // [slot][kMaxSym]: the first 24 bits of the left-aligned code, length in the low 8; 0: unused
+    uint16_t   *chunk_hist;     // [global chunk][256]: counts of the symbols from sym_off on, see kRunMax.  What
+                                // stands for the zero residual holds only in container version 2, where it counts
+                                // those that are coded; elsewhere they are the elements that are no other symbol
+    uint16_t   *chunk_hist_all; // [global chunk][kMaxSym]: counts of all symbols
+    uint32_t   *has_all;        // [global chunk]: nonzero = the row in chunk_hist_all is there
     uint32_t   *outl_cnt;       // [global chunk]: outliers
     uint32_t   *chunk_bits;     // [global chunk]: sum of codeword lengths
     uint32_t   *range_units;    // [chunk range]: payload units, later their exclusive prefix within the tensor

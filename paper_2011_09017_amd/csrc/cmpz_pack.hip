@@ -1,19 +1,20 @@
 // Sweep 2 of compression: chunked Huffman bit-packing (the entropy-coding stage of Section 3.1)
 // for all tensors of a call, in three launches with no ordering between workgroups:
 //
-//   k_lengths  one streaming pass over the symbols (8 or 16 bits each, as the first sweep left
-//              them): the bit count of every sub-block (written straight into the container),
-//              of every chunk and of every range of up to kPackChunks chunks;
+//   k_lengths  the bit count of every chunk and of every range of up to kPackChunks chunks, from the
+//              chunks' histograms (the first sweep's running counts) and the code lengths;
 //   k_scan     one workgroup per tensor: exclusive prefix sums of the ranges' payload units
 //              and outlier counts, the container header, the decision whether it fits;
 //   k_pack     the same ranges again: chunk offsets from the range's prefix, the codewords of
 //              a chunk (four neighbours merged in registers) OR-ed into a per-wave LDS image at
-//              their own bit positions, 128-bit stores; outlier records of the chunks that hold
-//              any.
+//              their own bit positions, 128-bit stores; the bit count of every sub-block, which the
+//              offsets' prefix sum yields on the way; outlier records of the chunks that hold any.
 //
-// Reading the symbols twice costs 1 to 2 bytes per element of extra traffic and buys packing
-// workgroups that never wait for one another: every wave walks its own chunks with no
-// workgroup barrier after the offsets are known.
+// The symbols are read once, 1 to 2 bytes per element, and packing workgroups never wait for one another:
+// every wave walks its own chunks with no workgroup barrier after the offsets are known.  While the bit
+// counts came from a pass over the symbols, the ResNet-18-shaped stream (591 M elements) took 138 us for
+// them and 240 for the packing, whose symbols that pass had brought nearer; now 35 and 262, and 10 more in
+// the first sweep.
 #include "cmpz_internal.h"
 
 #include <type_traits>
@@ -25,8 +26,6 @@ constexpr int kThreads = 256;
 constexpr int kWaves   = kThreads / kWave;
 static_assert(kPackChunks <= (uint32_t)kWave, "one lane per chunk of a range");
 
-constexpr uint32_t kPastEnd  = kMaxSym;      // symbol value of elements past the end of the tensor (codes to nothing)
-constexpr uint32_t kShortMax = 27;           // longest codeword the 32-bit table entries can hold
 
 // LDS written by some lanes of a wave is read by others: the hardware keeps a wave's LDS
 // operations in order, this keeps the compiler from moving them across.
@@ -51,123 +50,82 @@ __device__ __forceinline__ void unpack8(const uint4 &v, uint32_t s[8])
 }
 
 // ---------------------------------------------------------------------------
-// Bit counts.  A wave takes whole chunks; per step every lane holds 8 consecutive 16-bit symbols
-// or 16 consecutive bytes (one 128-bit load, consecutive lanes consecutive addresses), so a
-// sub-block of 32, 64 or 128 codes is a few neighbouring lanes of one DPP row.
+// Bit counts of the chunks, from their histograms: the length of every symbol's code times how
+// often it occurs.  A lane holds four neighbouring symbols; a wave takes whole chunks.
 // ---------------------------------------------------------------------------
-// ZB: container version 2 (sub-blocks of zero residuals have no bits)
-template <bool ZB>
 __global__ __launch_bounds__(kThreads) void k_lengths(BatchC b)
 {
-    __shared__ uint32_t lens_s[kMaxSym / 4 + 1];     // code length per symbol, one byte each; symbol kPastEnd: 0
+    __shared__ uint32_t lens_s[kMaxSym / 4];         // code length per symbol, one byte each
     __shared__ uint32_t bits_s[kPackChunks];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // The ranges are taken last first: the first sweep wrote the symbols in ascending order, so what
-    // it wrote last is what the memory-side cache still holds; and what this pass reads last (the
-    // first ranges) is what the packing pass, which runs forwards, reads first.
-    const uint32_t range = b.pack_wgs - 1u - blockIdx.x;
+    const uint32_t range = blockIdx.x;
     const uint32_t ti = tensor_of_range(b, range);
     const TensorC &tc = b.t[ti];
     const uint32_t c0 = (range - tc.pack_base) * b.pack_chunks;
     const uint32_t nq = (tc.nchunks - c0 < b.pack_chunks) ? tc.nchunks - c0 : b.pack_chunks;
-    const uint32_t numel = tc.numel;
+    const uint32_t byte_quad = b.sym_off / 4;        // the first four symbols with a byte form
+    // A wave takes up to kMine consecutive chunks: the rows of these and of the one before, as far as their bytes
+    // go, all loads in flight together
+    constexpr uint32_t kMine = kPackChunks / kWaves;
+    const uint32_t per = b.pack_chunks / kWaves, q0 = wv * per;
+    const uint32_t g0 = tc.chunk_base + c0 + q0;     // (rows of chunks that do not exist are not looked at)
+    const uint2 *__restrict__ byte_rows = reinterpret_cast<const uint2 *>(b.chunk_hist);           // 64 per chunk
+    const uint2 *__restrict__ all_rows = reinterpret_cast<const uint2 *>(b.chunk_hist_all);        // kMaxSym / 4 per chunk
+    uint2 v[kMine + 1] = {};
+    uint4 wq[kMine] = {};
+    if (q0 < nq && c0 + q0) v[0] = byte_rows[(uint64_t)(g0 - 1) * 64 + lane];
+#pragma unroll
+    for (uint32_t j = 0; j < kMine; ++j) {
+        if (j < per && q0 + j < nq) {                // uniform
+            v[j + 1] = byte_rows[(uint64_t)(g0 + j) * 64 + lane];
+            wq[j] = *reinterpret_cast<const uint4 *>(b.wide + (uint64_t)(g0 + j) * 4);
+        }
+    }
     static_assert(kMaxSym / 4 == kThreads, "one word of the length table per thread");
     lens_s[tid] = reinterpret_cast<const uint32_t *>(b.lens + (uint64_t)ti * kMaxSym)[tid];
-    if (tid == 0) lens_s[kMaxSym / 4] = 0;
     __syncthreads();
-    const uint8_t *L = reinterpret_cast<const uint8_t *>(lens_s);
-    const uint16_t *__restrict__ sym = b.sym + (uint64_t)tc.chunk_base * kChunk;
-    const Layout lay = make_layout(numel, b.radius, b.sub);
-    const OutRef oref = resolve_out(tc);
-    const bool fixed_fit = oref.cap >= lay.off_payload;              // room for the sections of fixed size (uniform)
-    uint16_t *__restrict__ sub_bits = reinterpret_cast<uint16_t *>(oref.out + lay.off_sub_bits);
-
-    for (uint32_t q = wv; q < nq; q += kWaves) {
-        const uint32_t c = c0 + q;
-        const uint32_t e0 = c * kChunk;              // first element of the chunk
-        const bool full = numel - e0 >= kChunk;
-        uint32_t chunk_bits = 0;
-        // sub-block bit counts from the lanes' bit counts
-        auto emit = [&](uint32_t bits, uint32_t first_sub, uint32_t group) {
-            const uint32_t inc = wave_inclusive_sum(bits);
-            const uint32_t exc = inc - bits;
-            // the first lane of a sub-block sits group-1 lanes below its last lane, in the same DPP row
-            const uint32_t first_exc = (group == 16) ? dpp_u32<0x11F, 0xf>(exc) : (group == 8) ? dpp_u32<0x117, 0xf>(exc)
-                                     : (group == 4)  ? dpp_u32<0x113, 0xf>(exc) : dpp_u32<0x111, 0xf>(exc);
-            if (fixed_fit && ((uint32_t)lane & (group - 1)) == group - 1)
-                sub_bits[(uint64_t)c * lay.nsub + first_sub + (uint32_t)lane / group] = (uint16_t)(inc - first_exc);
-            chunk_bits += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-        };
-        // the four quarters of the chunk, each with 16-bit symbols (8 per lane and step, two steps, a
-        // sub-block is 4, 8 or 16 lanes) or with bytes (16 per lane, one step, a sub-block is 2, 4 or 8
-        // lanes); all loads first (the scratch holds whole chunks: always in bounds)
-        const uint4 wq = *reinterpret_cast<const uint4 *>(b.wide + (uint64_t)(tc.chunk_base + c) * 4);
-        const bool wide[4] = {__builtin_amdgcn_readfirstlane(wq.x) != 0, __builtin_amdgcn_readfirstlane(wq.y) != 0,
-                              __builtin_amdgcn_readfirstlane(wq.z) != 0, __builtin_amdgcn_readfirstlane(wq.w) != 0};
-        uint4 v[4][2];
+    // Elements that are no other symbol are zero residuals: their code counts for every element, and the
+    // other symbols for what their codes are longer.  In container version 2 they are counted.
+    const int32_t zero_len = b.zero_blocks ? 0 : (int32_t)reinterpret_cast<const uint8_t *>(lens_s)[b.radius];
+    auto quad_bits = [&](uint2 n, uint32_t quad) -> int32_t {
+        const uint32_t L = lens_s[quad];
+        return (int32_t)(n.x & 0xffffu) * ((int32_t)(L & 0xffu) - zero_len) + (int32_t)(n.x >> 16) * ((int32_t)((L >> 8) & 0xffu) - zero_len) +
+               (int32_t)(n.y & 0xffffu) * ((int32_t)((L >> 16) & 0xffu) - zero_len) + (int32_t)(n.y >> 16) * ((int32_t)(L >> 24) - zero_len);
+    };
+    // The symbols without a byte form, of the counts after chunk g: looked at where g is not all bytes, and where
+    // the next one is not (the lane's share).
+    auto others = [&](uint32_t g) -> int32_t {
+        const uint2 *row = all_rows + (uint64_t)g * (kMaxSym / 4);
+        int32_t bits = 0;
 #pragma unroll
-        for (int qt = 0; qt < 4; ++qt) {
-            const uint16_t *slot = sym + e0 + 1024u * qt;
-            if (wide[qt]) {
-                v[qt][0] = *reinterpret_cast<const uint4 *>(slot + (uint32_t)lane * 8u);
-                v[qt][1] = *reinterpret_cast<const uint4 *>(slot + 512u + (uint32_t)lane * 8u);
-            } else {
-                v[qt][0] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(slot) + (uint32_t)lane * 16u);
-                v[qt][1] = v[qt][0];
-            }
+        for (uint32_t i = 0; i < kMaxSym / 4 / kWave; ++i) {
+            const uint32_t quad = i * kWave + lane;
+            if (quad - byte_quad >= (uint32_t)kWave) bits += quad_bits(row[quad], quad);
         }
-        const uint8_t *Lo = L + b.sym_off;
+        return bits;
+    };
+    int32_t others_before = 0;
+    bool have_before = false;                        // uniform
 #pragma unroll
-        for (int qt = 0; qt < 4; ++qt) {
-            if (wide[qt]) {
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    uint32_t s[8];
-                    unpack8(v[qt][j], s);
-                    if (!full) {
-                        const uint32_t i0 = e0 + 1024u * qt + 512u * j + (uint32_t)lane * 8u;
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) if (i0 + k >= numel) s[k] = kPastEnd;
-                    }
-                    uint32_t bits = 0;
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) bits += L[s[k]];
-                    if (ZB) {
-                        bool az = true;          // nothing but the zero residual (or nothing at all) in this lane
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) az = az && (s[k] == b.radius || s[k] == kPastEnd);
-                        if (group_all(az, (uint32_t)lane, b.sub / 8)) bits = 0;
-                    }
-                    emit(bits, (1024u * qt + 512u * j) / b.sub, b.sub / 8);
-                }
-            } else {
-                const uint32_t w[4] = {v[qt][0].x, v[qt][0].y, v[qt][0].z, v[qt][0].w};
-                const uint32_t i0 = e0 + 1024u * qt + (uint32_t)lane * 16u;
-                uint32_t bits = 0;
-                bool az = true;
-                if (full) {                                  // uniform; every chunk of a tensor but its last
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) {
-                        const uint32_t byte = (w[k >> 2] >> (8 * (k & 3))) & 0xffu;
-                        bits += Lo[byte];
-                        if (ZB) az = az && (byte + b.sym_off == b.radius);
-                    }
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) {
-                        const uint32_t byte = (w[k >> 2] >> (8 * (k & 3))) & 0xffu;
-                        const uint32_t len = Lo[byte];
-                        const bool there = i0 + k < numel;
-                        bits += there ? len : 0u;
-                        az = az && (!there || byte + b.sym_off == b.radius);
-                    }
-                }
-                if (ZB && group_all(az, (uint32_t)lane, b.sub / 16)) bits = 0;
-                emit(bits, (1024u * qt) / b.sub, b.sub / 16);
-            }
+    for (uint32_t j = 0; j < kMine; ++j) {
+        const uint32_t q = q0 + j;
+        if (j >= per || q >= nq) break;              // uniform
+        const uint32_t c = c0 + q, g = g0 + j;
+        const bool first = c % tc.run == 0;          // of its run: nothing to subtract
+        int32_t bits = quad_bits(v[j + 1], byte_quad + lane);
+        if (!first) bits -= quad_bits(v[j], byte_quad + lane);
+        const bool wide = uniform_u32(wq[j].x | wq[j].y | wq[j].z | wq[j].w) != 0;
+        if (wide) {
+            const int32_t now = others(g);
+            bits += now;
+            if (!first) bits -= have_before ? others_before : uniform_u32(b.has_all[g - 1]) ? others(g - 1) : 0;
+            others_before = now;
         }
-        if (lane == 0) { bits_s[q] = chunk_bits; b.chunk_bits[tc.chunk_base + c] = chunk_bits; }
+        have_before = wide;
+        const uint32_t n = (tc.numel - c * kChunk < kChunk) ? tc.numel - c * kChunk : kChunk;
+        const uint32_t tot = wave_inclusive_sum((uint32_t)bits) + n * (uint32_t)zero_len;
+        if (lane == 63) { bits_s[q] = tot; b.chunk_bits[g] = tot; }
     }
     __syncthreads();
     if (wv == 0) {
@@ -290,21 +248,30 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(BatchC b)
 }
 
 // ---------------------------------------------------------------------------
-// Packing.  A wave packs a chunk in steps of 1024 codes (16 per lane; 512 and 8 when codewords
-// may exceed 27 bits): the lanes' bit offsets come from a wave scan of their code lengths, every
+// Packing.  A wave packs a chunk in steps of 1024 codes (16 per lane): the lanes' bit offsets come from
+// a wave scan of their code lengths, every
 // codeword is OR-ed into the wave's zeroed LDS image at its own position (bit k of the chunk is bit
 // 31-(k%32) of little-endian word k/32), the 16-byte units that are complete go out with 128-bit
 // stores, and the unit that is still open moves to the front of the image for the next step.
+//
+// A table entry holds 24 bits of a codeword.  A code of 25 bits and more has a share of at most
+// 1 / Fibonacci(26) = 8e-6 of the elements, so few steps hold any: such a step puts its codewords into the
+// image one by one, from the full codes.  (While a tensor with one codeword of 28 bits or more was packed
+// from 64-bit entries throughout, the largest tensor of the ResNet-18-shaped stream, whose codes reach 28
+// bits under some seeds, took that launch from 240 to 315 us.)
 // ---------------------------------------------------------------------------
-constexpr uint32_t kStepBitsMax = 1024 * kShortMax;                    // = 27648 >= 512 * kMaxCodeLen
-static_assert(512 * kMaxCodeLen <= kStepBitsMax, "image size");
+constexpr uint32_t kStepBitsMax = 1024 * kMaxCodeLen;
 constexpr uint32_t kImageUnits = kStepBitsMax / 128 + 2;               // the open unit in front, one of slack behind
 constexpr uint32_t kImageWords = kImageUnits * 4;
 
-template <bool ZB>
-__global__ __launch_bounds__(kThreads, ZB ? 5 : 6) void k_pack(BatchC b)
+// ZB: container version 2; GROUP: lanes of a sub-block (16 codes each)
+template <bool ZB, int GROUP>
+// Five waves per SIMD: at six the 80 registers spill, which costs more than the sixth wave gives.
+__global__ __launch_bounds__(kThreads, 5) void k_pack(BatchC b)
 {
-    __shared__ uint64_t table[kMaxSym + 1];          // length << 56 | code; or, as 32-bit words, code << (32 - length) | length
+    __shared__ uint32_t table[kMaxSym];              // codeword left-aligned (its first 24 bits) | length
+    __shared__ uint32_t byte_table[256];             // the same by the byte form: at a constant address, so that a
+                                                     // byte becomes its entry's in one instruction
     __shared__ __align__(16) uint32_t images[kWaves][kImageWords];
     __shared__ uint32_t coff_s[kPackChunks], ooff_s[kPackChunks + 1], bits_s[kPackChunks];
     __shared__ uint16_t olists[kWaves][kWave];       // per wave: where in a step the outliers of one pass sit
@@ -313,22 +280,38 @@ __global__ __launch_bounds__(kThreads, ZB ? 5 : 6) void k_pack(BatchC b)
     const uint32_t ti = tensor_of_range(b, blockIdx.x);
     const TensorC &tc = b.t[ti];
     const TensorMeta &tm = b.tmeta[ti];
-    if (tm.skip) return;                             // uniform: the container does not fit, its header says so
+    if (uniform_u32(tm.skip)) return;                // the container does not fit, its header says so
     const uint32_t c0 = (blockIdx.x - tc.pack_base) * b.pack_chunks;
     const uint32_t nq = (tc.nchunks - c0 < b.pack_chunks) ? tc.nchunks - c0 : b.pack_chunks;
     const uint32_t numel = tc.numel;
-    const bool short_codes = tm.max_len <= kShortMax;                // uniform
+    const bool long_codes = uniform_u32(tm.max_len) > kEncBits;      // some entries are not whole,
+    const uint32_t long_from = uniform_u32(tm.long_from);            // those from here on
+    const uint32_t n_outliers = uniform_u32(tm.n_outliers);
     const Layout lay = make_layout(numel, b.radius, b.sub);
     uint8_t *const out = resolve_out(tc).out;
 
-    uint32_t *table32 = reinterpret_cast<uint32_t *>(table);
-    if (short_codes) {
-        const uint32_t *src = b.enc32 + (uint64_t)ti * kMaxSym;
-        for (int k = tid; k <= (int)kMaxSym; k += kThreads) table32[k] = (k < (int)kMaxSym) ? src[k] : 0u;
-    } else {
-        const uint64_t *src = b.codes + (uint64_t)ti * kMaxSym;
-        for (int k = tid; k <= (int)kMaxSym; k += kThreads) table[k] = (k < (int)kMaxSym) ? src[k] : 0ull;
-    }
+    const uint16_t *__restrict__ sym = b.sym + (uint64_t)tc.chunk_base * kChunk;
+    // per quarter of the wave's chunks (wv, wv + 4, ...), four bits each: 16-bit symbols, else bytes
+    static_assert(kPackChunks <= (uint32_t)kWave, "one lane per quarter of a wave's chunks");
+    const uint32_t flag_of = wv + (uint32_t)(lane & ~3);             // (chunk wv + 4 * (lane / 4), quarter lane % 4)
+    const unsigned long long wide_mask =
+        __ballot(flag_of < nq && b.wide[(uint64_t)(tc.chunk_base + c0 + flag_of) * 4 + (lane & 3)] != 0);
+    // The lane's 16 symbols of a quarter, a step's worth: 32 bytes of a wide quarter, 16 of a narrow one.
+    // They are fetched while the step before is packed, also across
+    // chunks: the first sweep's stores are long gone to memory.
+    // (A cache line each fetched a whole chunk ahead: 281 -> 299 us on the ResNet-18-shaped stream.)
+    auto fetch = [&](uint32_t q, uint32_t qt, uint4 &a, uint4 &c2) {
+        const bool wd = (wide_mask >> ((q & ~3u) + qt)) & 1u;
+        const uint8_t *p = reinterpret_cast<const uint8_t *>(sym + (uint64_t)(c0 + q) * kChunk + 1024u * qt) + (((uint32_t)lane * 16u) << (wd ? 1 : 0));
+        a = *reinterpret_cast<const uint4 *>(p);
+        if (wd) c2 = *reinterpret_cast<const uint4 *>(p + 16u);
+    };
+    uint4 lo = make_uint4(0, 0, 0, 0), hi = lo;
+    if ((uint32_t)wv < nq) fetch(wv, 0, lo, hi);
+    const uint32_t *entries = b.enc32 + (uint64_t)ti * kMaxSym;
+    for (int k = tid; k < (int)kMaxSym; k += kThreads) table[k] = entries[k];
+    static_assert(kThreads == 256, "one byte form per thread");
+    byte_table[tid] = entries[b.sym_off + tid];
     uint32_t *img = images[wv];
     uint16_t *olist = olists[wv];
     for (uint32_t k = lane; k < kImageUnits; k += kWave) reinterpret_cast<uint4 *>(img)[k] = make_uint4(0, 0, 0, 0);
@@ -351,137 +334,56 @@ __global__ __launch_bounds__(kThreads, ZB ? 5 : 6) void k_pack(BatchC b)
     __syncthreads();
     // ---- from here on the waves are on their own ----
 
-    const uint16_t *__restrict__ sym = b.sym + (uint64_t)tc.chunk_base * kChunk;
     const float *__restrict__ x = tc.x;
     const uint32_t W = tc.shape[3], HW = tc.shape[2] * W;
     uint4 *__restrict__ payload = reinterpret_cast<uint4 *>(out + lay.off_payload);
-    const uint64_t off_outl_idx = lay.off_payload + (uint64_t)tm.total_units * 16;
+    const uint64_t off_outl_idx = lay.off_payload + (uint64_t)uniform_u32(tm.total_units) * 16;
     uint32_t *__restrict__ oidx = reinterpret_cast<uint32_t *>(out + off_outl_idx);
-    int32_t *__restrict__ oval = reinterpret_cast<int32_t *>(out + off_outl_idx + ((4ull * tm.n_outliers + 15) & ~15ull));
+    int32_t *__restrict__ oval = reinterpret_cast<int32_t *>(out + off_outl_idx + ((4ull * n_outliers + 15) & ~15ull));
     bool failed = false;
 
     for (uint32_t q = wv; q < nq; q += kWaves) {
         const uint32_t c = c0 + q;
         const uint32_t e0 = c * kChunk;
         const bool full = numel - e0 >= kChunk;
-        const uint32_t chunk_units = (bits_s[q] + 127u) >> 7;
-        uint4 *__restrict__ dst = payload + coff_s[q];
-        uint32_t orank = ooff_s[q];
-        const bool has_outl = ooff_s[q + 1] != orank;                // uniform
+        const uint32_t chunk_bits = uniform_u32(bits_s[q]), chunk_units = (chunk_bits + 127u) >> 7;
+        uint4 *__restrict__ dst = payload + uniform_u32(coff_s[q]);
+        uint32_t orank = uniform_u32(ooff_s[q]);
+        const bool has_outl = uniform_u32(ooff_s[q + 1]) != orank;
+        uint16_t *__restrict__ sub_bits = reinterpret_cast<uint16_t *>(out + lay.off_sub_bits) + (uint64_t)c * lay.nsub;
         uint32_t bitpos = 0;                         // bits of the chunk packed so far
         uint32_t ubase = 0;                          // units of the chunk stored so far: image unit 0 is stream unit ubase
 
-        // one step: the lane's n consecutive symbols s[] starting at element i0.  narrow: s[] holds the
-        // bytes of a quarter stored with 8 bits per symbol, i.e. symbol - sym_off (no outlier among them)
-        auto step = [&](const uint32_t *s, auto n_c, auto narrow_c, uint32_t i0, bool last) {
-            constexpr int n = decltype(n_c)::value;
-            constexpr bool narrow = decltype(narrow_c)::value;
-            const uint32_t zero_sym = narrow ? b.radius - b.sym_off : b.radius;    // the zero residual, as s[] has it
-            const uint32_t past_sym = narrow ? kPastEnd - b.sym_off : kPastEnd;    // elements past the end of the tensor
-            const uint32_t *tab = narrow ? table32 + b.sym_off : table32;
-            // outlier records: rank the zero symbols of the step; then one lane per outlier recomputes
-            // its residual from x, so that the loads of all of them are in flight together
-            if (!narrow && has_outl) {
-                uint32_t mine = 0;
-                _Pragma("unroll") for (int k = 0; k < n; ++k) mine += (s[k] == 0u) ? 1u : 0u;
-                const uint32_t inc = wave_inclusive_sum(mine);
-                const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-                const uint32_t step0 = i0 - (uint32_t)lane * (uint32_t)n;          // first element of the step
-                for (uint32_t r0 = 0; r0 < total; r0 += kWave) {                 // uniform; one pass unless outliers crowd
-                    uint32_t rk = inc - mine - r0;                               // place of the lane's next outlier in this pass
-                    _Pragma("unroll") for (int k = 0; k < n; ++k) {
-                        if (s[k] == 0u) {
-                            if (rk < (uint32_t)kWave) olist[rk] = (uint16_t)(lane * n + k);
-                            ++rk;
-                        }
-                    }
-                    wave_sync();
-                    const uint32_t me = r0 + (uint32_t)lane;
-                    if (me < total) {
-                        const uint32_t i = step0 + olist[lane];
-                        const uint32_t p = tc.divHW.div(i);
-                        const uint32_t rem = i - p * HW;
-                        const uint32_t h = tc.divW.div(rem), w = rem - h * W;
-                        const uint32_t at = orank + me;
-                        if (at < tm.n_outliers) {
-                            oidx[at] = i;
-                            oval[at] = delta_from_x(x, i, h, w, W, tc.r);
-                        }
-                    }
-                    wave_sync();
-                }
-                orank += total;
-            }
-            // version 2: a sub-block of zero residuals (n symbols per lane: sub / n lanes) has no bits
-            bool coded = true;
-            if (ZB) {
-                bool az = true;
-                _Pragma("unroll") for (int k = 0; k < n; ++k) az = az && (s[k] == zero_sym || s[k] == past_sym);
-                coded = !group_all(az, (uint32_t)lane, b.sub / (uint32_t)n);
-            }
-            // bit offsets of the lanes; in the short-code case the table entries stay in registers for the packing
-            uint32_t bits = 0;
-            uint32_t e[n];
-            if (short_codes) { _Pragma("unroll") for (int k = 0; k < n; ++k) { e[k] = coded ? tab[s[k]] : 0u; bits += e[k] & 31u; } }
-            else             { _Pragma("unroll") for (int k = 0; k < n; ++k) bits += coded ? (uint32_t)(table[s[k]] >> 56) : 0u; }
-            const uint32_t inc = wave_inclusive_sum(bits);
-            uint32_t pos = bitpos - ubase * 128u + inc - bits;        // bit position in the image
-            if (short_codes) {
-                // Codewords go into the image in groups: two of them (at most 54 bits together) merged
-                // in registers cost three LDS atomics, and so do four when they fit 64 bits, which they
-                // nearly always do (uniform test over the wave; otherwise two by two).
-                uint32_t longest = 0;
-                _Pragma("unroll") for (int k = 0; k < n; k += 4) {
-                    const uint32_t tot = (e[k] & 31u) + (e[k + 1] & 31u) + (e[k + 2] & 31u) + (e[k + 3] & 31u);
-                    longest = tot > longest ? tot : longest;
-                }
-                auto pair_of = [](uint32_t ea, uint32_t eb, uint32_t &hi, uint32_t &lo, uint32_t &len) {
-                    const uint32_t ca = ea & ~31u, la = ea & 31u;                   // left-aligned codes
-                    const uint64_t second = (((uint64_t)(eb & ~31u)) << 32) >> la;
-                    hi = ca | (uint32_t)(second >> 32); lo = (uint32_t)second; len = la + (eb & 31u);
-                };
-                auto put = [&](uint32_t hi, uint32_t lo) {
-                    const uint32_t o = pos & 31u;
-                    uint32_t *w = img + (pos >> 5);
-                    atomicOr(w, hi >> o);
-                    atomicOr(w + 1, __builtin_amdgcn_alignbit(hi, lo, o));
-                    atomicOr(w + 2, __builtin_amdgcn_alignbit(lo, 0u, o));           // the part that spills over
-                };
-                if (!__any(longest > 64u)) {
-                    _Pragma("unroll") for (int k = 0; k < n; k += 4) {
-                        uint32_t h0, l0, n0, h1, l1, n1;
-                        pair_of(e[k], e[k + 1], h0, l0, n0);
-                        pair_of(e[k + 2], e[k + 3], h1, l1, n1);
-                        const uint64_t quad = (((uint64_t)h0 << 32) | l0) | ((((uint64_t)h1 << 32) | l1) >> n0);   // n0 <= 54
-                        put((uint32_t)(quad >> 32), (uint32_t)quad);
-                        pos += n0 + n1;
-                    }
-                } else {
-                    _Pragma("unroll") for (int k = 0; k < n; k += 2) {
-                        uint32_t h0, l0, n0;
-                        pair_of(e[k], e[k + 1], h0, l0, n0);
-                        put(h0, l0);
-                        pos += n0;
-                    }
-                }
-            } else {
-                _Pragma("unroll") for (int k = 0; k < n; ++k) {
-                    const uint64_t cw = coded ? table[s[k]] : 0ull;
-                    const uint32_t len = (uint32_t)(cw >> 56);
-                    if (len) {
-                        const uint64_t place = (cw & 0x00ffffffffffffffull) << (64u - len);   // left-aligned in 64 bits
-                        const uint32_t hi = (uint32_t)(place >> 32), lo = (uint32_t)place, o = pos & 31u;
-                        uint32_t *w = img + (pos >> 5);
-                        atomicOr(w, hi >> o);
-                        atomicOr(w + 1, __builtin_amdgcn_alignbit(hi, lo, o));
-                        atomicOr(w + 2, __builtin_amdgcn_alignbit(lo, 0u, o));
-                        pos += len;
-                    }
-                }
-            }
+        // Bits from each lane into offsets in the image.  The scan's first steps leave in a lane the sum over
+        // the 2, 4 and 8 lanes that end in it (of its row of 16): the last lane of a sub-block, if `mine`,
+        // stores the sub-block's bit count from there.
+        auto offsets = [&](uint32_t bits, uint32_t i0, bool mine) -> uint32_t {
+            const bool ends = mine && ((uint32_t)lane & (GROUP - 1)) == GROUP - 1;
+            uint16_t *at = sub_bits + (i0 - e0) / (16u * GROUP);
+            uint32_t inc = bits + dpp_u32<0x111, 0xf>(bits);                           // row_shr:1
+            if (GROUP == 2 && ends) *at = (uint16_t)inc;
+            inc += dpp_u32<0x112, 0xf>(inc);                                           // row_shr:2
+            if (GROUP == 4 && ends) *at = (uint16_t)inc;
+            inc += dpp_u32<0x114, 0xf>(inc);                                           // row_shr:4
+            if (GROUP == 8 && ends) *at = (uint16_t)inc;
+            inc += dpp_u32<0x118, 0xf>(inc);                                           // row_shr:8
+            inc += dpp_u32<0x142, 0xa>(inc);                                           // row_bcast:15 into rows 1 and 3
+            inc += dpp_u32<0x143, 0xc>(inc);                                           // row_bcast:31 into rows 2 and 3
+            const uint32_t pos = bitpos - ubase * 128u + inc - bits;                   // bit position in the image
             bitpos += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+            return pos;
+        };
+        // up to 64 left-aligned bits into the image
+        auto put = [&](uint32_t pos, uint32_t hi, uint32_t lo) {
+            const uint32_t o = pos & 31u;
+            uint32_t *w = img + (pos >> 5);
+            atomicOr(w, hi >> o);
+            atomicOr(w + 1, __builtin_amdgcn_alignbit(hi, lo, o));
+            atomicOr(w + 2, __builtin_amdgcn_alignbit(lo, 0u, o));           // the part that spills over
+        };
+        // complete units go out; at the end of the chunk also the open one (zero padded)
+        auto flush = [&](bool last) {
             wave_sync();
-            // complete units go out; at the end of the chunk also the open one (zero padded)
             uint32_t done = last ? chunk_units : (bitpos >> 7);
             if (done > chunk_units) { done = chunk_units; failed = true; }   // never past the chunk's own units
             const uint32_t nu = done - ubase;
@@ -502,74 +404,144 @@ __global__ __launch_bounds__(kThreads, ZB ? 5 : 6) void k_pack(BatchC b)
             ubase = done;
         };
 
-        // per quarter of the chunk: 16-bit symbols, else bytes (uniform)
-        const uint4 wq = *reinterpret_cast<const uint4 *>(b.wide + (uint64_t)(tc.chunk_base + c) * 4);
-        const uint32_t wide_mask = (__builtin_amdgcn_readfirstlane(wq.x) ? 1u : 0u) | (__builtin_amdgcn_readfirstlane(wq.y) ? 2u : 0u) |
-                                   (__builtin_amdgcn_readfirstlane(wq.z) ? 4u : 0u) | (__builtin_amdgcn_readfirstlane(wq.w) ? 8u : 0u);
-        const uint8_t *__restrict__ sb = reinterpret_cast<const uint8_t *>(sym + e0);
-        auto unpack_bytes = [&](uint32_t w, uint32_t *s4) {
-            s4[0] = (w & 0xffu) + b.sym_off; s4[1] = ((w >> 8) & 0xffu) + b.sym_off;
-            s4[2] = ((w >> 16) & 0xffu) + b.sym_off; s4[3] = (w >> 24) + b.sym_off;
-        };
-        if (short_codes) {
-            // 16 symbols per lane and step, the next step's symbols in flight.  A step is a quarter of the
-            // chunk (2048 bytes apart): a lane's 16 symbols are 32 bytes of a wide quarter, 16 of a narrow
-            // one (the second load then repeats the first)
-            auto fetch = [&](uint32_t qt, uint4 &a, uint4 &c2) {
-                const bool wd = (wide_mask >> qt) & 1u;
-                const uint8_t *p = sb + 2048u * qt + (((uint32_t)lane * 16u) << (wd ? 1 : 0));
-                a = *reinterpret_cast<const uint4 *>(p);
-                c2 = *reinterpret_cast<const uint4 *>(p + (wd ? 16u : 0u));
-            };
-            uint4 lo, hi;
-            fetch(0, lo, hi);
-#pragma unroll 1
-            for (uint32_t it = 0; it < 4; ++it) {
-                const uint32_t i0 = e0 + it * 1024u + (uint32_t)lane * 16u;
-                const bool wide = (wide_mask >> it) & 1u;
-                uint4 nlo, nhi;
-                fetch(it < 3 ? it + 1 : it, nlo, nhi);                    // the last step fetches its own symbols again
-                uint32_t s[16];
-                if (wide) {
-                    unpack8(lo, s); unpack8(hi, s + 8);
-                    if (!full) {
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) if (i0 + k >= numel) s[k] = kPastEnd;
+        // one step: the lane's 16 consecutive symbols s[] starting at element i0.  narrow: s[] holds the
+        // bytes of a quarter stored with 8 bits per symbol, i.e. symbol - sym_off (no outlier among them)
+        auto step = [&](const uint32_t *s, auto narrow_c, uint32_t i0, bool last, auto fetch_next) {
+            constexpr int n = 16;
+            constexpr bool narrow = decltype(narrow_c)::value;
+            const uint32_t zero_sym = narrow ? b.radius - b.sym_off : b.radius;    // the zero residual, as s[] has it
+            const uint32_t there = full ? 16u : i0 >= numel ? 0u : numel - i0 < 16u ? numel - i0 : 16u;    // elements that exist
+            // outlier records: rank the zero symbols of the step; then one lane per outlier recomputes
+            // its residual from x, so that the loads of all of them are in flight together
+            if (!narrow && has_outl) {
+                uint32_t mine = 0;
+                _Pragma("unroll") for (int k = 0; k < n; ++k) mine += (s[k] == 0u && (uint32_t)k < there) ? 1u : 0u;
+                const uint32_t inc = wave_inclusive_sum(mine);
+                const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+                const uint32_t step0 = i0 - (uint32_t)lane * (uint32_t)n;          // first element of the step
+                for (uint32_t r0 = 0; r0 < total; r0 += kWave) {                 // uniform; one pass unless outliers crowd
+                    uint32_t rk = inc - mine - r0;                               // place of the lane's next outlier in this pass
+                    _Pragma("unroll") for (int k = 0; k < n; ++k) {
+                        if (s[k] == 0u && (uint32_t)k < there) {
+                            if (rk < (uint32_t)kWave) olist[rk] = (uint16_t)(lane * n + k);
+                            ++rk;
+                        }
                     }
-                    step(s, std::integral_constant<int, 16>{}, std::false_type{}, i0, it == 3);
-                } else {
-                    const uint32_t w4[4] = {lo.x, lo.y, lo.z, lo.w};
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) s[k] = (w4[k >> 2] >> (8 * (k & 3))) & 0xffu;
-                    if (!full) {
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) if (i0 + k >= numel) s[k] = kPastEnd - b.sym_off;
+                    wave_sync();
+                    const uint32_t me = r0 + (uint32_t)lane;
+                    if (me < total) {
+                        const uint32_t i = step0 + olist[lane];
+                        const uint32_t p = tc.divHW.div(i);
+                        const uint32_t rem = i - p * HW;
+                        const uint32_t h = tc.divW.div(rem), w = rem - h * W;
+                        const uint32_t at = orank + me;
+                        if (at < n_outliers) {
+                            oidx[at] = i;
+                            oval[at] = delta_from_x(x, i, h, w, W, tc.r);
+                        }
                     }
-                    step(s, std::integral_constant<int, 16>{}, std::true_type{}, i0, it == 3);
+                    wave_sync();
                 }
-                lo = nlo; hi = nhi;
+                orank += total;
             }
-        } else {
+            // version 2: a sub-block of zero residuals (n symbols per lane: sub / n lanes) has no bits
+            bool coded = true;
+            if (ZB) {
+                bool az = true;
+                _Pragma("unroll") for (int k = 0; k < n; ++k) az = az && (s[k] == zero_sym || (uint32_t)k >= there);
+                coded = !group_all(az, (uint32_t)lane, GROUP);
+            }
+            uint32_t e[n];
+            _Pragma("unroll") for (int k = 0; k < n; ++k) e[k] = narrow ? byte_table[s[k]] : table[s[k]];
+            if (!full) { _Pragma("unroll") for (int k = 0; k < n; ++k) e[k] = (uint32_t)k < there ? e[k] : 0u; }
+            if (ZB) { _Pragma("unroll") for (int k = 0; k < n; ++k) e[k] = coded ? e[k] : 0u; }
+            // Codewords go into the image in groups: two of them (at most 48 bits together) merged
+            // in registers cost three LDS atomics, and so do four when they fit 64 bits, which they
+            // nearly always do (uniform test over the wave; otherwise two by two).  Sums of entries hold the
+            // sums of lengths in their low eight bits, and shifts look at their low six (48 at most) anyway.
+            fetch_next();                            // the next step's symbols, now that these are looked up
+            uint32_t bits = 0, longest = 0, quad_len[n / 4];
+            _Pragma("unroll") for (int k = 0; k < n; k += 4) {
+                const uint32_t len = (e[k] + e[k + 1] + e[k + 2] + e[k + 3]) & 0xffu;
+                quad_len[k / 4] = len;
+                bits += len;
+                longest = len > longest ? len : longest;
+            }
+            uint32_t pos = offsets(bits, i0, true);
+            if (long_codes) {
+                uint32_t most = 0;
+                _Pragma("unroll") for (int k = 0; k < n; ++k) most = e[k] > most ? e[k] : most;
+                if (__any(most >= long_from)) {
+                    // (a rolled loop that looks everything up again: small, and nothing has to be kept for it above)
+                    const uint4 *mine = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(sym + e0 + ((i0 - e0) & ~1023u)) +
+                                                                        (narrow ? 16u : 32u) * lane);
+                    const uint32_t count = coded ? there : 0u;
+                    uint4 v = mine[0];
 #pragma unroll 1
-            for (uint32_t it = 0; it < 8; ++it) {
-                const uint32_t i0 = e0 + it * 512u + (uint32_t)lane * 8u;
-                uint32_t s[8];
-                if ((wide_mask >> (it >> 1)) & 1u) {
-                    const uint4 v = *reinterpret_cast<const uint4 *>(sym + i0);
-                    unpack8(v, s);
-                } else {
-                    // quarter it/2, its first or second 512 bytes
-                    const uint2 v = *reinterpret_cast<const uint2 *>(sb + 2048u * (it >> 1) + 512u * (it & 1u) + (uint32_t)lane * 8u);
-                    unpack_bytes(v.x, s); unpack_bytes(v.y, s + 4);
+                    for (uint32_t k = 0; k < count; ++k) {
+                        if (!narrow && k == 8) v = mine[1];
+                        constexpr uint32_t kBits = narrow ? 8u : 16u;
+                        const uint32_t sy = v.x & ((1u << kBits) - 1u);
+                        v.x = __builtin_amdgcn_alignbit(v.y, v.x, kBits);
+                        v.y = __builtin_amdgcn_alignbit(v.z, v.y, kBits);
+                        v.z = __builtin_amdgcn_alignbit(v.w, v.z, kBits);
+                        v.w >>= kBits;
+                        const uint32_t en = narrow ? byte_table[sy] : table[sy];
+                        const uint32_t len = en & 0xffu;
+                        uint64_t place = (uint64_t)(en & ~0xffu) << 32;              // left-aligned in 64 bits
+                        if (len > kEncBits) place = b.codes[(uint64_t)ti * kMaxSym + sy + (narrow ? b.sym_off : 0u)] << (64u - len);
+                        put(pos, (uint32_t)(place >> 32), (uint32_t)place);
+                        pos += len;
+                    }
+                    flush(last);
+                    return;
                 }
-                if (!full) {
+            }
+            // two codewords, left-aligned in 64 bits
+            auto pair_of = [](uint32_t ea, uint32_t eb) -> uint64_t {
+                const uint64_t second = ((uint64_t)(eb & ~0xffu) << 32) >> (ea & 63u);
+                return second | ((uint64_t)(ea & ~0xffu) << 32);
+            };
+            if (!__any(longest > 64u)) {
+                _Pragma("unroll") for (int k = 0; k < n; k += 4) {
+                    const uint64_t quad = pair_of(e[k], e[k + 1]) | (pair_of(e[k + 2], e[k + 3]) >> ((e[k] + e[k + 1]) & 63u));
+                    put(pos, (uint32_t)(quad >> 32), (uint32_t)quad);
+                    pos += quad_len[k / 4];
+                }
+            } else {
+                _Pragma("unroll") for (int k = 0; k < n; k += 2) {
+                    const uint64_t pair = pair_of(e[k], e[k + 1]);
+                    put(pos, (uint32_t)(pair >> 32), (uint32_t)pair);
+                    pos += (e[k] + e[k + 1]) & 0xffu;
+                }
+            }
+            flush(last);
+        };
+
+#pragma unroll 1
+        for (uint32_t it = 0; it < 4; ++it) {
+            const uint32_t i0 = e0 + it * 1024u + (uint32_t)lane * 16u;
+            const bool wide = (wide_mask >> ((q & ~3u) + it)) & 1u;
+            auto fetch_next = [&]() {
+                if (it < 3) fetch(q, it + 1, lo, hi);
+                else if (q + kWaves < nq) fetch(q + kWaves, 0, lo, hi);
+            };
+            uint32_t s[16];
+            if (wide) {
+                unpack8(lo, s); unpack8(hi, s + 8);
+                if (!full) {                     // (past the end stands whatever was there)
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) if (i0 + k >= numel) s[k] = kPastEnd;
+                    for (int k = 0; k < 16; ++k) s[k] &= kMaxSym - 1u;
                 }
-                step(s, std::integral_constant<int, 8>{}, std::false_type{}, i0, it == 7);
+                step(s, std::false_type{}, i0, it == 3, fetch_next);
+            } else {
+                const uint32_t w4[4] = {lo.x, lo.y, lo.z, lo.w};
+#pragma unroll
+                for (int k = 0; k < 16; ++k) s[k] = (w4[k >> 2] >> (8 * (k & 3))) & 0xffu;
+                step(s, std::true_type{}, i0, it == 3, fetch_next);
             }
         }
-        if (bitpos != bits_s[q]) failed = true;      // the two passes disagree: cannot happen
+        if (bitpos != chunk_bits) failed = true;      // the two passes disagree: cannot happen
     }
     if (failed && lane == 0) atomicOr(b.status, kStInternal);
 }
@@ -668,14 +640,19 @@ void launch_clear(const BatchC &b, Profiler *prof, hipStream_t st)
 // Bit counts, offsets and header, packing: three launches over all tensors of the group.
 void launch_pack(const BatchC &b, Profiler *prof, hipStream_t st)
 {
-    if (b.pack_wgs) {
-        if (b.zero_blocks) launch(prof, kKLengths, k_lengths<true>, dim3(b.pack_wgs), dim3(kThreads), st, b);
-        else launch(prof, kKLengths, k_lengths<false>, dim3(b.pack_wgs), dim3(kThreads), st, b);
-    }
+    if (b.pack_wgs) launch(prof, kKLengths, k_lengths, dim3(b.pack_wgs), dim3(kThreads), st, b);
     launch(prof, kKScan, k_scan, dim3(b.n), dim3(kScanThreads), st, b);
     if (b.pack_wgs) {
-        if (b.zero_blocks) launch(prof, kKPack, k_pack<true>, dim3(b.pack_wgs), dim3(kThreads), st, b);
-        else launch(prof, kKPack, k_pack<false>, dim3(b.pack_wgs), dim3(kThreads), st, b);
+        auto pack = [&](auto group) {
+            constexpr int kGroup = decltype(group)::value;
+            if (b.zero_blocks) launch(prof, kKPack, k_pack<true, kGroup>, dim3(b.pack_wgs), dim3(kThreads), st, b);
+            else launch(prof, kKPack, k_pack<false, kGroup>, dim3(b.pack_wgs), dim3(kThreads), st, b);
+        };
+        switch (b.sub) {
+        case 32:  pack(std::integral_constant<int, 2>{}); break;
+        case 64:  pack(std::integral_constant<int, 4>{}); break;
+        default:  pack(std::integral_constant<int, 8>{}); break;
+        }
     }
 }
 

@@ -1,6 +1,6 @@
 // Sweep 1 of compression, LDS-tiled: pre-quantisation, 2D Lorenzo prediction,
 // quantisation-code / outlier split, histogram -- one read of x, one write of
-// the 16-bit symbols.
+// the symbols.
 //
 // The tensor is one linear array (element i has its neighbours at i-1, i-W and
 // i-W-1 of the same plane).  A workgroup takes chunks of 4096 consecutive
@@ -10,8 +10,9 @@
 // symbols, histogram (LDS-private, the zero residual counted per wave).  A wave's
 // 1024 symbols (a quarter of the chunk) are stored with 8 bits each if they all
 // lie within 127 of the zero residual (the usual case), one 128-bit store per
-// thread, otherwise with 16 bits, two stores: the second sweep reads that scratch
-// twice.  Rows wider than the halo capacity take the untiled kernel in
+// thread, otherwise with 16 bits, two stores.  Behind every chunk the histogram as it
+// stands goes to the chunk's row of counts, from which the second sweep knows
+// the chunk's bit count without its symbols.  Rows wider than the halo capacity take the untiled kernel in
 // cmpz_compress.hip.
 #include "cmpz_internal.h"
 
@@ -31,13 +32,14 @@ __device__ __forceinline__ int mask_of_bit(int m, int k)
     return r;
 }
 
-__global__ __launch_bounds__(kThreads) void k_quant_lorenzo_split_hist_tiled(BatchC b)
+__global__ __launch_bounds__(kThreads, 8) void k_quant_lorenzo_split_hist_tiled(BatchC b)
 {
     __shared__ __align__(16) int16_t Q[kQWords];
-    __shared__ uint32_t hist[kMaxSym];
-    __shared__ uint32_t ocnt;
+    __shared__ __align__(16) uint32_t hist[kMaxSym];
+    __shared__ uint32_t ocnt, has_wide;           // outliers so far; some quarter of a chunk was wide
     const int tid = threadIdx.x, lane = tid & 63;
     for (int k = tid; k < (int)kMaxSym; k += kThreads) hist[k] = 0;
+    if (tid == 0) { ocnt = 0; has_wide = 0; }
 
     // the tensor this workgroup works on (uniform: scalar loads from the kernel arguments)
     uint32_t ti = 0;
@@ -52,13 +54,33 @@ __global__ __launch_bounds__(kThreads) void k_quant_lorenzo_split_hist_tiled(Bat
     const float r = tc.r;
     uint32_t events = 0, zero_run = 0;            // clamped elements; symbols equal to R seen by this thread
 
-    for (uint32_t t = 0; t < b.sweep_chunks; ++t) {
-        const uint32_t c = wg * b.sweep_chunks + t;
-        if (c >= nchunks) break;
+    // The counts after a chunk: every thread reads four of them and stores them to the chunk's rows.  The
+    // reads stand before the next chunk's loads and the stores behind its first phase, so that nobody waits.
+    static_assert(kMaxSym == 4 * kThreads, "four counts per thread");
+    auto my_quad = [&]() -> uint32_t {                               // (or it and what follows from it are held in registers all along)
+        uint32_t q = (uint32_t)tid;
+        asm volatile("" : "+v"(q));
+        return q;
+    };
+    uint32_t outl_before = 0;
+    auto store_counts = [&](uint32_t c, const uint4 &n, uint32_t wide, uint32_t outl) {
+        const uint64_t g = tc.chunk_base + c;
+        const uint32_t quad = my_quad(), byte_quad = quad - b.sym_off / 4u;      // below 64: symbols with a byte form
+        const uint2 pk = make_uint2(n.x | (n.y << 16), n.z | (n.w << 16));
+        if (byte_quad < 64u) reinterpret_cast<uint2 *>(b.chunk_hist + g * 256)[byte_quad] = pk;
+        if (wide) reinterpret_cast<uint2 *>(b.chunk_hist_all + g * kMaxSym)[quad] = pk;
+        if (quad == 0) { b.has_all[g] = wide; b.outl_cnt[g] = outl - outl_before; }
+        outl_before = outl;
+    };
+
+    const uint32_t c_end = nchunks - wg * b.sweep_chunks < b.sweep_chunks ? nchunks : (wg + 1) * b.sweep_chunks;
+    for (uint32_t c = wg * b.sweep_chunks; c < c_end; ++c) {
+        const bool first = c == wg * b.sweep_chunks;
+        uint4 counts = make_uint4(0, 0, 0, 0);
+        uint32_t wide_before = 0, outl = 0;
+        if (!first) { counts = reinterpret_cast<const uint4 *>(hist)[my_quad()]; wide_before = has_wide; outl = ocnt; }
         const uint32_t t0 = c * kChunk;                              // first element of the chunk
         const uint32_t t1 = (numel - t0 < kChunk) ? numel : t0 + kChunk;
-        __syncthreads();                                             // previous chunk's phase B is done with Q
-        if (tid == 0) ocnt = 0;
 
         // ---- phase A: quantise [t0 - (W+1) rounded down to 4, t1) into Q ----
         const uint32_t want = W + 1;
@@ -101,6 +123,7 @@ __global__ __launch_bounds__(kThreads) void k_quant_lorenzo_split_hist_tiled(Bat
             // slot of element g: kHalo + (g - t0); g - t0 is a multiple of 4 (t0 and g are)
             *reinterpret_cast<uint2 *>(&Q[(int)kHalo + (int)g - (int)t0]) = pk;
         }
+        if (!first) store_counts(c - 1, counts, wide_before, outl);
         __syncthreads();
 
         // ---- phase B: 16 consecutive elements per thread ----
@@ -198,13 +221,22 @@ __global__ __launch_bounds__(kThreads) void k_quant_lorenzo_split_hist_tiled(Bat
         }
         // Version 2: the zero residuals of a sub-block that holds nothing else are not counted (a thread
         // that found only zeros has touched no other bin).  A sub-block is sub/16 neighbouring threads.
-        if (!(b.zero_blocks && group_all(zeros == nhere, (uint32_t)lane, b.sub / 16u))) zero_run += zeros;
+        // The bit count of the chunk needs their number then; otherwise it follows from all the others.
+        if (b.zero_blocks) {                                         // uniform
+            const uint32_t tot = wave_inclusive_sum(group_all(zeros == nhere, (uint32_t)lane, b.sub / 16u) ? 0u : zeros);
+            if (lane == 63 && tot) atomicAdd(&hist[R], tot);
+        } else {
+            zero_run += zeros;
+        }
         {
             // the wave's quarter of the chunk: bytes if every symbol has a byte form.  The scratch holds
             // whole chunks: the stores past the end of the tensor stay inside the chunk's slot.
             const bool wide_q = __ballot(bytes_or > 0xffu) != 0;         // uniform in the wave
             const uint32_t quarter = (uint32_t)tid >> 6;
-            if (lane == 0) b.wide[(uint64_t)(tc.chunk_base + c) * 4 + quarter] = wide_q ? 1u : 0u;
+            if (lane == 0) {
+                b.wide[(uint64_t)(tc.chunk_base + c) * 4 + quarter] = wide_q ? 1u : 0u;
+                if (wide_q) has_wide = 1u;
+            }
             if (g0 < t1) {
                 if (wide_q) {
                     uint4 o0, o1;
@@ -229,11 +261,12 @@ __global__ __launch_bounds__(kThreads) void k_quant_lorenzo_split_hist_tiled(Bat
             }
         }
         if (nout) atomicAdd(&ocnt, nout);
-        __syncthreads();
-        if (tid == 0) b.outl_cnt[tc.chunk_base + c] = ocnt;
+        __syncthreads();                                             // phase B is done with Q, the counts are complete
     }
+    store_counts(c_end - 1, reinterpret_cast<const uint4 *>(hist)[tid], has_wide, ocnt);
 
     // zero residuals: one LDS atomic per wave
+    __syncthreads();
     {
         const uint32_t tot = wave_inclusive_sum(zero_run);
         if (lane == 63 && tot) atomicAdd(&hist[R], tot);
