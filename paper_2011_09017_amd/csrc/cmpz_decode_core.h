@@ -1,39 +1,44 @@
 // Huffman decode core shared by the decompression kernels: table layout and the
 // per-lane decode loop.  Internal to libcmpz.
 //
-// Two lookup levels.  Level 1 is indexed by the next kLB bits and resolves every
-// codeword of at most kLB bits.  Canonical codes grow with their length when
-// left-aligned, so all longer codewords sit above a threshold t32 in the
-// left-aligned code space; level 2 is indexed by (next 32 bits - t32) >> sh and
-// resolves codewords of up to 32 - sh bits.  Whatever is longer still is found by
-// canonical search: decode_lds compares with the limits in range[] for lengths below
-// 32 and from there on with first[], as decode_run does for all of them.
+// One lookup table, indexed by where the next 32 bits of the stream lie in the left-aligned code space, on
+// a logarithmic scale: x = how far they lie below the top of the space, the table has 2^m entries for
+// every power of two of x.  Canonical codes grow with their length when left-aligned, so a code of L bits
+// starts where about 2^-L times the codes of its length are left of the space, and an entry there is about as
+// wide as the code whatever its length.  On a linear scale 2048 + 256 entries in two levels left 1.4 %
+// (eb 1e-2) to 77 % (eb 1e-3) of a wave's steps to the search below, and 26 to 98 % to the second level;
+// on this one it is below 0.1 % with m = 7, and 12 % at eb 1e-3 with m = 8.  64x256x56x56 at eb 5e-3 and
+// 128 codes per sub-block: 220 -> 159 us, 128x96x55x55 at eb 1e-3 and 32: 152 -> 102.  Flat codebooks, whose codes are all
+// about ten bits long, keep a linear scale.  The conversion of x to floating point is the logarithm: its
+// exponent and the first m bits of its mantissa, less those of the smallest x of the table, are the index.
+// Whatever the table leaves is found by canonical search: decode_lds compares with the limits in range[]
+// for lengths below 32 and from there on with first[], as decode_run does for all of them.
 #pragma once
 #include "cmpz_internal.h"
 
 namespace cmpz {
 
-constexpr uint32_t kT1Size = 1u << kLB;
-constexpr uint32_t kT2Bits = 8;
-constexpr uint32_t kT2Size = 1u << kT2Bits;
+constexpr uint32_t kTableSize = 2304;        // entries: 4608 bytes of LDS, with the fused decoder's other arrays five
+                                             // workgroups just fit a CU
+constexpr uint32_t kLinearBits = 11;         // of the index on a linear scale (2048 entries)
+constexpr uint32_t kLogMask = ~0xffu;        // bits of x that the index looks at: 24, so that the conversion is exact
 
 // Table entries: symbol in bits 0..9, code length in bits 10..15; 0 = not resolved here.
 struct DecodeTables {
-    uint16_t t1[kT1Size];
-    uint16_t t2[kT2Size];
+    uint16_t entry[kTableSize];
     uint32_t sorted3[(kMaxSym + 2) / 3];   // symbols ordered by (length, symbol), each as its residual
                                   // (symbol - radius) in 10 bits, two's complement, three to a word
-                                  // (read only for codewords that neither table level resolves)
+                                  // (read only for codewords that the table does not resolve)
     uint64_t first[kMaxCodeLen + 2];   // first canonical code of each length (indexed by the length)
     // Per length, side by side so that the search takes both with one access:
     //   .x  largest left-aligned 32-bit value that belongs to a code of at most that length (exact up to 32
     //       bits, and from the length of the shortest code on; rounded down beyond: no limit to search by)
     //   .y  what turns a code of that length into its index in the ordered symbols (mod 2^32)
     uint2    range[kMaxCodeLen + 2];
-    uint32_t t32;                 // left-aligned threshold above which codes are longer than kLB
-    uint32_t sh;                  // level-2 shift
-    uint32_t has_long;            // any code longer than kLB bits
-    uint32_t searched;            // share of the code space that neither level resolves, in units of 2^-32
+    uint32_t log_shift;           // 22 - m, or 0: the scale is linear
+    uint32_t log_min;             // the smallest x of the table as a floating-point number's bits
+    uint32_t from;                // shortest length that the table leaves to the search, for some of its codes
+    uint32_t searched;            // share of the code space that it leaves, in units of 2^-32
     uint32_t max_len;
     uint32_t payload_units;
     uint32_t n_outliers;
@@ -65,7 +70,7 @@ __device__ __forceinline__ void load_tables(DecodeTables &dst, const DecodeTable
 // Validation of the container header and code lengths, and construction of the decode tables
 // in LDS, by one workgroup of NT >= 256 threads (every workgroup of the fused decode kernel does
 // this for itself: about a microsecond, and no separate kernel or round trip through memory).
-// The first 256 threads do the work (four symbols each); the others only help to fill level 1.
+// The first 256 threads do the work (four symbols each); the others only help to fill the table.
 // `scratch` is LDS the caller does not need yet (at least 12 KB; the ordered symbols are laid out
 // there as 16-bit values while the tables are filled).  Returns 0 or the status bits
 // of the defect found; contains barriers, so all NT threads must call it.
@@ -214,15 +219,37 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
             *used_s = used;
             T.max_len = max_len;
         }
-        if (lane == (int)kLB) {
-            // codes longer than kLB bits occupy left-aligned 32-bit values [t32, 2^32)
-            const uint64_t t = incl >> (kMaxCodeLen - 32);
-            const uint64_t span = (1ull << 32) - (t < (1ull << 32) ? t : (1ull << 32));
-            uint32_t sh = 0;
-            while ((span >> sh) > kT2Size) ++sh;
-            const uint32_t has_long = (max_len > kLB && span > 0) ? 1u : 0u;
-            T.t32 = (uint32_t)t; T.sh = sh; T.has_long = has_long;
-            T.searched = has_long ? (uint32_t)((1ull << 32) - (lim[32 - sh > kLB ? 32 - sh : kLB] >> (kMaxCodeLen - 32))) : 0u;
+        // The scale that leaves the least of the code space to the search.  With 2^m entries for every power of
+        // two of x and `powers` of these, codes of this lane's length have no entry where the entries are wider,
+        // and below the table's smallest x (whose own entry is not used: what lies below ends up there).
+        const uint64_t xh = (1ull << kMaxCodeLen) - excl, xl = (1ull << kMaxCodeLen) - incl;     // they lie in [xl, xh)
+        auto left_open = [&](uint32_t m, uint32_t powers) -> uint64_t {
+            if (cnt == 0) return 0;
+            const uint32_t k = 33u + m + (kMaxCodeLen - 32) - (uint32_t)lane;                    // (lane <= kMaxCodeLen)
+            const uint64_t wide_from = 1ull << (k < kMaxCodeLen ? k : kMaxCodeLen);
+            const uint64_t smallest = (1ull << (kMaxCodeLen - powers)) + (1ull << (kMaxCodeLen - powers - m));
+            const uint64_t a = xl > wide_from ? xl : wide_from, b = a < xh ? a : xh;             // no entry in [b, xh)
+            const uint64_t d = smallest < b ? smallest : b;                                      // nor in [xl, d)
+            return (xh - b) + (xl < d ? d - xl : 0ull);
+        };
+        auto total = [&](uint64_t u) -> uint32_t {                   // in units of 2^-31
+            return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum((uint32_t)(u >> (kMaxCodeLen - 31))), 63);
+        };
+        uint64_t best = lane > (int)kLinearBits && cnt ? xh - xl : 0ull;
+        uint32_t least = total(best), best_m = 0, best_powers = 0;
+#pragma unroll
+        for (uint32_t m = 9; m >= 7; --m) {
+            const uint32_t powers = m == 7 ? 17u : kTableSize >> m;  // (entries no narrower than kLogMask allows)
+            const uint64_t u = left_open(m, powers);
+            const uint32_t t = total(u);
+            if (t <= least) { best = u; least = t; best_m = m; best_powers = powers; }
+        }
+        const unsigned long long some = __ballot(best != 0);
+        if (lane == 0) {
+            T.log_shift = best_m ? 22u - best_m : 0u;
+            T.log_min = (127u + 32u - best_powers) << 23;
+            T.from = some ? (uint32_t)__ffsll((long long)some) - 1u : 1u;
+            T.searched = least < 0x7fffffffu ? 2u * least : 0xffffffffu;
         }
     }
     __syncthreads();
@@ -234,49 +261,32 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
         if (L[q]) sorted[T.range[L[q]].y + (uint32_t)T.first[L[q]] + wave_cnt[q * 4 + wv][L[q]] + in_wave[q]] = (uint16_t)((q * 256 + tid - a.radius) & 1023u);
     __syncthreads();
 
-    // level 1: entry idx is the codeword (if any, of at most kLB bits) that prefixes idx
+    // the table: an entry holds a codeword only if all of it lies inside that code's part of the space
     {
-        uint32_t l1[kLB + 1];
+        const uint32_t log_shift = T.log_shift, log_min = T.log_min, m = 22u - log_shift;
+        for (uint32_t idx = tid; idx < kTableSize; idx += NT) {
+            uint32_t v, longest;                                 // its smallest left-aligned value; the longest code it may hold
+            if (log_shift) {                                     // uniform
+                const uint32_t f = log_min + (idx << (log_shift + 1u));
+                const uint32_t power = (f >> 23) - 127u;                         // below 32 for all x there are
+                const uint32_t x = power < 32u ? (uint32_t)(((uint64_t)((f & 0x7fffffu) | 0x800000u) << power) >> 23) : 0u;
+                v = ~(x + (1u << ((power - m) & 31u)) - 1u);
+                longest = power < 32u && idx ? 32u - (power - m) : 0u;
+            } else {
+                v = idx << (32u - kLinearBits);
+                longest = idx < (1u << kLinearBits) ? kLinearBits : 0u;
+            }
+            const uint64_t v48 = (uint64_t)v << (kMaxCodeLen - 32);
+            uint32_t l = 0;                                      // lengths whose codes all lie below v
 #pragma unroll
-        for (uint32_t l = 1; l <= kLB; ++l) {
-            const uint64_t v = lim[l] >> (kMaxCodeLen - kLB);
-            l1[l] = v > kT1Size ? kT1Size : (uint32_t)v;
-        }
-#pragma unroll 2
-        for (uint32_t idx = tid; idx < kT1Size; idx += NT) {
-            uint32_t l = 1;
-#pragma unroll
-            for (uint32_t k = 1; k <= kLB; ++k) l += (idx >= l1[k]) ? 1u : 0u;
+            for (uint32_t step = 32; step >= 1; step >>= 1) l += (v48 >= lim[l + step]) ? step : 0u;
+            ++l;
             uint32_t e = 0;
-            if (l <= kLB) e = sorted[T.range[l].y + (idx >> (kLB - l))] | (l << 10);
-            T.t1[idx] = (uint16_t)e;
+            if (l <= longest) e = sorted[T.range[l].y + (v >> (32u - l))] | (l << 10);
+            T.entry[idx] = (uint16_t)e;
         }
     }
-    // level 2: entry i covers left-aligned 32-bit values t32 + [i << sh, (i+1) << sh); it holds a
-    // codeword only if the whole entry lies inside it (length at most 32 - sh)
-    if (worker) {
-        const uint32_t sh = T.sh, t32 = T.t32, has_long = T.has_long;
-        const uint32_t lmax = (32 - sh < T.max_len) ? 32 - sh : T.max_len;
-        constexpr int kPer = (int)kT2Size / 256;            // entries per thread
-        static_assert(kPer * 256 == (int)kT2Size, "level 2 is filled by 256 threads");
-        uint64_t v[kPer];
-        uint32_t l[kPer];
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) { v[k] = (uint64_t)t32 + ((uint64_t)(tid + 256 * k) << sh); l[k] = kLB + 1; }
-        for (uint32_t j = kLB + 1; j <= lmax; ++j) {          // uniform
-            const uint64_t lj = lim[j] >> (kMaxCodeLen - 32);
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) l[k] += (v[k] >= lj) ? 1u : 0u;
-        }
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            uint32_t e = 0;
-            if (has_long && v[k] < (1ull << 32) && l[k] <= lmax)
-                e = sorted[T.range[l[k]].y + (uint32_t)(v[k] >> (32 - l[k]))] | (l[k] << 10);
-            T.t2[tid + 256 * k] = (uint16_t)e;
-        }
-    }
-    // the ordered symbols in their packed form, for the codewords the two levels leave
+    // the ordered symbols in their packed form, for the codewords that the table leaves
     {
         const uint32_t used = *used_s;
         for (uint32_t w = tid; w < (kMaxSym + 2) / 3; w += NT) {
@@ -297,13 +307,17 @@ __device__ __forceinline__ int32_t entry_residual(uint32_t e)
     return __builtin_amdgcn_sbfe((int)e, 0, 10);
 }
 
-// Level 2 resolves every codeword of at most 32 - sh bits (its entries start at t32, a multiple
-// of 2^sh whenever such a codeword exists, so each one covers whole entries): the search over
-// the lengths starts behind them.
-__device__ __forceinline__ uint32_t first_unresolved_length(uint32_t sh)
+// The table's entry for the next 32 bits of a stream; 0: not resolved.
+__device__ __forceinline__ uint32_t log_offset(uint32_t hi, uint32_t log_shift, uint32_t log_min)
 {
-    const uint32_t l = 33u - sh;
-    return l > kLB + 1 ? l : kLB + 1;
+    uint32_t x;                                               // ~hi & kLogMask in one instruction
+    asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(x) : "v"(hi), "s"(kLogMask));
+    // (what lies below the smallest x saturates to entry 0, which is empty)
+    return (__builtin_elementwise_sub_sat(__float_as_uint((float)x), log_min) >> log_shift) & ~1u;
+}
+__device__ __forceinline__ uint32_t linear_offset(uint32_t hi)
+{
+    return (hi >> (31u - kLinearBits)) & ((2u << kLinearBits) - 2u);
 }
 
 // Decode `count` codewords that start at bit `start` of a chunk stream whose 32-bit words
@@ -315,7 +329,7 @@ __device__ __forceinline__ uint32_t first_unresolved_length(uint32_t sh)
 //
 // The bit window is refilled from a word fetched one refill ahead, so the only memory
 // latency on the per-symbol dependency chain is the table lookup.
-template <bool EAGER, class RD, class PUT>
+template <class RD, class PUT>
 __device__ __forceinline__ uint32_t decode_run(const DecodeTables &T, RD rd, uint32_t start, uint32_t count,
                                                uint32_t klo, PUT put, bool &bad)
 {
@@ -324,40 +338,28 @@ __device__ __forceinline__ uint32_t decode_run(const DecodeTables &T, RD rd, uin
     int avail = 64 - (int)(start & 31);
     wi += 2;
     uint32_t nxt = rd(wi);
-    const uint32_t t32 = T.t32, sh = T.sh, has_long = T.has_long;
+    const uint32_t log_shift = uniform_u32(T.log_shift), log_min = uniform_u32(T.log_min);
+    const char *table = reinterpret_cast<const char *>(T.entry);
     for (uint32_t k = 0; k < count; ++k) {
-        if (EAGER) {
-            // cheap reads (LDS): branch-free refill, the next word is refetched every step
-            const bool need = avail <= 32;
-            const uint64_t add = ((uint64_t)nxt) << ((32 - avail) & 31);
-            win |= need ? add : 0ull;
-            avail += need ? 32 : 0;
-            wi += need ? 1u : 0u;
-            nxt = rd(wi);
-        } else if (avail <= 32) {
-            // global memory: touch the prefetched word only here, so that its latency is waited
-            // for once per consumed word and not on every step
+        if (avail <= 32) {
+            // touch the prefetched word only here, so that its latency is waited for once per consumed
+            // word and not on every step
             win |= ((uint64_t)nxt) << (32 - avail);
             avail += 32;
             ++wi;
             nxt = rd(wi);
         }
         const uint32_t hi = (uint32_t)(win >> 32);
-        uint32_t e = T.t1[hi >> (32 - kLB)];
+        uint32_t e = *reinterpret_cast<const uint16_t *>(table + (log_shift ? log_offset(hi, log_shift, log_min) : linear_offset(hi)));
         if (e == 0) {
-            if (has_long) {
-                uint32_t i2 = (hi - t32) >> sh;
-                i2 = i2 < kT2Size ? i2 : kT2Size - 1;
-                e = T.t2[i2];
-            }
-            if (e == 0) {
-                // canonical search on a fresh 64-bit window (codes longer than level 2 resolves)
+            {
+                // canonical search on a fresh 64-bit window
                 uint32_t pos = 32u * wi - (uint32_t)avail;
                 const uint32_t w0 = pos >> 5, off = pos & 31;
                 uint64_t w64 = ((((uint64_t)rd(w0)) << 32) | rd(w0 + 1)) << off;
                 if (off) w64 |= (uint64_t)(rd(w0 + 2) >> (32 - off));
                 uint32_t len = 0, sy = 0;                    // no match: residual 0
-                for (uint32_t L = has_long ? first_unresolved_length(sh) : kLB + 1; L <= T.max_len; ++L) {
+                for (uint32_t L = T.from; L <= T.max_len; ++L) {
                     const uint64_t code = w64 >> (64 - L);
                     if (code >= T.first[L] && code - T.first[L] < codes_of_length(T, L)) {
                         sy = sorted_at(T, T.range[L].y + (uint32_t)code);
@@ -394,20 +396,17 @@ __device__ __forceinline__ uint32_t decode_run(const DecodeTables &T, RD rd, uin
 // (stage_tail_words).
 constexpr uint32_t stage_tail_words(uint32_t count) { return count * kMaxCodeLen / 32 + 4; }
 //
-// BOTH: the two table levels are looked up side by side, and only codewords that neither resolves
-// take a branch.  Five more instructions per step, so not for loops that keep the vector units busy
-// (32 codes per sub-block: 0.937 -> 0.952 ms on the ResNet-18-shaped stream), but a shorter chain
-// where codes of more than kLB bits are common (64x256x56x56 at eb 5e-3, pooled: 277 -> 243 us).
+// LOG: the scale of the table (see there).
 constexpr int kStagePad = 4;
-template <bool BOTH, class PUT>
+template <bool LOG, class PUT>
 __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint32_t *S, uint32_t pos,
                                                uint32_t count, uint32_t skip, PUT put, bool &bad)
 {
-    const uint32_t t32 = T.t32, sh = T.sh;
-    const char *t1 = reinterpret_cast<const char *>(T.t1);
+    const uint32_t log_shift = uniform_u32(T.log_shift), log_min = uniform_u32(T.log_min);
+    const char *table = reinterpret_cast<const char *>(T.entry);
     // The three stream words around the position live in registers: wa, wb are the window of the
-    // current codeword, wc the word after them.  A codeword of the first two table levels is at
-    // most 27 bits long, so the window moves on by one word at most, and the word that then
+    // current codeword, wc the word after them.  A codeword of the table is at
+    // most 24 bits long, so the window moves on by one word at most, and the word that then
     // becomes wc is fetched a whole step before it can be needed: the only LDS access a step
     // has to wait for is the table look-up.
     uint32_t npos = 0u - pos;                                 // alignbit takes its shift from -pos mod 32
@@ -422,22 +421,10 @@ __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint
 #pragma unroll 4
     for (uint32_t k = 0; k < count; ++k) {
         const uint32_t hi = __builtin_amdgcn_alignbit(wa, wb, npos);
-        uint32_t e = *reinterpret_cast<const uint16_t *>(t1 + ((hi >> (31 - kLB)) & (2u * kT1Size - 2u)));
-        if (BOTH) {
-            uint32_t i2 = (hi - t32) >> sh;                   // (below t32 the first level has the codeword)
-            i2 = i2 < kT2Size ? i2 : kT2Size - 1;
-            const uint32_t e2 = T.t2[i2];
-            e = e ? e : e2;
-        }
+        uint32_t e = *reinterpret_cast<const uint16_t *>(table + (LOG ? log_offset(hi, log_shift, log_min) : linear_offset(hi)));
         if (__builtin_expect(e == 0, 0)) {
-            if (!BOTH) {
-                // (a codebook without long codes has a second table of zeros: no test for that case)
-                uint32_t i2 = (hi - t32) >> sh;
-                i2 = i2 < kT2Size ? i2 : kT2Size - 1;
-                e = T.t2[i2];
-            }
-            if (__builtin_expect(e == 0, 0)) {
-                // canonical search over the lengths the second level does not resolve.  Up to 31 bits the
+            {
+                // canonical search over the lengths that the table does not resolve.  Up to 31 bits the
                 // length is the first one whose limit is not below the window; the next length's limit is
                 // fetched beside the present one's.  Latency of LDS accesses bounds this: four limits per
                 // look, and the way to the symbol behind them, took longer where the first length or two
@@ -445,7 +432,7 @@ __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint
                 // eb 1e-3 and 32 codes 61.9 -> 59.3 (one length per look: 219 and 60.2).
                 uint32_t len = 0, sy = 0;                     // no match: residual 0
                 const uint32_t max_len = T.max_len;
-                uint32_t L = first_unresolved_length(sh);
+                uint32_t L = T.from;
                 uint2 r = T.range[L], next = T.range[L + 1];
                 while (L < 32u && hi > r.x) {
                     ++L; r = next;

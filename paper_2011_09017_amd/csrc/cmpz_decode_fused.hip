@@ -160,6 +160,10 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
             return;
         }
     }
+    const bool log_scale = uniform_u32(T.log_shift) != 0;
+    auto decode_staged = [&](const uint32_t *stage, uint32_t pos, uint32_t count, uint32_t skip, auto put, bool &lbad) -> uint32_t {
+        return log_scale ? decode_lds<true>(T, stage, pos, count, skip, put, lbad) : decode_lds<false>(T, stage, pos, count, skip, put, lbad);
+    };
     // ---- from here on the waves are on their own ----
     RT       *R = lds.Rs[wv];
     uint32_t *S = lds.Ss + wv * kStageWords;             // the wave's payload starts at S + kStagePad
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                         const uint32_t to_l = (uint32_t)__builtin_amdgcn_readlane((int)to, l),
                                        from_l = (uint32_t)__builtin_amdgcn_readlane((int)from, l);
                         if (lane == l) {
-                            const uint32_t e = decode_lds<false>(T, lds.Ss, spos, to_l, from_l, put, lbad);
+                            const uint32_t e = decode_staged(lds.Ss, spos, to_l, from_l, put, lbad);
                             if (fl & 0x800u) end = e;
                         }
                     }
@@ -433,7 +437,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                     if ((fl & 0xa000u) == 0xa000u) {
                         for (uint32_t k = from; k < to; ++k) put(k, 0);
                     } else if ((fl & 0x9000u) == 0x9000u) {
-                        end = decode_lds<true>(T, lds.Ss, spos, (uint32_t)SUB, 0u, put, lbad);
+                        end = decode_staged(lds.Ss, spos, (uint32_t)SUB, 0u, put, lbad);
                     }
                 }
                 bad |= lbad || end != spos + sb;
@@ -479,8 +483,8 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                         return start;
                     }
                     if (staged)
-                        return decode_lds<false>(T, S, spos, count, skip, put, lbad) - spos + start;
-                    return decode_run<false>(T, [&](uint32_t k) -> uint32_t { return gw[k < last ? k : last]; }, start,
+                        return decode_staged(S, spos, count, skip, put, lbad) - spos + start;
+                    return decode_run(T, [&](uint32_t k) -> uint32_t { return gw[k < last ? k : last]; }, start,
                                              count, skip, put, lbad);
                 };
                 if (SUB == 32 && n_here == 32u && folded) {

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(DecompressArgs a, const 
             end = start;
         } else if (nwords) {
             const uint32_t last = nwords - 1;
-            end = decode_run<false>(T, [&](uint32_t k) -> uint32_t { return words[k < last ? k : last]; }, start, n_here, 0u,
+            end = decode_run(T, [&](uint32_t k) -> uint32_t { return words[k < last ? k : last]; }, start, n_here, 0u,
                              [&](uint32_t k, int32_t d) { my[k] = (int16_t)d; }, bad);
         }
         if (end != start + sb) bad = true;

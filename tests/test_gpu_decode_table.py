@@ -1,0 +1,59 @@
+"""GPU parity of the decode table over the codebooks between which its scale is chosen: steep and flat ones, a
+single symbol, two levels of frequency, all 1024 symbols, codes that the table leaves to the search.
+
+Bar: the container equals the CPU oracle's byte for byte, the reconstruction bit for bit.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+EB = 1e-2
+STEP = float(np.float32(2) * (np.float32(EB) - np.float32(np.ldexp(np.float32(EB), -7))))
+N = 300_000
+
+
+def symbols(kind, rng):
+    """N residuals (planes of one element: every value is its own residual)."""
+    name, a = kind
+    if name == "flat":                       # a symbols, equally frequent
+        return rng.integers(0, a, N) - a // 2
+    if name == "steep":                      # a symbols for every bit of code length
+        d = np.floor(rng.exponential(a / np.log(2) / 2, N)).astype(np.int64) * rng.choice([-1, 1], N)
+        return np.clip(d, -511, 511)
+    if name == "peak":                       # one symbol with a share of a, the rest flat
+        return np.where(rng.random(N) < a, 3, rng.integers(-511, 512, N))
+    assert name == "two"                     # a flat group of each of two frequencies
+    return np.where(rng.random(N) < 0.97, rng.integers(0, a, N), rng.integers(-500, -100, N))
+
+
+@pytest.mark.parametrize("sub", [32, 64, 128])
+@pytest.mark.parametrize("kind", [("flat", 1), ("flat", 2), ("flat", 3), ("flat", 200), ("flat", 512), ("flat", 1000), ("flat", 1023),
+                                  ("steep", 1), ("steep", 4), ("steep", 16), ("steep", 60), ("steep", 140), ("steep", 300),
+                                  ("peak", 0.5), ("peak", 0.99), ("peak", 0.9999), ("two", 7), ("two", 90)])
+def test_scales(kind, sub, orc):
+    from paper_2011_09017_amd import binding as gpu
+    rng = np.random.default_rng(11)
+    x = (symbols(kind, rng) * STEP).astype(np.float32).reshape(1, N, 1, 1)
+    cfg = orc.Config(sub=sub)
+    rc, obuf, osize, _ = orc.compress(x, EB, cfg)
+    assert rc == 0
+    rc, oy = orc.decompress(obuf, x.shape, EB, cfg)
+    assert rc == 0
+    ctx = gpu.Context(sub=sub, max_numel=N)
+    buf, size, rc = ctx.compress(torch.from_numpy(x).cuda(), EB)
+    assert rc == 0 and size == osize and np.array_equal(buf[:size].cpu().numpy(), obuf)
+    y = ctx.decompress(buf, size, x.shape, EB)
+    assert ctx.last_status() == 0
+    assert np.array_equal(y.cpu().numpy().view(np.uint32), oy.view(np.uint32))
+    # the same elements as one plane of wide rows: the unfused kernels decode from memory
+    wide = x.reshape(1, 1, 400, N // 400)
+    rc, obuf, osize, _ = orc.compress(wide, EB, cfg)
+    rc2, oy = orc.decompress(obuf, wide.shape, EB, cfg)
+    assert rc == 0 and rc2 == 0
+    buf, size, rc = ctx.compress(torch.from_numpy(wide).cuda(), EB)
+    assert rc == 0 and size == osize and np.array_equal(buf[:size].cpu().numpy(), obuf)
+    y = ctx.decompress(buf, size, wide.shape, EB)
+    assert ctx.last_status() == 0
+    assert np.array_equal(y.cpu().numpy().view(np.uint32), oy.view(np.uint32))
