@@ -315,9 +315,43 @@ __device__ __forceinline__ uint32_t log_offset(uint32_t hi, uint32_t log_shift, 
     // (what lies below the smallest x saturates to entry 0, which is empty)
     return (__builtin_elementwise_sub_sat(__float_as_uint((float)x), log_min) >> log_shift) & ~1u;
 }
+// the same for m = 7, where the exponent and the bits of the mantissa are the upper half of the number
+constexpr uint32_t kShift7 = 22 - 7;
+// (`one` is 1, in a vector register)
+__device__ __forceinline__ uint32_t log7_offset(uint32_t hi, uint32_t log_min, uint32_t one)
+{
+    uint32_t x;
+    asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(x) : "v"(hi), "s"(kLogMask));
+    const uint32_t above = __builtin_elementwise_sub_sat(__float_as_uint((float)x), log_min);
+    uint32_t r;                                               // (above >> 16) << 1 in one instruction
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(r) : "v"(one), "v"(above));
+    return r;
+}
 __device__ __forceinline__ uint32_t linear_offset(uint32_t hi)
 {
     return (hi >> (31u - kLinearBits)) & ((2u << kLinearBits) - 2u);
+}
+
+// Canonical search over the lengths that the table does not resolve, for the entry it would have; v: the next 64
+// bits of the stream, of which kMaxCodeLen count.  As in decode_lds.
+__device__ __forceinline__ uint32_t search(const DecodeTables &T, uint64_t v, bool &bad)
+{
+    const uint32_t hi = (uint32_t)(v >> 32), max_len = T.max_len;
+    uint32_t L = T.from;
+    uint2 r = T.range[L];
+    while (L < 32u && hi > r.x) r = T.range[++L];
+    if (L <= max_len && L < 32u) {
+        const uint32_t i = (hi >> (32u - L)) + r.y;
+        if (i < kMaxSym) return sorted_at(T, i) | (L << 10);
+    }
+    if (max_len >= 32u) {
+        for (; L <= max_len; ++L) {
+            const uint64_t code = v >> (64 - L);
+            if (code >= T.first[L] && code - T.first[L] < codes_of_length(T, L)) return sorted_at(T, T.range[L].y + (uint32_t)code) | (L << 10);
+        }
+    }
+    bad = true;
+    return 1u << 10;                                             // no match: residual 0, one bit further on
 }
 
 // Decode `count` codewords that start at bit `start` of a chunk stream whose 32-bit words
@@ -475,6 +509,82 @@ __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint
         }
         N = Nn;
         if (k >= skip) put(k, entry_residual(e));
+    }
+    return 0u - npos;
+}
+
+// The scale of the table, as decode_rows_32 takes it.
+enum Scale : int { kScaleLinear = 0, kScaleLog = 1, kScaleLog7 = 2 };
+
+// decode_lds for complete sub-blocks of 32 codes, whose residuals are summed along the rows: bit k of
+// `keep` is 0 where element k starts a row; my[k] takes the sum.  Four codewords at a time: one that the table does
+// not resolve has entry 0, which moves nothing, so that the ones behind it find the same; whether there was any is
+// looked at once, behind the four.  Against a look behind every one (17 vector and 3 scalar
+// instructions per codeword, now 15.5 and 1): @@.
+template <int SCALE>
+__device__ __forceinline__ uint32_t decode_rows_32(const DecodeTables &T, const uint32_t *S, uint32_t pos, uint32_t keep,
+                                                   int16_t *my, bool &bad)
+{
+    const uint32_t log_shift = uniform_u32(T.log_shift), log_min = uniform_u32(T.log_min);
+    const char *table = reinterpret_cast<const char *>(T.entry);
+    uint32_t npos = 0u - pos;
+    int32_t N = (int32_t)npos >> 5;
+    const uint32_t *Sw = S + kStagePad;
+    typedef const uint32_t __attribute__((address_space(3))) *lds_word_ptr;
+    const uint32_t sw1 = (uint32_t)(uintptr_t)(lds_word_ptr)(Sw + 1);
+    uint32_t wa = Sw[-1 - N], wb = Sw[-N], wc = Sw[1 - N];
+    int32_t run = 0;
+    uint32_t one = 1;
+    asm("" : "+v"(one));
+    auto look = [&](uint32_t hi) -> uint32_t {
+        const uint32_t at = SCALE == kScaleLog7 ? log7_offset(hi, log_min, one) : SCALE == kScaleLog ? log_offset(hi, log_shift, log_min) : linear_offset(hi);
+        uint32_t e = *reinterpret_cast<const uint16_t *>(table + at);
+        asm("" : "+v"(e));                                    // (or it is kept as 16 bits and extended again)
+        return e;
+    };
+    // one codeword on (see decode_lds)
+    auto advance = [&](uint32_t e, uint32_t k) {
+        npos -= e >> 10;
+        const int32_t Nn = (int32_t)npos >> 5;
+        const bool moved = Nn != N;
+        wa = moved ? wb : wa;
+        wb = moved ? wc : wb;
+        uint32_t at;
+        asm("v_mad_i32_i24 %0, %1, -4, %2" : "=v"(at) : "v"(Nn), "s"(sw1));
+        wc = *(lds_word_ptr)(uintptr_t)at;
+        N = Nn;
+        // run * (0 where the row restarts, else 1) + residual in one multiply-add: the sums of a
+        // lane's 32 in-range residuals stay far inside 24 bits
+        const uint32_t keep01 = __builtin_amdgcn_ubfe(keep, k, 1);
+        asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(run) : "v"(run), "v"(keep01), "v"(entry_residual(e)));
+        // (volatile: or two of them become one access that is not aligned)
+        *(volatile int16_t __attribute__((address_space(3))) *)(my + k) = (int16_t)run;
+    };
+#pragma unroll 1
+    for (uint32_t group = 0; group < 32u; group += 4) {
+        const uint32_t k = uniform_u32(group);                // (the branch below would take it to a vector register)
+        uint32_t e[4];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            e[j] = look(__builtin_amdgcn_alignbit(wa, wb, npos));
+            advance(e[j], k + j);
+        }
+        if (__builtin_expect(e[3] == 0, 0)) {
+            uint32_t at = k + (e[0] != 0) + (e[1] != 0) + (e[2] != 0);
+            run = at ? my[at - 1] : 0;
+#pragma unroll 1
+            for (; at < k + 4; ++at) {
+                const uint32_t hi = __builtin_amdgcn_alignbit(wa, wb, npos);
+                uint32_t en = look(hi);
+                if (en == 0) {
+                    en = search(T, ((uint64_t)hi << 32) | __builtin_amdgcn_alignbit(wb, wc, npos), bad);
+                    // such a codeword may end two words further on: take the first of the two moves here
+                    const int32_t Nf = (int32_t)(npos - (en >> 10)) >> 5;
+                    if (Nf < N - 1) { wa = wb; wb = wc; wc = Sw[2 - N]; --N; }
+                }
+                advance(en, at);
+            }
+        }
     }
     return 0u - npos;
 }

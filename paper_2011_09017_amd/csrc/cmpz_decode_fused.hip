@@ -494,15 +494,19 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                     uint32_t k0 = klo + (w_first ? W - w_first : 0u);
                     my_reset = k0 < 32u ? k0 : (uint32_t)SUB;
                     for (; k0 < 32u; k0 += W) mask |= 1u << k0;
-                    int32_t run = 0;
-                    const uint32_t keep_mask = ~mask;
-                    end = run_decode(32u, 0u, [&](uint32_t k, int32_t d) {
-                        // run * (0 where the row restarts, else 1) + d in one multiply-add: the sums of a
-                        // lane's 32 in-range residuals stay far inside 24 bits
-                        const uint32_t keep01 = __builtin_amdgcn_ubfe(keep_mask, k, 1);
-                        asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(run) : "v"(run), "v"(keep01), "v"(d));
-                        my[k] = run;
-                    });
+                    if (staged && !zeros_only) {
+                        const uint32_t shift = uniform_u32(T.log_shift);
+                        const uint32_t e = shift == kShift7 ? decode_rows_32<kScaleLog7>(T, S, spos, ~mask, my, lbad)
+                                         : shift ? decode_rows_32<kScaleLog>(T, S, spos, ~mask, my, lbad)
+                                                 : decode_rows_32<kScaleLinear>(T, S, spos, ~mask, my, lbad);
+                        end = e - spos + start;
+                    } else {
+                        int32_t run = 0;
+                        end = run_decode(32u, 0u, [&](uint32_t k, int32_t d) {
+                            run = ((mask >> k) & 1u) ? d : run + d;
+                            my[k] = run;
+                        });
+                    }
                     my_tail = my[khi - 1];
                 } else if (folded) {
                     // running sum along the row, restarted at every row start
