@@ -168,8 +168,10 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     RT       *R = lds.Rs[wv];
     uint32_t *S = lds.Ss + wv * kStageWords;             // the wave's payload starts at S + kStagePad
     uint32_t *P = S + kPOff;
-    // per decode lane, after the decode: .x = offset of the lane's first row start (elements before
-    // it lack the carry), .y = the carry
+    // Element u of wave j's band is element j * kBandMax + u of all bands, `place` twice that, and with a pad slot
+    // behind every SUB elements it lies at byte place + 2 * (place / (2 * SUB)) of Rs, whatever the wave.
+    // Per decode lane, after the decode: .x = place of the lane's first row start (elements before it lack the
+    // carry), .y = the carry
     uint2 *RC = reinterpret_cast<uint2 *>(S + kStagePad);
     const uint32_t payload_units = T.payload_units, n_outl = T.n_outliers;
     // (uniform in the workgroup; nor where a band's share of the payload does not fit the staging buffer)
@@ -575,7 +577,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
             // what flows into a lane is the inclusive value of the lane before it; a band begins a row
             int32_t into = (int32_t)dpp_u32<0x138, 0xf>((uint32_t)v);   // wave_shr:1
             if (lane == 0) into = 0;
-            if (lane < kND) RC[lane] = make_uint2(lane < (int)nsb ? my_reset : 0u, (uint32_t)into);
+            if (lane < kND) RC[lane] = make_uint2(lane < (int)nsb ? 2u * (wv * kBandMax + lane * SUB + my_reset) : 0u, (uint32_t)into);
         }
         wave_sync();
 
@@ -589,39 +591,39 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
 
         // ---- column prefix sums (adding the lanes' carries), de-quantisation, stores: one lane per column ----
         const uint32_t nrow = pl.big ? rows : H;
-        // One column of a band (Rj: its sums along the rows, RCj: its lane records, first element
-        // uj0 slots into Rj, nrowj rows, output from outj on), continuing the column sum acc.
+        // One column of a band (of wave j: its sums along the rows and its lane records; first element uj0, nrowj
+        // rows, output from outj on), continuing the column sum acc.
         // Byte offsets from the band's first output element: the stores then take a uniform base
         // and a 32-bit offset per lane.
-        auto walk_band = [&](const RT *Rj, const uint2 *RCj, uint32_t uj0, uint32_t nrowj, char *__restrict__ band_out,
-                             uint32_t col, int32_t acc) -> int32_t {
-            const RT *R = Rj;
-            const uint2 *RC = RCj;
-            const uint32_t nrow = nrowj;
+        auto walk_band = [&](uint32_t j, uint32_t uj0, uint32_t nrow, char *__restrict__ band_out, uint32_t col, int32_t acc) -> int32_t {
+            const char *const sums = reinterpret_cast<const char *>(&lds.Rs[0][0]);
+            // (records by place: those of the waves before this one are not there)
+            const char *const records = reinterpret_cast<const char *>(lds.Ss + kStagePad + j * kStageWords) - 8u * kND * j;
             const uint32_t p = pl.big ? 0u : pl.divW.div(col);
             const uint32_t w = col - p * W;
-            uint32_t u = p * HW + w + uj0;
+            uint32_t place = 2u * (j * kBandMax + p * HW + w + uj0);
             uint32_t off = (p * HW + w) * 4u;
             // kRows rows at a time, their loads in flight together; then the short batch that may remain
             auto batch = [&](auto full_c, uint32_t nr) {
                 constexpr bool kFull = decltype(full_c)::value;
                 int32_t t8[kRows];
-                uint32_t kk[kRows];
+                uint32_t at[kRows];
                 uint2 rc[kRows];
 #pragma unroll
                 for (int q = 0; q < kRows; ++q) {
                     if (kFull || (uint32_t)q < nr) {
-                        const uint32_t uq = u + q * W;
-                        uint32_t t = uq >> kLog;
-                        asm("" : "+v"(t));           // one shift serves both addresses below (else the compiler derives each from uq anew)
-                        kk[q] = uq & (uint32_t)(SUB - 1);
-                        t8[q] = R[uq + t]; rc[q] = RC[t];
+                        at[q] = place + q * 2u * W;
+                        asm("" : "+v"(at[q]));       // (or the compiler derives the addresses below anew, each from its own sum)
+                        uint32_t t = at[q] >> (kLog + 1);
+                        asm("" : "+v"(t));
+                        t8[q] = *reinterpret_cast<const RT *>(sums + (2u * t + at[q]));
+                        rc[q] = *reinterpret_cast<const uint2 *>(records + 8u * t);
                     }
                 }
 #pragma unroll
                 for (int q = 0; q < kRows; ++q) {
                     if (kFull || (uint32_t)q < nr) {
-                        acc += t8[q] + ((kk[q] < rc[q].x) ? (int32_t)rc[q].y : 0);
+                        acc += t8[q] + ((at[q] < rc[q].x) ? (int32_t)rc[q].y : 0);
                         // the row's offset is uniform: it goes to the scalar base, the lane keeps one offset
                         *reinterpret_cast<float *>((band_out + (size_t)(q * 4u * W)) + off) = (float)(int16_t)acc * s;
                     }
@@ -630,14 +632,14 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
             uint32_t h = 0;
             for (; h + kRows <= nrow; h += kRows) {
                 batch(std::true_type{}, (uint32_t)kRows);
-                u += kRows * W;
+                place += kRows * 2u * W;
                 off += 4u * kRows * W;
             }
             if (h < nrow) batch(std::false_type{}, nrow - h);        // uniform
             return acc;
         };
         auto walk = [&](uint32_t col, int32_t acc) -> int32_t {
-            return walk_band(R, RC, u0, nrow, reinterpret_cast<char *>(a.xout + e0), col, acc);
+            return walk_band(wv, u0, nrow, reinterpret_cast<char *>(a.xout + e0), col, acc);
         };
         if (coop) {
             // every wave has decoded its band of this round: now a quarter of the columns each,
@@ -654,8 +656,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                         if (row0 >= H) break;                        // uniform
                         const uint32_t rowsj = (H - row0 < pl.Rb) ? H - row0 : pl.Rb;
                         const uint32_t ej0 = item * HW + row0 * W;
-                        acc = walk_band(lds.Rs[j], reinterpret_cast<const uint2 *>(lds.Ss + j * kStageWords + kStagePad),
-                                        ej0 - ((ej0 >> kLog) << kLog), rowsj, reinterpret_cast<char *>(a.xout + ej0), col, acc);
+                        acc = walk_band(j, ej0 - ((ej0 >> kLog) << kLog), rowsj, reinterpret_cast<char *>(a.xout + ej0), col, acc);
                     }
                     colacc[c] = acc;
                 }
