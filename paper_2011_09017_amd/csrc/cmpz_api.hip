@@ -518,12 +518,12 @@ int cmp_arena_push(cmp_ctx *ctx, void *d_arena, size_t arena_cap, void *d_state,
     BatchC b;
     group_begin(&b, ctx->cfg, ctx->s);
     group_add(&b, ck, d_arena, arena_cap);
-    b.t[0].arena = static_cast<const ArenaState *>(d_state);
+    b.t[0].arena = static_cast<ArenaState *>(d_state);
+    b.t[0].arena_slot = slot;
     group_plan_sweep(&b, ctx->cus);
     group_plan_pack(&b, ctx->cus);
     group_launch_begin(b, &ctx->prof, st);
     group_launch_finish(b, &ctx->prof, st);
-    launch_arena_pushed(b, static_cast<ArenaState *>(d_state), slot, st);
     ctx->last_numel = b.t[0].numel;
     ctx->last_out = nullptr;                                   // its place is known to the GPU only
     return hipGetLastError() == hipSuccess ? CMP_OK : CMP_E_HIP;
@@ -547,7 +547,8 @@ int cmp_arena_pop(cmp_ctx *ctx, const void *d_arena, void *d_state, uint32_t slo
     TensorD &t = b.t[0];
     t.buf = static_cast<const uint8_t *>(d_arena);
     t.size = 0;
-    t.slot = static_cast<const ArenaState *>(d_state)->slot + slot;      // address arithmetic only: a device pointer
+    t.arena = static_cast<ArenaState *>(d_state);
+    t.arena_slot = slot;
     t.xout = d_xout;
     for (int k = 0; k < 4; ++k) t.shape[k] = (uint32_t)shape[k];
     t.numel = (uint32_t)numel;
@@ -560,7 +561,6 @@ int cmp_arena_pop(cmp_ctx *ctx, const void *d_arena, void *d_state, uint32_t slo
     if (!guard.ok) return CMP_E_HIP;
     hipStream_t st = static_cast<hipStream_t>(stream);
     launch_decode_fused(b, ctx->cus, &ctx->prof, st);
-    launch_arena_release(static_cast<ArenaState *>(d_state), slot, st);
     return hipGetLastError() == hipSuccess ? CMP_OK : CMP_E_HIP;
 }
 

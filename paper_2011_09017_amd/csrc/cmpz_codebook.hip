@@ -9,7 +9,7 @@
 // The merge runs in rounds that join up to 32 pairs at once (see step 4).  Sorting is by
 // counting ranks in blocks of 64 and binary search across blocks, depths by walking parent
 // links, ranks within a length by wave ballots.
-#include "cmpz_internal.h"
+#include "cmpz_offsets.h"
 
 namespace cmpz {
 namespace {
@@ -71,6 +71,8 @@ __device__ __forceinline__ uint64_t bitonic_merge_64(uint64_t k, int lane)
     return exchange_dpp<0xB1>(k, (lane & 1) != 0);           // quad_perm 1,0,3,2
 }
 
+// SMALL: the tensors' offsets and headers too (see small_group).
+template <bool SMALL>
 __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
 {
     // one workgroup per tensor of the group
@@ -259,13 +261,80 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     // container section `lens`: 2*radius bytes, zero padded to a multiple of 16
     const uint32_t padded = (nsym + 15u) & ~15u;
     if ((uint32_t)tid < padded && oref.cap >= kHeaderBytes + padded) out[kHeaderBytes + tid] = ((uint32_t)tid < nsym) ? (uint8_t)L : 0;
+    if (!SMALL) return;
+
+    // 7. a small tensor's bit counts, offsets and header, without the two launches that spread this over the chip.
+    //    Bound by the latency of the loads: every wave takes consecutive chunks, four at a time, and learns
+    //    beforehand which of them have symbols without a byte form.
+    const TensorC &tc = b.t[ti];
+    uint8_t *lens_s = reinterpret_cast<uint8_t *>(leaf_w);           // (what the tree was built in is free)
+    uint32_t *bits_s = node_w;
+    static_assert(kSmallChunks <= kMaxSym && kSmallChunks <= (uint32_t)kCbThreads, "a thread and a word of node_w per chunk");
+    lens_s[tid] = (uint8_t)L;
+    __syncthreads();
+    {
+        ChunkBits cb(b, leaf_w, lane);
+        constexpr uint32_t kTogether = 4;                            // chunks whose loads are in flight together
+        const uint32_t per = (tc.nchunks + 15u) >> 4, first = wv * per;
+        const uint32_t end = first + per < tc.nchunks ? first + per : tc.nchunks;
+        uint2 before = make_uint2(0, 0);
+        if (first < end && first) before = cb.row(tc.chunk_base + first - 1);
+        uint64_t wide = 0;                                           // of the wave's chunks from c on
+        static_assert(kSmallChunks <= 16 * kWave, "a lane per chunk of a wave");
+        if (first + lane < end) wide = cb.is_wide(tc.chunk_base + first + lane);
+        wide = __ballot(wide != 0);
+        for (uint32_t c = first; c < end; c += kTogether, wide >>= kTogether) {          // uniform
+            uint2 v[kTogether] = {}, o[kTogether][ChunkBits::kOthers] = {};
+#pragma unroll
+            for (uint32_t j = 0; j < kTogether; ++j) {
+                if (c + j < end) v[j] = cb.row(tc.chunk_base + c + j);
+                if ((wide >> j) & 1u) cb.fetch_others(tc.chunk_base + c + j, o[j]);
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < kTogether; ++j) {
+                if (c + j >= end) break;
+                const uint32_t bits = cb.chunk(tc, c + j, before, v[j], (wide >> j) & 1u, [&] { return cb.others_bits(o[j]); });
+                if (lane == 63) bits_s[c + j] = bits;
+                before = v[j];
+            }
+        }
+    }
+    __syncthreads();
+    const bool there = (uint32_t)tid < tc.nchunks;
+    const uint32_t bits = there ? bits_s[tid] : 0u, outl = there ? b.outl_cnt[tc.chunk_base + tid] : 0u, units = (bits + 127u) >> 7;
+    const uint32_t iu = wave_inclusive_sum(units), io = wave_inclusive_sum(outl), ib = wave_inclusive_sum(bits);
+    uint32_t (*sums)[64] = wave_cnt;                                 // [0..2][wave]
+    if (lane == 63) { sums[0][wv] = iu; sums[1][wv] = io; sums[2][wv] = ib; }
+    __syncthreads();
+    uint32_t pu = 0, po = 0, tu = 0, to = 0;
+    uint64_t tb = 0;
+    for (int k = 0; k < kCbThreads / kWave; ++k) {
+        if (k < wv) { pu += sums[0][k]; po += sums[1][k]; }
+        tu += sums[0][k]; to += sums[1][k]; tb += sums[2][k];
+    }
+    if (there) {
+        b.chunk_bits[tc.chunk_base + tid] = bits;
+        if ((uint32_t)tid % b.pack_chunks == 0) {
+            b.range_units[tc.pack_base + (uint32_t)tid / b.pack_chunks] = pu + iu - units;
+            b.range_outl[tc.pack_base + (uint32_t)tid / b.pack_chunks] = po + io - outl;
+        }
+    }
+    finish_container(b, ti, tu, to, tb, reinterpret_cast<Header *>(skey), tid);
 }
 
 }  // namespace
 
+bool small_group(const BatchC &b)
+{
+    for (uint32_t k = 0; k < b.n; ++k)
+        if (b.t[k].nchunks > kSmallChunks) return false;
+    return true;
+}
+
 void launch_codebook(const BatchC &b, Profiler *prof, hipStream_t st)
 {
-    launch(prof, kKCodebook, k_codebook, dim3(b.n), dim3(kCbThreads), st, b);
+    if (small_group(b)) launch(prof, kKCodebook, k_codebook<true>, dim3(b.n), dim3(kCbThreads), st, b);
+    else launch(prof, kKCodebook, k_codebook<false>, dim3(b.n), dim3(kCbThreads), st, b);
 }
 
 }  // namespace cmpz

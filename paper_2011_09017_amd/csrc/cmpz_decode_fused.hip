@@ -146,15 +146,34 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     const DecompressArgs a = decompress_args(b, td);
     FusedPlan pl;
     pl.big = td.big; pl.G = td.G; pl.Rb = td.Rb; pl.nitems = td.nitems; pl.divW = td.divW;
-    // a container on the device-side stack: an empty slot, or one too short for the sections of fixed
-    // size, is not looked at (the host has checked this for containers it knows the size of)
-    if (td.slot && a.size < a.lay.off_payload) {
+    // A container on the device-side stack: its slot is read above; whichever workgroup comes last to this
+    // point gives the slot back.  Space comes back when the slots above it are free too.  (The container itself
+    // stays where it is until the next push, which follows this launch on its stream.)
+    auto release = [&]() {
+        if (!td.arena || tid != 0) return;
+        ArenaState *as = td.arena;
+        const uint32_t part = blockIdx.x % kReaderParts, grid = gridDim.x;
+        if (atomicAdd(&as->readers[part].n, 1u) != (grid - part - 1u) / kReaderParts) return;
+        as->readers[part].n = 0;
+        if (atomicAdd(&as->parts_read.n, 1u) != (grid < kReaderParts ? grid : kReaderParts) - 1u) return;
+        as->parts_read.n = 0;
+        if (td.arena_slot >= as->slots_cap) return;
+        as->slot[td.arena_slot].size = 0;
+        uint32_t n = as->nslots;
+        while (n > 0 && as->slot[n - 1].size == 0) { --n; as->top = as->slot[n].offset; }
+        as->nslots = n;
+    };
+    // an empty slot, or one too short for the sections of fixed size, is not looked at (the host has
+    // checked this for containers it knows the size of)
+    if (td.arena && a.size < a.lay.off_payload) {
         if (blockIdx.x == td.wg_base && tid == 0) atomicOr(a.status, kStFormat);
+        release();
         return;
     }
     // every workgroup validates the container and builds the decode tables for itself
     {
         const uint32_t defect = build_tables<kThreads>(T, a, reinterpret_cast<uint32_t *>(&lds.Rs[0][0]));
+        release();                                       // (behind the barriers of the build: all waves have the slot)
         if (defect) {
             if (blockIdx.x == td.wg_base && tid == 0) atomicOr(a.status, defect);
             return;

@@ -114,6 +114,11 @@ enum MetaWord : int {
 // a range of pack_chunks consecutive chunks of one tensor; those ranges are numbered
 // consecutively too (tensor t owns pack_base .. ).
 constexpr int      kBatchMax   = 24;        // tensors per launch group (kernel arguments hold their descriptors)
+// Most chunks of a tensor whose offsets and header the codebook kernel finds, rather than two kernels that spread
+// this over the chip.  In us, two kernels / the codebook kernel: one tensor of 49 chunks, there and back, 79.2 /
+// 76.7; a batch of up to 131 chunks 42.7 / 41.2; the saved activations of ResNet-18 at batch 16 with the tensors up to
+// 128 chunks this way 1104 / 1098, to 256 / 1101, to 512 / 1123; a tensor of 580 chunks at a tight bound 270 / 324.
+constexpr uint32_t kSmallChunks = 256;
 constexpr uint32_t kPackChunks = 28;        // chunks per workgroup of the bit-count and packing kernels: at most,
 constexpr uint32_t kPackChunksMin = 4;      // and at least (one per wave); always a multiple of that
 
@@ -121,12 +126,17 @@ constexpr uint32_t kPackChunksMin = 4;      // and at least (one per wave); alwa
 // next container goes is known to the GPU only (it depends on the sizes of the containers before
 // it), so the host can push tensor after tensor without ever waiting (cmp_arena_* in cmpz.h).
 struct ArenaSlot { uint64_t offset, size; };   // size 0: not held (never pushed, failed, or popped)
+constexpr uint32_t kReaderParts = 32;
 struct ArenaState {
     uint64_t top;          // bytes in use: where the next container starts
     uint64_t peak;         // largest `top` so far
     uint32_t nslots;       // slots pushed and not yet given back (slots are numbered in push order)
     uint32_t failed;       // pushes that did not fit
     uint32_t slots_cap, pad;
+    // Workgroups of the pop at hand that have read its slot, zero between calls: workgroup i counts in
+    // part i % kReaderParts, the last of each part in `parts_read`.  (A counter per memory line: the additions to
+    // one follow each other at 7 ns.)
+    struct Counter { uint32_t n, pad[15]; } readers[kReaderParts], parts_read;
     ArenaSlot slot[1];     // [slots_cap]
 };
 constexpr uint64_t kArenaAlign = 256;          // containers start at multiples of this
@@ -135,7 +145,8 @@ struct TensorC {
     const float *x;
     uint8_t     *out;
     uint64_t     out_cap;
-    const ArenaState *arena;    // not NULL: the container goes to out + arena->top (out_cap counts from out)
+    ArenaState  *arena;         // not NULL: the container goes to out + arena->top (out_cap counts from out),
+    uint32_t     arena_slot;    // and this is its slot
     uint32_t     shape[4];
     uint32_t     numel, nchunks, chunk_base, eb_bits;
     float        r;
@@ -155,6 +166,7 @@ struct TensorMeta {
     uint32_t long_from;         // smallest left-aligned 32 bits of a code longer than kEncBits (max_len says if any is)
     uint64_t total_bits;
     uint64_t total_size;        // container bytes
+    uint64_t out_off;           // where it starts in the tensor's `out`
 };
 
 // A value that is the same in all lanes, in a scalar register (a load from memory that the kernel may
@@ -165,7 +177,7 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
     return ((uint64_t)uniform_u32((uint32_t)(v >> 32)) << 32) | uniform_u32((uint32_t)v);
 }
 
-// Where the container of a tensor goes and how much room there is.
+// Where the container of a tensor goes and how much room there is (until finish_container has moved the top).
 struct OutRef { uint8_t *out; uint64_t cap; };
 __device__ __forceinline__ OutRef resolve_out(const TensorC &tc)
 {
@@ -226,8 +238,8 @@ struct DecompressArgs {
 struct TensorD {
     const uint8_t *buf;
     uint64_t       size;
-    const ArenaSlot *slot;                  // not NULL (fused kernel only): the container is at buf + slot->offset,
-                                            // slot->size bytes
+    ArenaState    *arena;                   // not NULL (fused kernel only): the container is at buf + slot offset,
+    uint32_t       arena_slot;              // slot size bytes, and the slot is released
     float         *xout;
     uint32_t       shape[4];
     uint32_t       numel, eb_bits;
@@ -251,7 +263,11 @@ __host__ __device__ inline DecompressArgs decompress_args(const BatchD &b, const
     DecompressArgs a;
     a.buf = t.buf; a.size = t.size; a.xout = t.xout;
 #if defined(__HIP_DEVICE_COMPILE__)
-    if (t.slot) { a.buf = t.buf + t.slot->offset; a.size = t.slot->size; }
+    if (t.arena) {
+        const bool there = t.arena_slot < t.arena->slots_cap;
+        a.buf = t.buf + (there ? t.arena->slot[t.arena_slot].offset : 0ull);
+        a.size = there ? t.arena->slot[t.arena_slot].size : 0ull;
+    }
 #endif
     a.numel = t.numel; a.planes = t.shape[0] * t.shape[1];
     a.H = t.shape[2]; a.W = t.shape[3]; a.HW = a.H * a.W;
@@ -381,12 +397,11 @@ inline void launch(Profiler *p, int id, K kernel, dim3 grid, dim3 block, hipStre
 void launch_sweep1(const BatchC &b, Profiler *prof, hipStream_t st);
 void launch_sweep1_untiled(const BatchC &b, uint32_t t, Profiler *prof, hipStream_t st);
 bool sweep1_tiled_fits(uint32_t W);
+bool small_group(const BatchC &b);            // all tensors are small: the codebook kernel does the offsets and headers too
 void launch_codebook(const BatchC &b, Profiler *prof, hipStream_t st);
 void launch_pack(const BatchC &b, Profiler *prof, hipStream_t st);
 void launch_clear(const BatchC &b, Profiler *prof, hipStream_t st);
 void launch_arena_init(ArenaState *st_dev, uint32_t slots, hipStream_t st);
-void launch_arena_pushed(const BatchC &b, ArenaState *st_dev, uint32_t slot, hipStream_t st);
-void launch_arena_release(ArenaState *st_dev, uint32_t slot, hipStream_t st);
 void launch_widen(uint16_t *sym, uint32_t *wide, uint32_t sym_off, uint32_t nchunks, hipStream_t st);
 size_t decode_tables_bytes();
 bool plan_decode_fused(TensorD *t, uint32_t sub, bool wide);

@@ -15,7 +15,7 @@
 // counts came from a pass over the symbols, the ResNet-18-shaped stream (591 M elements) took 138 us for
 // them and 240 for the packing, whose symbols that pass had brought nearer; now 35 and 262, and 10 more in
 // the first sweep.
-#include "cmpz_internal.h"
+#include "cmpz_offsets.h"
 
 #include <type_traits>
 
@@ -64,68 +64,31 @@ __global__ __launch_bounds__(kThreads) void k_lengths(BatchC b)
     const TensorC &tc = b.t[ti];
     const uint32_t c0 = (range - tc.pack_base) * b.pack_chunks;
     const uint32_t nq = (tc.nchunks - c0 < b.pack_chunks) ? tc.nchunks - c0 : b.pack_chunks;
-    const uint32_t byte_quad = b.sym_off / 4;        // the first four symbols with a byte form
     // A wave takes up to kMine consecutive chunks: the rows of these and of the one before, as far as their bytes
     // go, all loads in flight together
     constexpr uint32_t kMine = kPackChunks / kWaves;
     const uint32_t per = b.pack_chunks / kWaves, q0 = wv * per;
     const uint32_t g0 = tc.chunk_base + c0 + q0;     // (rows of chunks that do not exist are not looked at)
-    const uint2 *__restrict__ byte_rows = reinterpret_cast<const uint2 *>(b.chunk_hist);           // 64 per chunk
-    const uint2 *__restrict__ all_rows = reinterpret_cast<const uint2 *>(b.chunk_hist_all);        // kMaxSym / 4 per chunk
-    uint2 v[kMine + 1] = {};
-    uint4 wq[kMine] = {};
-    if (q0 < nq && c0 + q0) v[0] = byte_rows[(uint64_t)(g0 - 1) * 64 + lane];
-#pragma unroll
-    for (uint32_t j = 0; j < kMine; ++j) {
-        if (j < per && q0 + j < nq) {                // uniform
-            v[j + 1] = byte_rows[(uint64_t)(g0 + j) * 64 + lane];
-            wq[j] = *reinterpret_cast<const uint4 *>(b.wide + (uint64_t)(g0 + j) * 4);
-        }
-    }
     static_assert(kMaxSym / 4 == kThreads, "one word of the length table per thread");
     lens_s[tid] = reinterpret_cast<const uint32_t *>(b.lens + (uint64_t)ti * kMaxSym)[tid];
     __syncthreads();
-    // Elements that are no other symbol are zero residuals: their code counts for every element, and the
-    // other symbols for what their codes are longer.  In container version 2 they are counted.
-    const int32_t zero_len = b.zero_blocks ? 0 : (int32_t)reinterpret_cast<const uint8_t *>(lens_s)[b.radius];
-    auto quad_bits = [&](uint2 n, uint32_t quad) -> int32_t {
-        const uint32_t L = lens_s[quad];
-        return (int32_t)(n.x & 0xffffu) * ((int32_t)(L & 0xffu) - zero_len) + (int32_t)(n.x >> 16) * ((int32_t)((L >> 8) & 0xffu) - zero_len) +
-               (int32_t)(n.y & 0xffffu) * ((int32_t)((L >> 16) & 0xffu) - zero_len) + (int32_t)(n.y >> 16) * ((int32_t)(L >> 24) - zero_len);
-    };
-    // The symbols without a byte form, of the counts after chunk g: looked at where g is not all bytes, and where
-    // the next one is not (the lane's share).
-    auto others = [&](uint32_t g) -> int32_t {
-        const uint2 *row = all_rows + (uint64_t)g * (kMaxSym / 4);
-        int32_t bits = 0;
+    ChunkBits cb(b, lens_s, lane);
+    uint2 v[kMine + 1] = {};
+    uint32_t wq[kMine] = {};
+    if (q0 < nq && c0 + q0) v[0] = cb.row(g0 - 1);
 #pragma unroll
-        for (uint32_t i = 0; i < kMaxSym / 4 / kWave; ++i) {
-            const uint32_t quad = i * kWave + lane;
-            if (quad - byte_quad >= (uint32_t)kWave) bits += quad_bits(row[quad], quad);
+    for (uint32_t j = 0; j < kMine; ++j) {
+        if (j < per && q0 + j < nq) {                // uniform
+            v[j + 1] = cb.row(g0 + j);
+            wq[j] = cb.is_wide(g0 + j);
         }
-        return bits;
-    };
-    int32_t others_before = 0;
-    bool have_before = false;                        // uniform
+    }
 #pragma unroll
     for (uint32_t j = 0; j < kMine; ++j) {
         const uint32_t q = q0 + j;
         if (j >= per || q >= nq) break;              // uniform
-        const uint32_t c = c0 + q, g = g0 + j;
-        const bool first = c % tc.run == 0;          // of its run: nothing to subtract
-        int32_t bits = quad_bits(v[j + 1], byte_quad + lane);
-        if (!first) bits -= quad_bits(v[j], byte_quad + lane);
-        const bool wide = uniform_u32(wq[j].x | wq[j].y | wq[j].z | wq[j].w) != 0;
-        if (wide) {
-            const int32_t now = others(g);
-            bits += now;
-            if (!first) bits -= have_before ? others_before : uniform_u32(b.has_all[g - 1]) ? others(g - 1) : 0;
-            others_before = now;
-        }
-        have_before = wide;
-        const uint32_t n = (tc.numel - c * kChunk < kChunk) ? tc.numel - c * kChunk : kChunk;
-        const uint32_t tot = wave_inclusive_sum((uint32_t)bits) + n * (uint32_t)zero_len;
-        if (lane == 63) { bits_s[q] = tot; b.chunk_bits[g] = tot; }
+        const uint32_t tot = cb.chunk(tc, c0 + q, v[j], v[j + 1], uniform_u32(wq[j]) != 0, [&] { return cb.others(g0 + j); });
+        if (lane == 63) { bits_s[q] = tot; b.chunk_bits[g0 + j] = tot; }
     }
     __syncthreads();
     if (wv == 0) {
@@ -150,6 +113,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(BatchC b)
 {
     __shared__ uint32_t wave_u[kScanThreads / kWave], wave_o[kScanThreads / kWave];
     __shared__ unsigned long long bits_s;
+    __shared__ Header hd_s;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const uint32_t ti = blockIdx.x;
     const TensorC &tc = b.t[ti];
@@ -187,64 +151,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(BatchC b)
         if (lane == 63) atomicAdd(&bits_s, (unsigned long long)lo + ((unsigned long long)mid << 24) + ((unsigned long long)hi << 48));
     }
     __syncthreads();
-    if (tid != 0) return;
-
-    const Layout lay = make_layout(tc.numel, b.radius, b.sub);
-    TensorMeta &tm = b.tmeta[ti];
-    const uint64_t total_units = base_u, n_out = base_o;
-    const uint64_t off_outl_idx = lay.off_payload + total_units * 16;
-    const uint64_t sect = (4 * n_out + 15) & ~15ull;
-    const uint64_t off_outl_val = off_outl_idx + sect;
-    const uint64_t total = off_outl_val + sect;
-    const OutRef oref = resolve_out(tc);
-    const bool fixed_fit = oref.cap >= lay.off_payload;
-    const bool fits = total <= oref.cap;
-    const uint32_t range_events = tm.range_events;
-
-    // end markers and zero padding of the two offset tables (the fixed sections always fit)
-    uint32_t *chunk_off = reinterpret_cast<uint32_t *>(oref.out + lay.off_chunk_off);
-    uint32_t *outl_off = reinterpret_cast<uint32_t *>(oref.out + lay.off_outl_off);
-    const uint32_t padded = (tc.nchunks + 1 + 3) & ~3u;
-    if (fixed_fit) {
-        chunk_off[tc.nchunks] = (uint32_t)total_units;
-        outl_off[tc.nchunks] = (uint32_t)n_out;
-        for (uint32_t k = tc.nchunks + 1; k < padded; ++k) { chunk_off[k] = 0; outl_off[k] = 0; }
-    }
-    if (fits) {
-        // zero padding of both outlier sections
-        uint32_t *oidx = reinterpret_cast<uint32_t *>(oref.out + off_outl_idx);
-        uint32_t *oval = reinterpret_cast<uint32_t *>(oref.out + off_outl_val);
-        for (uint64_t k = n_out; k < ((n_out + 3) & ~3ull); ++k) { oidx[k] = 0; oval[k] = 0; }
-    }
-
-    Header hd;
-    uint32_t *raw = reinterpret_cast<uint32_t *>(&hd);
-    for (uint32_t k = 0; k < kHeaderBytes / 4; ++k) raw[k] = 0;
-    hd.magic = kMagic; hd.version = b.zero_blocks ? kVersionZB : kVersion; hd.status = fits ? 0u : kStNoSpace;
-    hd.eb_bits = tc.eb_bits;
-    for (int k = 0; k < 4; ++k) hd.shape[k] = tc.shape[k];
-    hd.numel = tc.numel;
-    hd.radius = b.radius; hd.chunk = kChunk; hd.sub = b.sub; hd.guard_shift = b.guard_shift;
-    hd.nchunks = tc.nchunks; hd.n_outliers = (uint32_t)n_out;
-    hd.range_events = range_events; hd.max_len = tc.numel ? tm.max_len : 0u;
-    hd.total_bits = bits_s;
-    hd.off_lens = lay.off_lens; hd.off_chunk_off = lay.off_chunk_off;
-    hd.off_outl_off = lay.off_outl_off; hd.off_sub_bits = lay.off_sub_bits;
-    hd.off_payload = lay.off_payload; hd.off_outl_idx = off_outl_idx;
-    hd.off_outl_val = off_outl_val; hd.total_size = total;
-    uint32_t *dst = reinterpret_cast<uint32_t *>(oref.out);
-    if (fixed_fit) for (uint32_t k = 0; k < kHeaderBytes / 4; ++k) dst[k] = raw[k];
-
-    uint32_t st = 0;
-    if (!fits) st |= kStNoSpace;
-    if (range_events) st |= kStRange;
-    if (st) atomicOr(b.status, st);
-    tm.skip = fits ? 0u : 1u;
-    tm.n_outliers = (uint32_t)n_out;
-    tm.total_units = (uint32_t)total_units;
-    tm.total_bits = bits_s;
-    tm.total_size = total;
-    tm.range_events = 0;                             // ready for the next call
+    finish_container(b, ti, base_u, base_o, bits_s, &hd_s, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -288,7 +195,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_pack(BatchC b)
     const uint32_t long_from = uniform_u32(tm.long_from);            // those from here on
     const uint32_t n_outliers = uniform_u32(tm.n_outliers);
     const Layout lay = make_layout(numel, b.radius, b.sub);
-    uint8_t *const out = resolve_out(tc).out;
+    uint8_t *const out = tc.out + uniform_u64(tm.out_off);
 
     const uint16_t *__restrict__ sym = b.sym + (uint64_t)tc.chunk_base * kChunk;
     // per quarter of the wave's chunks (wv, wv + 4, ...), four bits each: 16-bit symbols, else bytes
@@ -582,34 +489,9 @@ __global__ __launch_bounds__(64) void k_widen(uint16_t *sym, uint32_t *wide, uin
 // ---- the stack of containers (one thread each: a few words of bookkeeping) ----
 __global__ void k_arena_init(ArenaState *st, uint32_t slots)
 {
-    st->top = 0; st->peak = 0; st->nslots = 0; st->failed = 0; st->slots_cap = slots; st->pad = 0;
+    st->top = 0; st->peak = 0; st->nslots = 0; st->failed = 0; st->slots_cap = slots; st->pad = 0; st->parts_read.n = 0;
+    for (uint32_t k = 0; k < kReaderParts; ++k) st->readers[k].n = 0;
     for (uint32_t k = 0; k < slots; ++k) { st->slot[k].offset = 0; st->slot[k].size = 0; }
-}
-
-// After the kernels of a push: the container is complete, record it and move the top past it.
-__global__ void k_arena_pushed(BatchC b, ArenaState *st, uint32_t slot)
-{
-    const TensorMeta &tm = b.tmeta[0];
-    if (slot >= st->slots_cap) { st->failed += 1; return; }
-    if (tm.skip) {                                   // it did not fit: the slot stays empty
-        st->slot[slot].offset = st->top; st->slot[slot].size = 0;
-        st->failed += 1;
-    } else {
-        st->slot[slot].offset = st->top; st->slot[slot].size = tm.total_size;
-        st->top += (tm.total_size + kArenaAlign - 1) / kArenaAlign * kArenaAlign;
-        if (st->top > st->peak) st->peak = st->top;
-    }
-    if (slot + 1 > st->nslots) st->nslots = slot + 1;
-}
-
-// A container is no longer needed.  Space comes back when the slots above it are free too.
-__global__ void k_arena_release(ArenaState *st, uint32_t slot)
-{
-    if (slot >= st->slots_cap) return;
-    st->slot[slot].size = 0;
-    uint32_t n = st->nslots;
-    while (n > 0 && st->slot[n - 1].size == 0) { --n; st->top = st->slot[n].offset; }
-    st->nslots = n;
 }
 
 }  // namespace
@@ -618,15 +500,6 @@ void launch_arena_init(ArenaState *st_dev, uint32_t slots, hipStream_t st)
 {
     hipLaunchKernelGGL(k_arena_init, dim3(1), dim3(1), 0, st, st_dev, slots);
 }
-void launch_arena_pushed(const BatchC &b, ArenaState *st_dev, uint32_t slot, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_arena_pushed, dim3(1), dim3(1), 0, st, b, st_dev, slot);
-}
-void launch_arena_release(ArenaState *st_dev, uint32_t slot, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_arena_release, dim3(1), dim3(1), 0, st, st_dev, slot);
-}
-
 void launch_widen(uint16_t *sym, uint32_t *wide, uint32_t sym_off, uint32_t nchunks, hipStream_t st)
 {
     if (nchunks) hipLaunchKernelGGL(k_widen, dim3(4 * nchunks), dim3(64), 0, st, sym, wide, sym_off);
@@ -640,8 +513,10 @@ void launch_clear(const BatchC &b, Profiler *prof, hipStream_t st)
 // Bit counts, offsets and header, packing: three launches over all tensors of the group.
 void launch_pack(const BatchC &b, Profiler *prof, hipStream_t st)
 {
-    if (b.pack_wgs) launch(prof, kKLengths, k_lengths, dim3(b.pack_wgs), dim3(kThreads), st, b);
-    launch(prof, kKScan, k_scan, dim3(b.n), dim3(kScanThreads), st, b);
+    if (!small_group(b)) {
+        if (b.pack_wgs) launch(prof, kKLengths, k_lengths, dim3(b.pack_wgs), dim3(kThreads), st, b);
+        launch(prof, kKScan, k_scan, dim3(b.n), dim3(kScanThreads), st, b);
+    }
     if (b.pack_wgs) {
         auto pack = [&](auto group) {
             constexpr int kGroup = decltype(group)::value;

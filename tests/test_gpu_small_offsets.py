@@ -1,0 +1,92 @@
+"""GPU parity where the kernel that builds the code also finds a tensor's offsets and header (tensors of at
+most 256 chunks), and the device-side stack's bookkeeping by the kernels that write and read the containers.
+
+Bar: the container equals the CPU oracle's byte for byte.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+EB = 1e-2
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2011_09017_amd import binding
+    binding.lib()
+    return binding
+
+
+def tensor(shape, seed):
+    """a smooth field with rare outliers, and a part with symbols of every size"""
+    rng = np.random.default_rng(seed)
+    x = (0.02 * rng.standard_normal(shape)).astype(np.float32)
+    flat = x.reshape(-1)
+    n = flat.size
+    flat[n // 2:n // 2 + n // 8] *= 100.0
+    flat[rng.integers(0, n, 1 + n // 5000)] = 60.0
+    return x
+
+
+def oracle(orc, x, sub, zero_blocks):
+    rc, buf, size, _ = orc.compress(x, EB, orc.Config(sub=sub, zero_blocks=zero_blocks))
+    assert rc == 0
+    return buf, size
+
+
+# one element; both sides of a chunk, of a wave's four chunks, of the limit
+@pytest.mark.parametrize("sub,zero_blocks", [(32, 0), (128, 1)])
+@pytest.mark.parametrize("n", [1, 4096, 4097, 16 * 4096, 16 * 4096 + 1, 65 * 4096 + 5, 256 * 4096 - 1, 256 * 4096, 256 * 4096 + 1])
+def test_sizes(gpu, orc, n, sub, zero_blocks):
+    x = tensor((1, 1, 1, n) if n < 200 else (1, n, 1, 1) if n % 16 else (n // 16, 1, 4, 4), n)
+    ctx = gpu.Context(sub=sub, max_numel=n, zero_blocks=zero_blocks)
+    buf, size, rc = ctx.compress(torch.from_numpy(x).cuda(), EB)
+    assert rc == 0
+    want, want_size = oracle(orc, x, sub, zero_blocks)
+    assert size == want_size and np.array_equal(buf[:size].cpu().numpy(), want)
+
+
+# all small, and one too large among them
+@pytest.mark.parametrize("large", [False, True])
+def test_batches(gpu, orc, large):
+    shapes = [(2, 3, 20, 20), (1, 70, 61, 61), (1, 1, 1, 1), (3, 128, 28, 29)] + ([(5, 70, 61, 61)] if large else [])
+    xs = [tensor(s, k) for k, s in enumerate(shapes)]
+    ctx = gpu.Context(sub=32, max_numel=sum(-(-x.size // 4096) * 4096 for x in xs))
+    bufs, sizes, rc = ctx.compress_batch([torch.from_numpy(x).cuda() for x in xs], [EB] * len(xs))
+    assert rc == 0
+    for x, buf, size in zip(xs, bufs, sizes):
+        want, want_size = oracle(orc, x, 32, False)
+        assert size == want_size and np.array_equal(buf[:size].cpu().numpy(), want)
+
+
+# pops by launches of fewer and of more workgroups than the stack counts in parts, in and out of order
+def test_stack(gpu):
+    shapes = [(1, 3, 9, 9), (4, 64, 28, 28), (8, 100, 56, 57), (1, 1, 1, 3), (64, 33, 14, 14)]
+    xs = [torch.from_numpy(tensor(s, k)).cuda() for k, s in enumerate(shapes)]
+    ctx = gpu.Context(sub=32, max_numel=max(x.numel() for x in xs))
+    cap = 1 << 24
+    arena = torch.empty(cap, dtype=torch.uint8, device="cuda")
+    state = torch.empty(gpu.cmp_arena_state_bytes(len(xs)), dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    alone = []
+    for x in xs:
+        buf, size, _ = ctx.compress(x, EB)
+        alone.append((ctx.decompress(buf, size, x.shape, EB), size))
+    assert gpu.cmp_arena_init(ctx._h, state.data_ptr(), len(xs), stream) == 0
+    for order in ([4, 3, 2, 1, 0], [0, 1, 2, 3, 4], [2, 4, 0, 3, 1]):
+        for k, x in enumerate(xs):
+            assert gpu.cmp_arena_push(ctx._h, arena.data_ptr(), cap, state.data_ptr(), k, x.data_ptr(), x.shape, EB, stream) == 0
+        held = set(range(len(xs)))
+        ends = np.cumsum([-(-size // 256) * 256 for _, size in alone])
+        for k in order:
+            y = torch.empty_like(xs[k])
+            assert gpu.cmp_arena_pop(ctx._h, arena.data_ptr(), state.data_ptr(), k, xs[k].shape, EB, y.data_ptr(), stream) == 0
+            held.discard(k)
+            rc, top, peak, n, failed = gpu.cmp_arena_stats(ctx._h, state.data_ptr(), stream)
+            assert rc == 0 and failed == 0 and n == (max(held) + 1 if held else 0)
+            assert top == (ends[max(held)] if held else 0) and peak == ends[-1]
+            assert torch.equal(y.view(torch.int32), alone[k][0].view(torch.int32))
+    assert ctx.last_status() == 0
