@@ -7,8 +7,8 @@
 // Codes are canonical: ordered by (length, symbol), first code 0, read MSB first.
 //
 // The merge runs in rounds that join up to 32 pairs at once (see step 4).  Sorting is by
-// counting ranks in blocks of 64 and binary search across blocks, depths by walking parent
-// links, ranks within a length by wave ballots.
+// counting ranks in blocks of 64 and binary search across blocks, depths by pointer jumping,
+// ranks within a length by wave ballots.
 #include "cmpz_offsets.h"
 
 namespace cmpz {
@@ -71,6 +71,28 @@ __device__ __forceinline__ uint64_t bitonic_merge_64(uint64_t k, int lane)
     return exchange_dpp<0xB1>(k, (lane & 1) != 0);           // quad_perm 1,0,3,2
 }
 
+// The same for keys of 32 bits: one instruction each for the smaller and the larger key of a pair.
+template <int CTRL>
+__device__ __forceinline__ uint32_t exchange_dpp(uint32_t k, bool upper)
+{
+    const uint32_t p = dpp_u32<CTRL, 0xf>(k), least = p < k ? p : k, most = p < k ? k : p;
+    return upper ? most : least;
+}
+__device__ __forceinline__ uint32_t bitonic_merge_64(uint32_t k, int lane)
+{
+    const auto h = __builtin_amdgcn_permlane32_swap(k, k, false, false);
+    k = (lane & 32) ? (h[0] > h[1] ? h[0] : h[1]) : (h[0] < h[1] ? h[0] : h[1]);
+    const auto r = __builtin_amdgcn_permlane16_swap(k, k, false, false);
+    k = (lane & 16) ? (r[0] > r[1] ? r[0] : r[1]) : (r[0] < r[1] ? r[0] : r[1]);
+    k = exchange_dpp<0x128>(k, (lane & 8) != 0);             // row_ror:8
+    {
+        const uint32_t p = lane_xor4(k), least = p < k ? p : k, most = p < k ? k : p;
+        k = (lane & 4) ? most : least;
+    }
+    k = exchange_dpp<0x4E>(k, (lane & 2) != 0);              // quad_perm 2,3,0,1
+    return exchange_dpp<0xB1>(k, (lane & 1) != 0);           // quad_perm 1,0,3,2
+}
+
 // SMALL: the tensors' offsets and headers too (see small_group).
 template <bool SMALL>
 __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
@@ -80,12 +102,12 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     uint32_t *__restrict__ g_hist = b.hist + (uint64_t)ti * kHistCopies * kMaxSym;
     const OutRef oref = resolve_out(b.t[ti]);
     uint8_t *__restrict__ out = oref.out;
-    __shared__ uint64_t key[kMaxSym];            // used symbols, compacted: count << 10 | symbol
+    alignas(16) __shared__ uint64_t key[kMaxSym];    // used symbols, compacted: count << 10 | symbol; then all ones
     __shared__ uint64_t skey[kMaxSym];           // the same, every block of 64 in ascending order
     __shared__ uint32_t leaf_w[kMaxSym + 192];   // leaf weights, ascending, padded with kInf
     __shared__ uint16_t leaf_sym[kMaxSym];
     __shared__ uint32_t node_w[kMaxSym + 192];   // internal node weights in creation order, kInf = not made
-    __shared__ uint16_t parent[2 * kMaxSym];     // node ids: leaves 0..n-1, internal n..2n-2
+    __shared__ uint32_t link[2 * kMaxSym];       // of leaves 0..n-1, internal nodes n..2n-2: a node above, and how far << 16
     __shared__ uint32_t len_of[kMaxSym];         // code length per symbol
     __shared__ uint32_t wave_cnt[16][64];
     __shared__ uint64_t first_code[64];
@@ -95,12 +117,12 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     const uint32_t nsym = 2 * b.radius;
 
     // 1. fetch the histogram, leave it zeroed for the next call, keep a copy for inspection
-    uint32_t cnt = 0;
+    uint32_t part[kHistCopies], cnt = 0;
 #pragma unroll
-    for (uint32_t k = 0; k < kHistCopies; ++k) {
-        if ((uint32_t)tid < nsym) cnt += g_hist[k * kMaxSym + tid];
-        g_hist[k * kMaxSym + tid] = 0;
-    }
+    for (uint32_t k = 0; k < kHistCopies; ++k) part[k] = g_hist[k * kMaxSym + tid];
+#pragma unroll
+    for (uint32_t k = 0; k < kHistCopies; ++k) { cnt += part[k]; g_hist[k * kMaxSym + tid] = 0; }
+    if ((uint32_t)tid >= nsym) cnt = 0;
     b.hist_copy[ti * kMaxSym + tid] = cnt;
     len_of[tid] = 0;
 
@@ -112,35 +134,44 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     for (int k = 0; k < 16; ++k) { if (k < wv) my_slot += wave_used[k]; n += wave_used[k]; }
     my_slot += (uint32_t)__popcll(used_mask & ((1ull << lane) - 1ull));
     if (cnt) key[my_slot] = ((uint64_t)cnt << 10) | (uint64_t)tid;
+    if ((uint32_t)tid >= n) key[tid] = ~0ull;                        // heavier than any key
     __syncthreads();
 
     // 3. sort (keys are distinct).  Every wave orders its own 64 keys by counting the smaller ones
-    //    among them; the rank of a key is then its place in its own block plus, by binary search,
-    //    the number of smaller keys in every other block.
+    //    among them; the rank of a key is then, by binary search, the number of smaller keys in every block.  Four
+    //    searches at a time: they are chains of seven LDS accesses.
     const uint32_t nblocks = (n + 63u) >> 6;                         // uniform
-    const uint64_t mine = ((uint32_t)tid < n) ? key[tid] : ~0ull;    // past the end: heavier than any key
-    uint32_t in_block = (uint32_t)lane;
+    const uint64_t mine = key[tid];
     if ((uint32_t)wv < nblocks) {
-        if ((uint32_t)tid < n) {
-            const uint32_t first = (uint32_t)wv << 6;
-            const uint32_t here = (n - first < 64u) ? n - first : 64u;
-            in_block = 0;
-#pragma unroll 8
-            for (uint32_t j = 0; j < here; ++j) in_block += (key[first + j] < mine) ? 1u : 0u;
+        const ulonglong2 *block = reinterpret_cast<const ulonglong2 *>(key + ((uint32_t)wv << 6));
+        uint32_t in_block = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < 32; ++j) {
+            const ulonglong2 two = block[j];
+            in_block += (two.x < mine) ? 1u : 0u;
+            in_block += (two.y < mine) ? 1u : 0u;
         }
+        if ((uint32_t)tid >= n) in_block = (uint32_t)lane;
         skey[((uint32_t)wv << 6) + in_block] = mine;
     }
     __syncthreads();
     if ((uint32_t)tid < n) {
-        uint32_t rank = in_block;
-        for (uint32_t w = 0; w < nblocks; ++w) {
-            if (w == (uint32_t)wv) continue;                         // uniform
-            const uint64_t *blk = skey + (w << 6);
-            uint32_t pos = 0;
+        uint32_t rank = 0;
+        for (uint32_t w = 0; w < nblocks; w += 4) {
+            const uint64_t *blk[4];
+            uint32_t pos[4] = {};
 #pragma unroll
-            for (uint32_t step = 32; step >= 1; step >>= 1) pos += (blk[pos + step - 1] < mine) ? step : 0u;
-            pos += (blk[pos] < mine) ? 1u : 0u;                      // a count of 63 may be 64
-            rank += pos;
+            for (uint32_t j = 0; j < 4; ++j) blk[j] = skey + ((w + j < nblocks ? w + j : w) << 6);
+#pragma unroll
+            for (uint32_t step = 32; step >= 1; step >>= 1) {
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) pos[j] += (blk[j][pos[j] + step - 1] < mine) ? step : 0u;
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                pos[j] += (blk[j][pos[j]] < mine) ? 1u : 0u;         // a count of 63 may be 64
+                if (w + j < nblocks) rank += pos[j];
+            }
         }
         leaf_w[rank] = (uint32_t)(mine >> 10);
         leaf_sym[rank] = (uint16_t)(mine & 1023u);
@@ -148,6 +179,7 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     if ((uint32_t)tid < 192) leaf_w[n + tid] = kInf;
     node_w[tid] = kInf;
     if (tid < 192) node_w[kMaxSym + tid] = kInf;
+    if (tid == 0 && n) link[2 * n - 2] = 2 * n - 2;                  // the root
     __syncthreads();
 
     // 4. the two-queue merge, by wave 0, in rounds of up to 32 nodes.  The sequential rule takes the
@@ -165,51 +197,81 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     //    by binary search in LDS (four dependent accesses), LDS counters for the lengths and a serial
     //    loop over the first codes the kernel went from 22.6 to 14.8 us on one 64x56x56 activation,
     //    32.6 to 22.4 us on 64x256x56x56 (eb 5e-3) and 39.4 to 26.0 us with all 1024 symbols in use.
+    //    Keys of 32 bits instead of 64 in all rounds but the last ones of large tensors, the histogram's loads and
+    //    the searches of the sort in flight together, pointer jumping for the depths and ballots over the bits of
+    //    the lengths: 13.6 to 10.6 us, 20.4 to 15.2 us and 25.6 to 19.7 us, between the first and the last of its
+    //    own instructions (370 to 270 ns per round).
     if (__builtin_amdgcn_readfirstlane(wv) == 0 && __builtin_amdgcn_readfirstlane((int)n) >= 2) {
         const uint32_t nu = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);   // n came from LDS: tell the compiler it is uniform
         const uint32_t steps = nu - 1;
         uint32_t ql = 0, qi = 0, m = 0;                      // leaves used, internal nodes used, internal nodes made
-        while (m < steps) {
-            const uint32_t lw = leaf_w[ql + lane];           // kInf past the last leaf
-            const uint32_t iw = node_w[qi + 63 - lane];      // kInf at and past node m
-            // place in the window, leaves before nodes: the order among equal weights
-            const uint64_t kl = ((uint64_t)lw << 32) | (uint32_t)lane, ki = ((uint64_t)iw << 32) | (uint32_t)(127 - lane);
-            const uint64_t k = bitonic_merge_64(ki < kl ? ki : kl, lane);
-            const uint32_t w = (uint32_t)(k >> 32), id = (uint32_t)k;
-            const uint64_t t = (uint64_t)rdlane(w, 0) + rdlane(w, 1);
-            const uint32_t t32 = (t < (uint64_t)kInf) ? (uint32_t)t : kInf - 1u;
-            uint32_t npairs = (uint32_t)__popcll(__ballot(w <= t32)) >> 1;       // (a prefix of the lanes)
+        // one round: the 64 lightest nodes in order, each lane's weight and place (leaves from 0, nodes from 64 on)
+        auto join = [&](uint32_t w, uint32_t id, uint32_t t) {
+            uint32_t npairs = (uint32_t)__popcll(__ballot(w <= t)) >> 1;         // (a prefix of the lanes)
             npairs = npairs < steps - m ? npairs : steps - m;
             // the two lightest nodes always weigh <= t, so a round joins at least one pair; a histogram
             // whose counts do not add up below 2^32 (damaged scratch memory) could break that: leave
             // rather than spin
             if (npairs == 0) {
                 if (lane == 0) atomicOr(b.status, kStInternal);
-                break;
+                m = steps;
+                return;
             }
             const bool used = (uint32_t)lane < 2u * npairs, leaf = id < 64u;
             const uint32_t sum = w + dpp_u32<0xB1, 0xf>(w);                      // with the pair's other node
-            if (used) parent[leaf ? ql + id : nu + qi + (id - 64u)] = (uint16_t)(nu + m + ((uint32_t)lane >> 1));
+            if (used) link[leaf ? ql + id : nu + qi + (id - 64u)] = (nu + m + ((uint32_t)lane >> 1)) | (1u << 16);
             if (used && !(lane & 1)) node_w[m + ((uint32_t)lane >> 1)] = sum;
             wave_lds_sync();
             const uint32_t nl = (uint32_t)__popcll(__ballot(used && leaf));
             ql += nl;
             qi += 2u * npairs - nl;
             m += npairs;
+        };
+        // while t is below 2^25 - 1, weight and place fit 32 bits: heavier nodes have no part in the round
+        constexpr uint32_t kMost = (1u << 25) - 1u;
+        while (m < steps) {
+            const uint32_t lw = leaf_w[ql + lane], iw = node_w[qi + 63 - lane];  // kInf past the last leaf; at and past node m
+            const uint32_t kl = ((lw < kMost ? lw : kMost) << 7) | (uint32_t)lane;
+            const uint32_t ki = ((iw < kMost ? iw : kMost) << 7) | (uint32_t)(127 - lane);
+            const uint32_t k = bitonic_merge_64(ki < kl ? ki : kl, lane);
+            const uint32_t t = (rdlane(k, 0) >> 7) + (rdlane(k, 1) >> 7);
+            if (t >= kMost) break;
+            join(k >> 7, k & 127u, t);
+        }
+        while (m < steps) {
+            const uint32_t lw = leaf_w[ql + lane], iw = node_w[qi + 63 - lane];
+            // place in the window, leaves before nodes: the order among equal weights
+            const uint64_t kl = ((uint64_t)lw << 32) | (uint32_t)lane, ki = ((uint64_t)iw << 32) | (uint32_t)(127 - lane);
+            const uint64_t k = bitonic_merge_64(ki < kl ? ki : kl, lane);
+            const uint32_t w = (uint32_t)(k >> 32);
+            const uint64_t t = (uint64_t)rdlane(w, 0) + rdlane(w, 1);
+            join(w, (uint32_t)k, (t < (uint64_t)kInf) ? (uint32_t)t : kInf - 1u);
         }
     }
     __syncthreads();
 
-    // 5. depth of every leaf = its code length
-    if ((uint32_t)tid < n) {
-        uint32_t depth = 0;
-        if (n == 1) depth = 1;
-        else {
-            const uint32_t root = 2 * n - 2;
-            // (bounded: a walk over a complete tree ends at the root after at most kMaxCodeLen steps)
-            for (uint32_t v = tid; v != root && depth < 64u; v = parent[v] & (2 * kMaxSym - 1)) ++depth;
+    // 5. depth of every leaf = its code length: every node's link is replaced by the link of the node it leads to
+    //    until it leads to the root, at twice the distance each time.  The words are read and written
+    //    whole, so a link is right whether the other has been replaced already or not: no barriers.
+    {
+        const uint32_t root = 2 * n - 2;
+        volatile uint32_t *const links = link;
+        const uint32_t leaf = tid, node = n + tid;
+        const bool is_leaf = n > 1 && leaf < n, is_node = node < root && n > 1;
+        uint32_t a = is_leaf ? links[leaf] : root, c = is_node ? links[node] : root;
+        // (bounded: a step goes at least one node up, and a complete tree has at most kMaxCodeLen levels)
+        for (uint32_t k = 0; k < 64u; ++k) {
+            const bool more_a = (a & 0xffffu) != root, more_c = (c & 0xffffu) != root;
+            if (!__any(more_a || more_c)) break;
+            if (more_a || more_c) {
+                const uint32_t qa = links[a & (2 * kMaxSym - 1)], qc = links[c & (2 * kMaxSym - 1)];
+                a = (qa & 0xffffu) | ((a & 0xffff0000u) + (qa & 0xffff0000u));
+                c = (qc & 0xffffu) | ((c & 0xffff0000u) + (qc & 0xffff0000u));
+                if (is_leaf) links[leaf] = a;
+                if (is_node) links[node] = c;
+            }
         }
-        len_of[leaf_sym[tid]] = depth;
+        if (leaf < n) len_of[leaf_sym[leaf]] = n == 1 ? 1u : a >> 16;
     }
     __syncthreads();
 
@@ -217,17 +279,17 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     //    length, turns the waves' counts into offsets and finds the first code of its length: with
     //    P = the sum of count[j] << (48 - j) over all shorter lengths j it is P >> (48 - length).
     const uint32_t L = len_of[tid] & 63u;
-    uint32_t in_wave = 0;
     wave_cnt[wv][lane] = 0;
     wave_lds_sync();
-    unsigned long long remaining = __ballot(L != 0);
-    while (remaining) {                                   // wave-uniform
-        const uint32_t Lx = rdlane(L, (uint32_t)__ffsll((long long)remaining) - 1u);
-        const unsigned long long same = __ballot(L == Lx);
-        if (L == Lx) in_wave = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
-        if (lane == 0) wave_cnt[wv][Lx] = (uint32_t)__popcll(same);
-        remaining &= ~same;
+    unsigned long long same = ~0ull;                      // the lanes with this length
+#pragma unroll
+    for (uint32_t k = 0; k < 6; ++k) {
+        const bool set = (L >> k) & 1u;
+        const unsigned long long those = __ballot(set);
+        same &= set ? those : ~those;
     }
+    const uint32_t in_wave = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+    if (L && in_wave == 0) wave_cnt[wv][L] = (uint32_t)__popcll(same);
     __syncthreads();
     if (wv == 0) {
         uint32_t total = 0;

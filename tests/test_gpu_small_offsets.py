@@ -90,3 +90,31 @@ def test_stack(gpu):
             assert top == (ends[max(held)] if held else 0) and peak == ends[-1]
             assert torch.equal(y.view(torch.int32), alone[k][0].view(torch.int32))
     assert ctx.last_status() == 0
+
+
+# the codebook: every count of used symbols around its blocks of 64 and of 256, and weights on both sides of what
+# fits a key of 32 bits (2^25), with the same weights many times over
+@pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 65, 128, 256, 257, 321, 1000])
+def test_used_symbols(gpu, orc, n):
+    rng = np.random.default_rng(n)
+    step = np.float32(2) * (np.float32(EB) - np.float32(np.ldexp(np.float32(EB), -7)))
+    counts = rng.choice([1, 2, 3, 5, 8, 13, 40], n)
+    q = np.repeat(rng.permutation(np.arange(-(n // 2), n - n // 2)), counts)
+    x = (rng.permutation(q) * step).astype(np.float32).reshape(1, -1, 1, 1)
+    ctx = gpu.Context(sub=32, max_numel=x.size)
+    buf, size, rc = ctx.compress(torch.from_numpy(x).cuda(), EB)
+    want, want_size = oracle(orc, x, 32, False)
+    assert rc == 0 and size == want_size and np.array_equal(buf[:size].cpu().numpy(), want)
+
+
+def test_heavy_symbols(gpu, orc):
+    step = float(np.float32(2) * (np.float32(EB) - np.float32(np.ldexp(np.float32(EB), -7))))
+    x = np.zeros(9 << 22, np.float32)                                # 37.7 M elements, 2^24 and 2^22 of which another value
+    x[:1 << 24] = step
+    x[1 << 24:(1 << 24) + (1 << 22)] = -step
+    x[-3000:] = step * np.random.default_rng(1).integers(-200, 200, 3000)
+    x = x.reshape(1, -1, 1, 1)
+    ctx = gpu.Context(sub=32, max_numel=x.size)
+    buf, size, rc = ctx.compress(torch.from_numpy(x).cuda(), EB)
+    want, want_size = oracle(orc, x, 32, False)
+    assert rc == 0 and size == want_size and np.array_equal(buf[:size].cpu().numpy(), want)
