@@ -709,17 +709,19 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
 // Wide planes are always shared by the waves of a workgroup, which walk down the plane: with few
 // planes, or the longer chains of longer sub-blocks, the passes over memory of the unfused kernels,
 // which spread a plane over the chip, are faster.  How many planes it takes depends on the bound: with
-// outliers in every band the walk takes three times as long, and the host does not know of them.  So
-// the lines lie where a tight bound loses nothing.  Fused / unfused in us, planes of 375x500 at eb 1e-2,
-// 192 of them: 211 / 284, 512: 252 / 811; at eb 1e-3, 192: 614 / 364, 320: 665 / 570, 448: 673 / 905; planes of
-// 64x384 at eb 1e-3, 320: 108 / 100, 448: 108 / 135.  In planes of one or two rounds of bands the unfused
-// kernels' five launches weigh more: 20x512 at eb 1e-3, 192: 53 / 68, 40x300: 56 / 75.  Tensors larger than
-// the memory-side cache (256 MB) are slower for the unfused kernels: at eb 1e-3 320 planes of 1500x300
-// 1546 / 1904, of 2000x512 3697 / 3648, 256 of them 3567 / 3053.  With 128 codes per sub-block 256 planes of
-// 375x500 take 780 / 328; 64 planes of 700x1100, which need more column groups, 2122 / 429.
-static bool enough_wide_planes(uint32_t planes, uint32_t nbands, uint32_t numel)
+// outliers in every band the walk takes twice as long, and the host does not know of them.  So
+// the lines lie where a tight bound loses nothing.  Fused / unfused in us at eb 1e-2; 1e-3:
+//   planes of one or two rounds of bands, where the unfused kernels' five launches weigh more: 20x512, one
+//     plane: 23 / 37; 33 / 38, 64: 24 / 40; 36 / 44, 192: 24 / 46; 37 / 50; 40x300, one: 25 / 37; 36 / 40
+//   three rounds: 31x512, 64 planes: 31 / 41; 48 / 46; 60x300, 64: 34 / 43; 50 / 48, 128: 35 / 49; 51 / 54
+//   four: 95x300, 128: 45 / 58; 67 / 63, 192: 45 / 64; 67 / 68
+//   more: 190x300, 256: 80 / 108; 125 / 116; 375x500, 192: 179 / 217; 339 / 234, 288: 193 / 313; 362 / 345, 320:
+//     208 / 365; 377 / 413, 512: 227 / 643; 395 / 720; 64x384, 320: 44 / 66; 66 / 71
+//   tensors larger than the memory-side cache (256 MB): 2000x512, 256: 1309 / 1668; 2218 / 1985, 320:
+//     1416 / 2081; 2330 / 2472; 1500x300, 320: 973 / 1108 at eb 1e-3
+static bool enough_wide_planes(uint32_t planes, uint32_t nbands)
 {
-    return planes >= (nbands <= 2u * kWaves ? 192u : numel > (1u << 26) ? 320u : 448u);
+    return nbands <= 2u * kWaves || planes >= (nbands <= 4u * kWaves ? 192u : 320u);
 }
 
 bool plan_decode_fused(TensorD *t, uint32_t sub, bool wide)
@@ -737,7 +739,7 @@ bool plan_decode_fused(TensorD *t, uint32_t sub, bool wide)
         t->big = 1; t->G = 1; t->Rb = (uint32_t)(cap / W);
         t->nitems = planes;
     } else if (wide && sub == 32 && W <= (uint32_t)(kWideGroups * kWave * kWaves) &&
-               enough_wide_planes(planes, (uint32_t)((H + cap / W - 1) / (cap / W)), t->numel)) {
+               enough_wide_planes(planes, (uint32_t)((H + cap / W - 1) / (cap / W)))) {
         t->big = 3; t->G = 1; t->Rb = (uint32_t)(cap / W);
         t->nitems = planes;
     } else {
