@@ -61,18 +61,18 @@ MEASURED_TRAFFIC = {
     ("cfg5_resnet18_stream", 32, 1e-2): {
         "profile": "profiles/hbm_traffic_cfg5_resnet18_stream.txt",
         "per_elem": {
-            "k_quant_lorenzo_split_hist": 4.0177 + 1.0509,     # 8-bit symbols in the scratch
-            "k_lengths": 1.0088 + 0.0672,
-            "k_pack": 1.0138 + 0.6639,
-            "k_decode_fused": 0.8349 + 4.0088,
+            "k_quant_lorenzo_split_hist": 4.0178 + 1.1825,     # 8-bit symbols in the scratch
+            "k_lengths": 0.1413 + 0.0020,
+            "k_pack": 1.0110 + 0.7400,
+            "k_decode_fused": 0.8306 + 4.0090,
         },
         # vector instructions per element and the fraction of the kernel's time its vector units are busy
         # (profiles/instruction_counters_cfg5_resnet18_stream.txt)
         "valu": {
-            "k_quant_lorenzo_split_hist": (26.48, 0.684),
-            "k_lengths": (2.98, 0.355),
-            "k_pack": (12.27, 0.830),
-            "k_decode_fused": (46.02, 0.814),
+            "k_quant_lorenzo_split_hist": (27.47, 0.704),
+            "k_lengths": (0.57, 0.269),
+            "k_pack": (12.01, 0.732),
+            "k_decode_fused": (43.57, 0.828),
         },
     },
 }
