@@ -1,5 +1,6 @@
 // Huffman codebook on the GPU: histogram -> code lengths -> canonical codes.
-// One workgroup per tensor; no host round trip between the two sweeps of a compress.
+// One workgroup per tensor; no host round trip between the two sweeps of a compress.  For small tensors it
+// finds the container's offsets and writes its header too.
 //
 // Rule (fixes one of the equally optimal codebooks): leaves sorted ascending by
 // (count, symbol); two FIFO queues, leaves and internal nodes in creation order;

@@ -10,6 +10,8 @@
 //              their own bit positions, 128-bit stores; the bit count of every sub-block, which the
 //              offsets' prefix sum yields on the way; outlier records of the chunks that hold any.
 //
+// Where all tensors of the call are small (small_group), k_codebook does the work of the first two.
+//
 // The symbols are read once, 1 to 2 bytes per element, and packing workgroups never wait for one another:
 // every wave walks its own chunks with no workgroup barrier after the offsets are known.  While the bit
 // counts came from a pass over the symbols, the ResNet-18-shaped stream (591 M elements) took 138 us for
@@ -510,7 +512,8 @@ void launch_clear(const BatchC &b, Profiler *prof, hipStream_t st)
     if (b.n) launch(prof, kKClear, k_clear, dim3(b.n), dim3(kThreads), st, b);
 }
 
-// Bit counts, offsets and header, packing: three launches over all tensors of the group.
+// Bit counts, offsets and header (unless the codebook kernel has done these), packing: up to three launches over all
+// tensors of the group.
 void launch_pack(const BatchC &b, Profiler *prof, hipStream_t st)
 {
     if (!small_group(b)) {
