@@ -301,6 +301,7 @@ def test_roundtrip_random_shapes(orc, n, c, h, w, eb, radius, seed):
     assume(n * c * h * w >= 2)          # the generator divides by the sample std
     cfg = orc.Config(radius=radius, chunk=256, sub=32)
     x = activation((n, c, h, w), 3, 0.5, seed=seed).numpy()
+    assume(np.isfinite(x).all())        # a plane of two elements may be constant after the box filter: no spread to divide by
     rc, buf, size, stg = orc.compress(x, eb, cfg, want_stages=True)
     assert rc == 0
     assert np.array_equal(py_decode(buf, cfg), stg.sym)
