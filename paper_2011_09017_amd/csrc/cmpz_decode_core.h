@@ -1,16 +1,23 @@
 // Huffman decode core shared by the decompression kernels: table layout and the
 // per-lane decode loop.  Internal to libcmpz.
 //
-// One lookup table, indexed by where the next 32 bits of the stream lie in the left-aligned code space, on
-// a logarithmic scale: x = how far they lie below the top of the space, the table has 2^m entries for
-// every power of two of x.  Canonical codes grow with their length when left-aligned, so a code of L bits
-// starts where about 2^-L times the codes of its length are left of the space, and an entry there is about as
-// wide as the code whatever its length.  On a linear scale 2048 + 256 entries in two levels left 1.4 %
-// (eb 1e-2) to 77 % (eb 1e-3) of a wave's steps to the search below, and 26 to 98 % to the second level;
-// on this one it is below 0.1 % with m = 7, and 12 % at eb 1e-3 with m = 8.  64x256x56x56 at eb 5e-3 and
-// 128 codes per sub-block: 220 -> 159 us, 128x96x55x55 at eb 1e-3 and 32: 152 -> 102.  Flat codebooks, whose codes are all
-// about ten bits long, keep a linear scale.  The conversion of x to floating point is the logarithm: its
-// exponent and the first m bits of its mantissa, less those of the smallest x of the table, are the index.
+// One lookup table, indexed by where the next 32 bits of the stream lie in the left-aligned code space.  Canonical
+// codes grow with their length when left-aligned, so a code of L bits starts where about 2^-L times the codes of its
+// length are left of the space, and on a logarithmic scale of x, how far the bits lie below the top of the space,
+// an entry is about as wide as the code whatever its length: 2^m entries for every power of two of x.  The conversion
+// of x to floating point is the logarithm: its exponent and the first m bits of its mantissa, less those of the
+// smallest number of the scale, are the index.  Every codebook takes one of five scales, by what they leave of the
+// code space to the search below and by what their index costs (build_tables):
+//   x, m = 7      codes of up to 24 bits: steep codebooks
+//   x + 2^j, (j, m) = (24, 8)   codes of up to 16 bits in the upper 256th of the space, of fewer below
+//                     (28, 9)   13 bits in the upper sixteenth, fewer below
+//                     (30, 10)  every code of up to 12 bits: of at most 1024 codes those of 11 bits lie in the upper half of
+//                               the space and those of 12 in its upper quarter
+//                     (32, 11)  linear: every code of up to 11 bits
+// Share of the code space left to the search, with 2048 + 256 linear entries in two levels / with these five: eb 1e-2
+// 0.0003 / 0.00001, eb 1e-3 0.02 / below 0.0006, eb 5e-4 (codes of 10 to 12 bits) 0 / 0.  Restored in us, two levels / five scales:
+// 64x256x56x56 at eb 5e-3 with 128 codes per sub-block 214 / 149; 128x96x55x55 at eb 1e-3 with 32 codes 150 / 82 (90 with m = 8 on x
+// itself, which leaves 0.002), with 128 316 / 200; 3x256x51x53 at eb 5e-4 with 128 codes 55 / 51 (91 on the linear scale).
 // Whatever the table leaves is found by canonical search: decode_lds compares with the limits in range[]
 // for lengths below 32 and from there on with first[], as decode_run does for all of them.
 #pragma once
@@ -21,7 +28,9 @@ namespace cmpz {
 constexpr uint32_t kTableSize = 2304;        // entries: 4608 bytes of LDS, with the fused decoder's other arrays five
                                              // workgroups just fit a CU
 constexpr uint32_t kLinearBits = 11;         // of the index on a linear scale (2048 entries)
-constexpr uint32_t kLogMask = ~0xffu;        // bits of x that the index looks at: 24, so that the conversion is exact
+// Bits of x that the index looks at: as many as keep the conversion, and the sum with 2^j, exact (24 bits)
+constexpr uint32_t kLog7Mask = ~0xffu, kOffsetMask = ~0x1ffu;
+constexpr uint32_t kPowers7 = 17;            // powers of two there (entries no narrower than kLog7Mask allows)
 
 // Table entries: symbol in bits 0..9, code length in bits 10..15; 0 = not resolved here.
 struct DecodeTables {
@@ -35,8 +44,9 @@ struct DecodeTables {
     //       bits, and from the length of the shortest code on; rounded down beyond: no limit to search by)
     //   .y  what turns a code of that length into its index in the ordered symbols (mod 2^32)
     uint2    range[kMaxCodeLen + 2];
-    uint32_t log_shift;           // 22 - m, or 0: the scale is linear
-    uint32_t log_min;             // the smallest x of the table as a floating-point number's bits
+    uint32_t scale_min;           // the smallest number of the scale, as the bits of a float
+    uint32_t scale_shift;         // 23 - m
+    float    offset;              // 2^j, or 0
     uint32_t from;                // shortest length that the table leaves to the search, for some of its codes
     uint32_t searched;            // share of the code space that it leaves, in units of 2^-32
     uint32_t max_len;
@@ -69,8 +79,8 @@ __device__ __forceinline__ void load_tables(DecodeTables &dst, const DecodeTable
 
 // Validation of the container header and code lengths, and construction of the decode tables
 // in LDS, by one workgroup of NT >= 256 threads (every workgroup of the fused decode kernel does
-// this for itself: about a microsecond, and no separate kernel or round trip through memory).
-// The first 256 threads do the work (four symbols each); the others only help to fill the table.
+// this for itself: 12 400 clock cycles, 5 us, and no separate kernel or round trip through memory).
+// A chain of latencies bounds it: the four waves evaluate a scale each, and a thread looks up its nine entries side by side.
 // `scratch` is LDS the caller does not need yet (at least 12 KB; the ordered symbols are laid out
 // there as 16-bit values while the tables are filled).  Returns 0 or the status bits
 // of the defect found; contains barriers, so all NT threads must call it.
@@ -82,16 +92,18 @@ __device__ __forceinline__ void load_tables(DecodeTables &dst, const DecodeTable
 template <int NT>
 __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const DecompressArgs &a, uint32_t *scratch)
 {
-    static_assert(NT >= 256 && NT % 64 == 0, "whole waves, at least four");
+    static_assert(NT == 256 && kTableSize % NT == 0, "four waves: four symbols and nine entries per thread");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const bool worker = tid < 256;                                    // uniform in a wave
     Header *hd = reinterpret_cast<Header *>(scratch);                 // 64 words
     uint32_t *ends = scratch + 64;                                    // 4 words
     uint32_t *bad_s = scratch + 68, *bad2_s = scratch + 69;       // defects found before / after the second barrier
-    uint64_t *lim = reinterpret_cast<uint64_t *>(scratch + 72);       // 64 x u64: P[l+1], units of 2^-48
+    uint32_t *used_s = scratch + 70;
+    uint32_t *lim = scratch + 72;                                     // 64: P[l+1] in units of 2^-32, below 2^32
+    uint32_t *left_s = scratch + 136;                                 // per scale: share of the code space left to the search, 2^-31
+    uint32_t *from_s = scratch + 144;                                 // per scale: the shortest length that has some of it
     uint32_t (*wave_cnt)[64] = reinterpret_cast<uint32_t (*)[64]>(scratch + 200);   // 16 x 64: [pass*4 + wave][length]
     uint16_t *sorted = reinterpret_cast<uint16_t *>(scratch + 1224);  // kMaxSym x u16
-    uint32_t *used_s = scratch + 70;
+    uint32_t (*wave_off)[64] = reinterpret_cast<uint32_t (*)[64]>(scratch + 1736);  // the same: symbols in earlier passes and waves
     const uint32_t nsym = 2 * a.radius;
 
     if (tid < (int)(kHeaderBytes / 4)) {
@@ -114,7 +126,7 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
     for (int q = 0; q < 4; ++q) {
         const uint32_t k = q * 256u + tid;
         uint32_t v = 0;
-        if (worker && k < padded) v = a.buf[a.lay.off_lens + k];
+        if (k < padded) v = a.buf[a.lay.off_lens + k];
         if ((k >= nsym && v) || v > kMaxCodeLen) { bad_len = true; v = 0; }
         L[q] = v;
     }
@@ -163,127 +175,142 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
     uint32_t in_wave[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const uint32_t Lq = L[q];
-        uint32_t r = 0;
-        unsigned long long remaining = __ballot(Lq != 0);
-        while (remaining) {                                   // wave-uniform
-            const int leader = __ffsll((long long)remaining) - 1;
-            const uint32_t Lx = (uint32_t)__builtin_amdgcn_readlane((int)Lq, leader);
-            const unsigned long long m = __ballot(Lq == Lx);
-            if (Lq == Lx) r = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-            if (lane == leader) wave_cnt[q * 4 + wv][Lx] = (uint32_t)__popcll(m);
-            remaining &= ~m;
+        in_wave[q] = 0;
+        if (!__any(L[q] != 0)) continue;                              // (uniform; a small tensor's symbols lie close together)
+        unsigned long long same = ~0ull;                              // the lanes with this length
+#pragma unroll
+        for (uint32_t k = 0; k < 6; ++k) {
+            const bool set = (L[q] >> k) & 1u;
+            const unsigned long long those = __ballot(set);
+            same &= set ? those : ~those;
         }
-        in_wave[q] = r;
+        in_wave[q] = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+        if (L[q] && in_wave[q] == 0) wave_cnt[q * 4 + wv][L[q]] = (uint32_t)__popcll(same);
     }
     __syncthreads();
     if (*bad_s) return *bad_s;
 
-    // wave 0, lane = length: totals per length, start of every (pass, wave) group, first codes
-    if (wv == 0) {
+    // Every wave, lane = length: totals per length, the part of the code space of every length.  Wave 0 writes them down.
+    {
         uint32_t cnt = 0;
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             const uint32_t c = wave_cnt[k][lane];
-            wave_cnt[k][lane] = cnt;                          // symbols of this length in earlier groups
+            if (k / 4 == wv) wave_off[k][lane] = cnt;
             cnt += c;
         }
-        if (lane == 0) cnt = 0;
-        const uint32_t used = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(cnt), 63);
-        const uint32_t offs = wave_inclusive_sum(cnt) - cnt;
-        const unsigned long long present = __ballot(cnt != 0);
-        const uint32_t max_len = present ? 63u - (uint32_t)__builtin_clzll(present) : 0u;
+        const uint32_t sum = wave_inclusive_sum(cnt);
+        const uint32_t offs = sum - cnt, used = (uint32_t)__builtin_amdgcn_readlane((int)sum, 63);
         // s < 2^58: three limbs of 24 bits, each scanned in 32 bits without overflow
         const uint64_t sl = (lane >= 1 && lane <= (int)kMaxCodeLen) ? ((uint64_t)cnt << (kMaxCodeLen - lane)) : 0ull;
         const uint32_t i0 = wave_inclusive_sum((uint32_t)(sl & 0xffffffu));
         const uint32_t i1 = wave_inclusive_sum((uint32_t)((sl >> 24) & 0xffffffu));
         const uint32_t i2 = wave_inclusive_sum((uint32_t)(sl >> 48));
         const uint64_t incl = (uint64_t)i0 + ((uint64_t)i1 << 24) + ((uint64_t)i2 << 48);
-        const uint64_t excl = incl - sl;
-        const uint64_t first = (lane >= 1 && lane <= (int)kMaxCodeLen) ? (excl >> (kMaxCodeLen - lane)) : 0ull;
-        if (lane <= (int)kMaxCodeLen) {
-            T.first[lane] = first;
-            T.range[lane] = make_uint2((uint32_t)(incl >> (kMaxCodeLen - 32)) - 1u, offs - (uint32_t)first);
+        const uint64_t excl = incl - sl, one = 1ull << kMaxCodeLen;
+        if (wv == 0) {
+            const unsigned long long present = __ballot(cnt != 0);
+            const uint32_t max_len = present ? 63u - (uint32_t)__builtin_clzll(present) : 0u;
+            const uint64_t first = (lane >= 1 && lane <= (int)kMaxCodeLen) ? (excl >> (kMaxCodeLen - lane)) : 0ull;
+            if (lane <= (int)kMaxCodeLen) {
+                T.first[lane] = first;
+                T.range[lane] = make_uint2((uint32_t)(incl >> (kMaxCodeLen - 32)) - 1u, offs - (uint32_t)first);
+            }
+            if (lane == (int)kMaxCodeLen) T.first[lane + 1] = (first + cnt) << 1;
+            // (the top of the space is 2^32 here: one less is above every entry's smallest value too)
+            lim[lane] = incl < one ? (uint32_t)(incl >> (kMaxCodeLen - 32)) : 0xffffffffu;
+            if (lane == 63) {
+                uint32_t bad = 0;
+                if (used >= 2 && incl != one) bad = kStFormat;
+                if (used == 1 && max_len != 1) bad = kStFormat;
+                // no codeword at all: an empty tensor, or (version 2) nothing but sub-blocks of zero residuals
+                if (used == 0 && a.numel != 0 && !(a.zero_blocks && hd->total_bits == 0)) bad = kStFormat;
+                if (hd->max_len != max_len) bad = kStFormat;
+                if (bad) *bad2_s = bad;
+                *used_s = used;
+                T.max_len = max_len;
+            }
+            const unsigned long long beyond = __ballot(cnt != 0 && lane > (int)kLinearBits);
+            if (lane == (int)kLinearBits) {
+                left_s[4] = incl < one ? (uint32_t)((one - incl) >> (kMaxCodeLen - 31)) : 0u;
+                from_s[4] = beyond ? (uint32_t)__ffsll((long long)beyond) - 1u : 1u;
+            }
         }
-        if (lane == (int)kMaxCodeLen) T.first[lane + 1] = (first + cnt) << 1;
-        lim[lane] = incl;
-        if (lane == 63) {
-            uint32_t bad = 0;
-            const uint64_t one = 1ull << kMaxCodeLen;
-            if (used >= 2 && incl != one) bad = kStFormat;
-            if (used == 1 && max_len != 1) bad = kStFormat;
-            // no codeword at all: an empty tensor, or (version 2) nothing but sub-blocks of zero residuals
-            if (used == 0 && a.numel != 0 && !(a.zero_blocks && hd->total_bits == 0)) bad = kStFormat;
-            if (hd->max_len != max_len) bad = kStFormat;
-            if (bad) *bad2_s = bad;
-            *used_s = used;
-            T.max_len = max_len;
-        }
-        // The scale that leaves the least of the code space to the search.  With 2^m entries for every power of
-        // two of x and `powers` of these, codes of this lane's length have no entry where the entries are wider,
-        // and below the table's smallest x (whose own entry is not used: what lies below ends up there).
-        const uint64_t xh = (1ull << kMaxCodeLen) - excl, xl = (1ull << kMaxCodeLen) - incl;     // they lie in [xl, xh)
-        auto left_open = [&](uint32_t m, uint32_t powers) -> uint64_t {
-            if (cnt == 0) return 0;
-            const uint32_t k = 33u + m + (kMaxCodeLen - 32) - (uint32_t)lane;                    // (lane <= kMaxCodeLen)
-            const uint64_t wide_from = 1ull << (k < kMaxCodeLen ? k : kMaxCodeLen);
-            const uint64_t smallest = (1ull << (kMaxCodeLen - powers)) + (1ull << (kMaxCodeLen - powers - m));
-            const uint64_t a = xl > wide_from ? xl : wide_from, b = a < xh ? a : xh;             // no entry in [b, xh)
+        // The wave's scale: what it leaves of the codes of this lane's length, x in [xl, xh).  They have no entry where the
+        // entries are wider than they are, and on x itself below the smallest x (whose own entry is not used: what lies
+        // below ends up there).
+        const uint32_t m = 7u + wv;
+        const uint64_t added = wv == 0 ? 0ull : wv == 1 ? 1ull << (24 + kMaxCodeLen - 32) : wv == 2 ? 1ull << (28 + kMaxCodeLen - 32) : 1ull << (30 + kMaxCodeLen - 32);
+        uint64_t left = 0;
+        if (cnt != 0 && lane >= 1 && lane <= (int)kMaxCodeLen) {
+            const uint64_t xh = one - excl, xl = one - incl;
+            const uint64_t sum_from = 1ull << (kMaxCodeLen + 1u + m - (uint32_t)lane);           // of x + 2^j: wider from here on
+            const uint64_t wide_from = sum_from > added ? sum_from - added : 0ull;
+            const uint64_t smallest = wv == 0 ? (1ull << (kMaxCodeLen - kPowers7)) + (1ull << (kMaxCodeLen - kPowers7 - 7)) : 0ull;
+            const uint64_t from = xl > wide_from ? xl : wide_from, b = from < xh ? from : xh;    // no entry in [b, xh)
             const uint64_t d = smallest < b ? smallest : b;                                      // nor in [xl, d)
-            return (xh - b) + (xl < d ? d - xl : 0ull);
-        };
-        auto total = [&](uint64_t u) -> uint32_t {                   // in units of 2^-31
-            return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum((uint32_t)(u >> (kMaxCodeLen - 31))), 63);
-        };
-        uint64_t best = lane > (int)kLinearBits && cnt ? xh - xl : 0ull;
-        uint32_t least = total(best), best_m = 0, best_powers = 0;
-#pragma unroll
-        for (uint32_t m = 9; m >= 7; --m) {
-            const uint32_t powers = m == 7 ? 17u : kTableSize >> m;  // (entries no narrower than kLogMask allows)
-            const uint64_t u = left_open(m, powers);
-            const uint32_t t = total(u);
-            if (t <= least) { best = u; least = t; best_m = m; best_powers = powers; }
+            left = (xh - b) + (xl < d ? d - xl : 0ull);
         }
-        const unsigned long long some = __ballot(best != 0);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum((uint32_t)(left >> (kMaxCodeLen - 31))), 63);
+        const unsigned long long some = __ballot(left != 0);
         if (lane == 0) {
-            T.log_shift = best_m ? 22u - best_m : 0u;
-            T.log_min = (127u + 32u - best_powers) << 23;
-            T.from = some ? (uint32_t)__ffsll((long long)some) - 1u : 1u;
-            T.searched = least < 0x7fffffffu ? 2u * least : 0xffffffffu;
+            left_s[wv] = total;
+            from_s[wv] = some ? (uint32_t)__ffsll((long long)some) - 1u : 1u;
         }
     }
     __syncthreads();
     if (*bad2_s) return *bad2_s;
 
+    // The scale to take.  An index on x with m = 7 takes two instructions more than a linear one and one on x + 2^j three, of some
+    // sixteen per codeword; a search takes about ten codewords' time, and the 64 lanes of a wave wait for any of them.
+    uint32_t scale = 4, least = left_s[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t cost = left_s[k] + (k ? 3u << 18 : 1u << 18);  // (2^18: 0.00012 of the space)
+        if (cost < least) { least = cost; scale = k; }
+    }
+    scale = uniform_u32(scale);
+    const uint32_t m = 7u + scale, j = scale == 1u ? 24u : scale == 2u ? 28u : scale == 3u ? 30u : 32u;
+    const uint32_t shift = 23u - m, least_f = (127u + (scale ? j : 32u - kPowers7)) << 23;
+    const uint64_t added = scale ? 1ull << j : 0ull;
+    if (tid == 0) {
+        T.scale_min = least_f; T.scale_shift = shift;
+        T.offset = (float)added;
+        T.from = from_s[scale];
+        T.searched = left_s[scale] < 0x7fffffffu ? 2u * left_s[scale] : 0xffffffffu;
+    }
+
     // symbols ordered by (length, symbol)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        if (L[q]) sorted[T.range[L[q]].y + (uint32_t)T.first[L[q]] + wave_cnt[q * 4 + wv][L[q]] + in_wave[q]] = (uint16_t)((q * 256 + tid - a.radius) & 1023u);
-    __syncthreads();
+        if (L[q]) sorted[T.range[L[q]].y + (uint32_t)T.first[L[q]] + wave_off[q * 4 + wv][L[q]] + in_wave[q]] = (uint16_t)((q * 256 + tid - a.radius) & 1023u);
 
     // the table: an entry holds a codeword only if all of it lies inside that code's part of the space
     {
-        const uint32_t log_shift = T.log_shift, log_min = T.log_min, m = 22u - log_shift;
-        for (uint32_t idx = tid; idx < kTableSize; idx += NT) {
-            uint32_t v, longest;                                 // its smallest left-aligned value; the longest code it may hold
-            if (log_shift) {                                     // uniform
-                const uint32_t f = log_min + (idx << (log_shift + 1u));
-                const uint32_t power = (f >> 23) - 127u;                         // below 32 for all x there are
-                const uint32_t x = power < 32u ? (uint32_t)(((uint64_t)((f & 0x7fffffu) | 0x800000u) << power) >> 23) : 0u;
-                v = ~(x + (1u << ((power - m) & 31u)) - 1u);
-                longest = power < 32u && idx ? 32u - (power - m) : 0u;
-            } else {
-                v = idx << (32u - kLinearBits);
-                longest = idx < (1u << kLinearBits) ? kLinearBits : 0u;
-            }
-            const uint64_t v48 = (uint64_t)v << (kMaxCodeLen - 32);
-            uint32_t l = 0;                                      // lengths whose codes all lie below v
+        constexpr uint32_t kPer = kTableSize / NT;
+        uint32_t v[kPer], longest[kPer], l[kPer];                // its smallest left-aligned value; the longest code it may hold
 #pragma unroll
-            for (uint32_t step = 32; step >= 1; step >>= 1) l += (v48 >= lim[l + step]) ? step : 0u;
-            ++l;
-            uint32_t e = 0;
-            if (l <= longest) e = sorted[T.range[l].y + (v >> (32u - l))] | (l << 10);
-            T.entry[idx] = (uint16_t)e;
+        for (uint32_t i = 0; i < kPer; ++i) {
+            const uint32_t idx = tid + i * NT;
+            const uint32_t f = least_f + (idx << shift), power = (f >> 23) - 127u;                     // at most 33
+            const uint64_t end = (((uint64_t)((f & 0x7fffffu) | 0x800000u) << power) >> 23) + (1ull << (power - m)) - added;     // of its x
+            v[i] = 0u - (uint32_t)end;
+            longest[i] = end <= (1ull << 32) && (idx || added) ? 32u - (power - m) : 0u;
+            l[i] = 0;                                            // lengths whose codes all lie below v (no more than 31 count)
+        }
+#pragma unroll
+        for (uint32_t step = 16; step >= 1; step >>= 1) {
+#pragma unroll
+            for (uint32_t i = 0; i < kPer; ++i) l[i] += (v[i] >= lim[l[i] + step]) ? step : 0u;
+        }
+        uint32_t at[kPer];
+#pragma unroll
+        for (uint32_t i = 0; i < kPer; ++i) { ++l[i]; at[i] = T.range[l[i]].y + (v[i] >> (32u - l[i])); }
+        __syncthreads();                                         // the symbols are in order
+#pragma unroll
+        for (uint32_t i = 0; i < kPer; ++i) {
+            const uint32_t e = sorted[at[i] & (kMaxSym - 1u)] | (l[i] << 10);
+            T.entry[tid + i * NT] = (uint16_t)(l[i] <= longest[i] ? e : 0u);
         }
     }
     // the ordered symbols in their packed form, for the codewords that the table leaves
@@ -307,30 +334,44 @@ __device__ __forceinline__ int32_t entry_residual(uint32_t e)
     return __builtin_amdgcn_sbfe((int)e, 0, 10);
 }
 
-// The table's entry for the next 32 bits of a stream; 0: not resolved.
-__device__ __forceinline__ uint32_t log_offset(uint32_t hi, uint32_t log_shift, uint32_t log_min)
-{
-    uint32_t x;                                               // ~hi & kLogMask in one instruction
-    asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(x) : "v"(hi), "s"(kLogMask));
-    // (what lies below the smallest x saturates to entry 0, which is empty)
-    return (__builtin_elementwise_sub_sat(__float_as_uint((float)x), log_min) >> log_shift) & ~1u;
-}
-// the same for m = 7, where the exponent and the bits of the mantissa are the upper half of the number
-constexpr uint32_t kShift7 = 22 - 7;
-// (`one` is 1, in a vector register)
-__device__ __forceinline__ uint32_t log7_offset(uint32_t hi, uint32_t log_min, uint32_t one)
-{
-    uint32_t x;
-    asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(x) : "v"(hi), "s"(kLogMask));
-    const uint32_t above = __builtin_elementwise_sub_sat(__float_as_uint((float)x), log_min);
-    uint32_t r;                                               // (above >> 16) << 1 in one instruction
-    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(r) : "v"(one), "v"(above));
-    return r;
-}
-__device__ __forceinline__ uint32_t linear_offset(uint32_t hi)
-{
-    return (hi >> (31u - kLinearBits)) & ((2u << kLinearBits) - 2u);
-}
+// Where in the table (in bytes) the entry for the next 32 bits of a stream lies; an entry of 0: not resolved.
+enum Scale : int { kScaleLinear = 0, kScaleOffset = 1, kScaleLog7 = 2 };
+struct ScaleArgs {
+    uint32_t min, shift, base;                                // (uniform)
+    float    offset;
+    __device__ __forceinline__ explicit ScaleArgs(const DecodeTables &T)
+        : min(uniform_u32(T.scale_min)), shift(uniform_u32(T.scale_shift)), base(0u - ((min >> shift) << 1)),
+          offset(__uint_as_float(uniform_u32(__float_as_uint(T.offset))))
+    {
+    }
+    __device__ __forceinline__ int scale() const { return offset == 0.0f ? kScaleLog7 : shift == 23u - kLinearBits ? kScaleLinear : kScaleOffset; }
+    // ~hi & mask in one instruction
+    static __device__ __forceinline__ uint32_t x_of(uint32_t hi, uint32_t mask)
+    {
+        uint32_t x;
+        asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(x) : "v"(hi), "s"(mask));
+        return x;
+    }
+    // five instructions (kScaleOffset, which does for kScaleLinear too), four or two
+    template <int SCALE>
+    __device__ __forceinline__ uint32_t place(uint32_t hi) const
+    {
+        if (SCALE == kScaleLinear) return ~(hi >> (31u - kLinearBits)) & ((2u << kLinearBits) - 2u);
+        if (SCALE == kScaleOffset) return ((__float_as_uint((float)x_of(hi, kOffsetMask) + offset) >> shift) << 1) + base;
+        // (what lies below the smallest x saturates to entry 0, which is empty)
+        const uint32_t above = __builtin_elementwise_sub_sat(__float_as_uint((float)x_of(hi, kLog7Mask)), min);
+        uint32_t r;                                           // (above >> 16) * 2 in one instruction
+        asm("v_mad_u32_u16 %0, %1, 2, 0 op_sel:[1,0,0,0]" : "=v"(r) : "v"(above));
+        return r;
+    }
+    // the same for any scale; mask: kLog7Mask or kOffsetMask, uniform
+    __device__ __forceinline__ uint32_t mask() const { return offset == 0.0f ? kLog7Mask : kOffsetMask; }
+    __device__ __forceinline__ uint32_t place_any(uint32_t hi, uint32_t mask) const
+    {
+        const uint32_t f = __float_as_uint((float)x_of(hi, mask) + offset);
+        return (((f > min ? f : min) >> shift) << 1) + base;
+    }
+};
 
 // Canonical search over the lengths that the table does not resolve, for the entry it would have; v: the next 64
 // bits of the stream, of which kMaxCodeLen count.  As in decode_lds.
@@ -372,7 +413,8 @@ __device__ __forceinline__ uint32_t decode_run(const DecodeTables &T, RD rd, uin
     int avail = 64 - (int)(start & 31);
     wi += 2;
     uint32_t nxt = rd(wi);
-    const uint32_t log_shift = uniform_u32(T.log_shift), log_min = uniform_u32(T.log_min);
+    const ScaleArgs sc(T);
+    const uint32_t mask = sc.mask();
     const char *table = reinterpret_cast<const char *>(T.entry);
     for (uint32_t k = 0; k < count; ++k) {
         if (avail <= 32) {
@@ -384,7 +426,7 @@ __device__ __forceinline__ uint32_t decode_run(const DecodeTables &T, RD rd, uin
             nxt = rd(wi);
         }
         const uint32_t hi = (uint32_t)(win >> 32);
-        uint32_t e = *reinterpret_cast<const uint16_t *>(table + (log_shift ? log_offset(hi, log_shift, log_min) : linear_offset(hi)));
+        uint32_t e = *reinterpret_cast<const uint16_t *>(table + sc.place_any(hi, mask));
         if (e == 0) {
             {
                 // canonical search on a fresh 64-bit window
@@ -430,13 +472,12 @@ __device__ __forceinline__ uint32_t decode_run(const DecodeTables &T, RD rd, uin
 // (stage_tail_words).
 constexpr uint32_t stage_tail_words(uint32_t count) { return count * kMaxCodeLen / 32 + 4; }
 //
-// LOG: the scale of the table (see there).
 constexpr int kStagePad = 4;
-template <bool LOG, class PUT>
+template <int SCALE, class PUT>
 __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint32_t *S, uint32_t pos,
                                                uint32_t count, uint32_t skip, PUT put, bool &bad)
 {
-    const uint32_t log_shift = uniform_u32(T.log_shift), log_min = uniform_u32(T.log_min);
+    const ScaleArgs sc(T);
     const char *table = reinterpret_cast<const char *>(T.entry);
     // The three stream words around the position live in registers: wa, wb are the window of the
     // current codeword, wc the word after them.  A codeword of the table is at
@@ -455,7 +496,7 @@ __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint
 #pragma unroll 4
     for (uint32_t k = 0; k < count; ++k) {
         const uint32_t hi = __builtin_amdgcn_alignbit(wa, wb, npos);
-        uint32_t e = *reinterpret_cast<const uint16_t *>(table + (LOG ? log_offset(hi, log_shift, log_min) : linear_offset(hi)));
+        uint32_t e = *reinterpret_cast<const uint16_t *>(table + sc.place<SCALE>(hi));
         if (__builtin_expect(e == 0, 0)) {
             {
                 // canonical search over the lengths that the table does not resolve.  Up to 31 bits the
@@ -513,9 +554,6 @@ __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint
     return 0u - npos;
 }
 
-// The scale of the table, as decode_rows_32 takes it.
-enum Scale : int { kScaleLinear = 0, kScaleLog = 1, kScaleLog7 = 2 };
-
 // decode_lds for complete sub-blocks of 32 codes, whose residuals are summed along the rows: bit k of
 // `keep` is 0 where element k starts a row; my[k] takes the sum.  Four codewords at a time: one that the table does
 // not resolve has entry 0, which moves nothing, so that the ones behind it find the same; whether there was any is
@@ -525,7 +563,7 @@ template <int SCALE>
 __device__ __forceinline__ uint32_t decode_rows_32(const DecodeTables &T, const uint32_t *S, uint32_t pos, uint32_t keep,
                                                    int16_t *my, bool &bad)
 {
-    const uint32_t log_shift = uniform_u32(T.log_shift), log_min = uniform_u32(T.log_min);
+    const ScaleArgs sc(T);
     const char *table = reinterpret_cast<const char *>(T.entry);
     uint32_t npos = 0u - pos;
     int32_t N = (int32_t)npos >> 5;
@@ -534,11 +572,8 @@ __device__ __forceinline__ uint32_t decode_rows_32(const DecodeTables &T, const 
     const uint32_t sw1 = (uint32_t)(uintptr_t)(lds_word_ptr)(Sw + 1);
     uint32_t wa = Sw[-1 - N], wb = Sw[-N], wc = Sw[1 - N];
     int32_t run = 0;
-    uint32_t one = 1;
-    asm("" : "+v"(one));
     auto look = [&](uint32_t hi) -> uint32_t {
-        const uint32_t at = SCALE == kScaleLog7 ? log7_offset(hi, log_min, one) : SCALE == kScaleLog ? log_offset(hi, log_shift, log_min) : linear_offset(hi);
-        uint32_t e = *reinterpret_cast<const uint16_t *>(table + at);
+        uint32_t e = *reinterpret_cast<const uint16_t *>(table + sc.place<SCALE>(hi));
         asm("" : "+v"(e));                                    // (or it is kept as 16 bits and extended again)
         return e;
     };

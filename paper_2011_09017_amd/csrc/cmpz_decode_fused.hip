@@ -179,9 +179,11 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
             return;
         }
     }
-    const bool log_scale = uniform_u32(T.log_shift) != 0;
+    const int scale = ScaleArgs(T).scale();              // uniform
     auto decode_staged = [&](const uint32_t *stage, uint32_t pos, uint32_t count, uint32_t skip, auto put, bool &lbad) -> uint32_t {
-        return log_scale ? decode_lds<true>(T, stage, pos, count, skip, put, lbad) : decode_lds<false>(T, stage, pos, count, skip, put, lbad);
+        return scale == kScaleLog7 ? decode_lds<kScaleLog7>(T, stage, pos, count, skip, put, lbad)
+             : scale == kScaleOffset ? decode_lds<kScaleOffset>(T, stage, pos, count, skip, put, lbad)
+                                     : decode_lds<kScaleLinear>(T, stage, pos, count, skip, put, lbad);
     };
     // ---- from here on the waves are on their own ----
     RT       *R = lds.Rs[wv];
@@ -516,10 +518,9 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
                     my_reset = k0 < 32u ? k0 : (uint32_t)SUB;
                     for (; k0 < 32u; k0 += W) mask |= 1u << k0;
                     if (staged && !zeros_only) {
-                        const uint32_t shift = uniform_u32(T.log_shift);
-                        const uint32_t e = shift == kShift7 ? decode_rows_32<kScaleLog7>(T, S, spos, ~mask, my, lbad)
-                                         : shift ? decode_rows_32<kScaleLog>(T, S, spos, ~mask, my, lbad)
-                                                 : decode_rows_32<kScaleLinear>(T, S, spos, ~mask, my, lbad);
+                        const uint32_t e = scale == kScaleLog7 ? decode_rows_32<kScaleLog7>(T, S, spos, ~mask, my, lbad)
+                                         : scale == kScaleOffset ? decode_rows_32<kScaleOffset>(T, S, spos, ~mask, my, lbad)
+                                                                 : decode_rows_32<kScaleLinear>(T, S, spos, ~mask, my, lbad);
                         end = e - spos + start;
                     } else {
                         int32_t run = 0;
