@@ -79,8 +79,11 @@ __device__ __forceinline__ void load_tables(DecodeTables &dst, const DecodeTable
 
 // Validation of the container header and code lengths, and construction of the decode tables
 // in LDS, by one workgroup of NT >= 256 threads (every workgroup of the fused decode kernel does
-// this for itself: 12 400 clock cycles, 5 us, and no separate kernel or round trip through memory).
-// A chain of latencies bounds it: the four waves evaluate a scale each, and a thread looks up its nine entries side by side.
+// this for itself, and no separate kernel or round trip through memory).  10 400 clock cycles, 4.3 us, of which 1900 until the
+// code lengths are here; latencies bound it, so a thread looks up its nine entries side by side, the waves evaluate a
+// scale each, and the header's check has a wave of its own (12 400 with that check before the ranks, one more barrier and the
+// shares in 64 bits; 17 300 with one entry after the other, all scales in one wave and a pass per length for the ranks:
+// 1x64x56x56 17.3 / 15.3 / 14.5 us).
 // `scratch` is LDS the caller does not need yet (at least 12 KB; the ordered symbols are laid out
 // there as 16-bit values while the tables are filled).  Returns 0 or the status bits
 // of the defect found; contains barriers, so all NT threads must call it.
@@ -96,19 +99,21 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     Header *hd = reinterpret_cast<Header *>(scratch);                 // 64 words
     uint32_t *ends = scratch + 64;                                    // 4 words
-    uint32_t *bad_s = scratch + 68, *bad2_s = scratch + 69;       // defects found before / after the second barrier
+    uint32_t *bad_s = scratch + 68, *bad2_s = scratch + 69;       // defects found in the header or in a length / in the lengths together
     uint32_t *used_s = scratch + 70;
     uint32_t *lim = scratch + 72;                                     // 64: P[l+1] in units of 2^-32, below 2^32
     uint32_t *left_s = scratch + 136;                                 // per scale: share of the code space left to the search, 2^-31
-    uint32_t *from_s = scratch + 144;                                 // per scale: the shortest length that has some of it
+    uint32_t *from_s = scratch + 144;                                 // per scale: the shortest length that has some of it; 0: none
     uint32_t (*wave_cnt)[64] = reinterpret_cast<uint32_t (*)[64]>(scratch + 200);   // 16 x 64: [pass*4 + wave][length]
     uint16_t *sorted = reinterpret_cast<uint16_t *>(scratch + 1224);  // kMaxSym x u16
     uint32_t (*wave_off)[64] = reinterpret_cast<uint32_t (*)[64]>(scratch + 1736);  // the same: symbols in earlier passes and waves
     const uint32_t nsym = 2 * a.radius;
 
+    bool bad_here = false;                                            // the reserved tail of the header must be zero
     if (tid < (int)(kHeaderBytes / 4)) {
         const uint32_t v = reinterpret_cast<const uint32_t *>(a.buf)[tid];
         scratch[tid] = v;
+        bad_here = tid >= (int)(offsetof(Header, zero) / 4) && v != 0;
     }
     if (tid >= 64 && tid < 68) {
         const uint32_t *chunk_off = reinterpret_cast<const uint32_t *>(a.buf + a.lay.off_chunk_off);
@@ -117,64 +122,22 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
         ends[k] = (k == 0) ? chunk_off[0] : (k == 1) ? chunk_off[a.lay.nchunks] : (k == 2) ? outl_off[0] : outl_off[a.lay.nchunks];
     }
     if (tid == 68) { *bad_s = 0; *bad2_s = 0; }
-    for (int k = tid; k < 16 * 64; k += NT) (&wave_cnt[0][0])[k] = 0;
-    // code lengths, 4 symbols per thread (symbol q*256 + tid), fetched while the header arrives
+    // code lengths, 4 symbols per thread (symbol q*256 + tid)
     const uint32_t padded = (nsym + 15u) & ~15u;
     uint32_t L[4];
-    bool bad_len = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const uint32_t k = q * 256u + tid;
         uint32_t v = 0;
         if (k < padded) v = a.buf[a.lay.off_lens + k];
-        if ((k >= nsym && v) || v > kMaxCodeLen) { bad_len = true; v = 0; }
+        if ((k >= nsym && v) || v > kMaxCodeLen) { bad_here = true; v = 0; }
         L[q] = v;
     }
-    __syncthreads();
-    {
-        // the reserved tail of the header must be zero
-        constexpr int kFirstZero = (int)(offsetof(Header, zero) / 4);
-        bool nz = false;
-        if (tid >= kFirstZero && tid < (int)(kHeaderBytes / 4)) nz = scratch[tid] != 0;
-        if (nz || bad_len) atomicOr(bad_s, kStFormat);
-    }
-    if (tid == 0) {
-        uint32_t bad = 0;
-        const Layout &l = a.lay;
-        if (hd->magic != kMagic || (hd->version != kVersion && hd->version != kVersionZB) || hd->status != 0) bad = kStFormat;
-        if (!bad) {
-            if (hd->eb_bits != a.eb_bits) bad = kStMismatch;
-            if (hd->version != (a.zero_blocks ? kVersionZB : kVersion)) bad = kStMismatch;
-            for (int k = 0; k < 4; ++k) if (hd->shape[k] != a.shape[k]) bad = kStMismatch;
-            if (hd->radius != a.radius || hd->chunk != kChunk || hd->sub != a.sub ||
-                hd->guard_shift != a.guard_shift) bad = kStMismatch;
-        }
-        if (!bad) {
-            const uint64_t n_out = hd->n_outliers;
-            const uint64_t sect = (4 * n_out + 15) & ~15ull;
-            if (hd->numel != a.numel || hd->nchunks != l.nchunks) bad = kStFormat;
-            else if (hd->off_lens != l.off_lens || hd->off_chunk_off != l.off_chunk_off ||
-                     hd->off_outl_off != l.off_outl_off || hd->off_sub_bits != l.off_sub_bits ||
-                     hd->off_payload != l.off_payload) bad = kStFormat;
-            else if (hd->total_size > a.size || n_out > a.numel || hd->range_events > a.numel) bad = kStFormat;
-            else if (hd->off_outl_idx < l.off_payload || ((hd->off_outl_idx - l.off_payload) & 15)) bad = kStFormat;
-            else if (hd->off_outl_val != hd->off_outl_idx + sect || hd->total_size != hd->off_outl_val + sect)
-                bad = kStFormat;
-            else if (((hd->off_outl_idx - l.off_payload) >> 4) >= (1ull << 32)) bad = kStFormat;
-            if (!bad) {
-                const uint32_t units = (uint32_t)((hd->off_outl_idx - l.off_payload) >> 4);
-                if (ends[0] != 0 || ends[1] != units) bad = kStFormat;
-                if (ends[2] != 0 || ends[3] != (uint32_t)n_out) bad = kStFormat;
-                T.payload_units = units;
-                T.n_outliers = (uint32_t)n_out;
-            }
-        }
-        if (bad) atomicOr(bad_s, bad);
-    }
-    // rank of every symbol among the symbols of its length in its wave and pass
+    // rank of every symbol among the symbols of its length in its wave and pass (the wave's own rows: no barrier)
     uint32_t in_wave[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+        wave_cnt[q * 4 + wv][lane] = 0;
         in_wave[q] = 0;
         if (!__any(L[q] != 0)) continue;                              // (uniform; a small tensor's symbols lie close together)
         unsigned long long same = ~0ull;                              // the lanes with this length
@@ -185,10 +148,11 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
             same &= set ? those : ~those;
         }
         in_wave[q] = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");        // (the row is cleared)
         if (L[q] && in_wave[q] == 0) wave_cnt[q * 4 + wv][L[q]] = (uint32_t)__popcll(same);
     }
     __syncthreads();
-    if (*bad_s) return *bad_s;
+    if (bad_here) atomicOr(bad_s, kStFormat);
 
     // Every wave, lane = length: totals per length, the part of the code space of every length.  Wave 0 writes them down.
     {
@@ -196,7 +160,7 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             const uint32_t c = wave_cnt[k][lane];
-            if (k / 4 == wv) wave_off[k][lane] = cnt;
+            wave_off[k][lane] = cnt;                                  // (every wave, the same)
             cnt += c;
         }
         const uint32_t sum = wave_inclusive_sum(cnt);
@@ -233,32 +197,65 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
             const unsigned long long beyond = __ballot(cnt != 0 && lane > (int)kLinearBits);
             if (lane == (int)kLinearBits) {
                 left_s[4] = incl < one ? (uint32_t)((one - incl) >> (kMaxCodeLen - 31)) : 0u;
-                from_s[4] = beyond ? (uint32_t)__ffsll((long long)beyond) - 1u : 1u;
+                from_s[4] = beyond ? (uint32_t)__ffsll((long long)beyond) - 1u : 0u;
             }
+        }
+        if (tid == 192) {
+            uint32_t bad = 0;
+            const Layout &l = a.lay;
+            if (hd->magic != kMagic || (hd->version != kVersion && hd->version != kVersionZB) || hd->status != 0) bad = kStFormat;
+            if (!bad) {
+                if (hd->eb_bits != a.eb_bits) bad = kStMismatch;
+                if (hd->version != (a.zero_blocks ? kVersionZB : kVersion)) bad = kStMismatch;
+                for (int k = 0; k < 4; ++k) if (hd->shape[k] != a.shape[k]) bad = kStMismatch;
+                if (hd->radius != a.radius || hd->chunk != kChunk || hd->sub != a.sub ||
+                    hd->guard_shift != a.guard_shift) bad = kStMismatch;
+            }
+            if (!bad) {
+                const uint64_t n_out = hd->n_outliers;
+                const uint64_t sect = (4 * n_out + 15) & ~15ull;
+                if (hd->numel != a.numel || hd->nchunks != l.nchunks) bad = kStFormat;
+                else if (hd->off_lens != l.off_lens || hd->off_chunk_off != l.off_chunk_off ||
+                         hd->off_outl_off != l.off_outl_off || hd->off_sub_bits != l.off_sub_bits ||
+                         hd->off_payload != l.off_payload) bad = kStFormat;
+                else if (hd->total_size > a.size || n_out > a.numel || hd->range_events > a.numel) bad = kStFormat;
+                else if (hd->off_outl_idx < l.off_payload || ((hd->off_outl_idx - l.off_payload) & 15)) bad = kStFormat;
+                else if (hd->off_outl_val != hd->off_outl_idx + sect || hd->total_size != hd->off_outl_val + sect)
+                    bad = kStFormat;
+                else if (((hd->off_outl_idx - l.off_payload) >> 4) >= (1ull << 32)) bad = kStFormat;
+                if (!bad) {
+                    const uint32_t units = (uint32_t)((hd->off_outl_idx - l.off_payload) >> 4);
+                    if (ends[0] != 0 || ends[1] != units) bad = kStFormat;
+                    if (ends[2] != 0 || ends[3] != (uint32_t)n_out) bad = kStFormat;
+                    T.payload_units = units;
+                    T.n_outliers = (uint32_t)n_out;
+                }
+            }
+            if (bad) atomicOr(bad_s, bad);
         }
         // The wave's scale: what it leaves of the codes of this lane's length, x in [xl, xh).  They have no entry where the
         // entries are wider than they are, and on x itself below the smallest x (whose own entry is not used: what lies
         // below ends up there).
-        const uint32_t m = 7u + wv;
-        const uint64_t added = wv == 0 ? 0ull : wv == 1 ? 1ull << (24 + kMaxCodeLen - 32) : wv == 2 ? 1ull << (28 + kMaxCodeLen - 32) : 1ull << (30 + kMaxCodeLen - 32);
-        uint64_t left = 0;
-        if (cnt != 0 && lane >= 1 && lane <= (int)kMaxCodeLen) {
-            const uint64_t xh = one - excl, xl = one - incl;
-            const uint64_t sum_from = 1ull << (kMaxCodeLen + 1u + m - (uint32_t)lane);           // of x + 2^j: wider from here on
-            const uint64_t wide_from = sum_from > added ? sum_from - added : 0ull;
-            const uint64_t smallest = wv == 0 ? (1ull << (kMaxCodeLen - kPowers7)) + (1ull << (kMaxCodeLen - kPowers7 - 7)) : 0ull;
-            const uint64_t from = xl > wide_from ? xl : wide_from, b = from < xh ? from : xh;    // no entry in [b, xh)
-            const uint64_t d = smallest < b ? smallest : b;                                      // nor in [xl, d)
-            left = (xh - b) + (xl < d ? d - xl : 0ull);
+        // In units of 2^-31, which are exact up to 24 bits; no scale has longer codes.
+        const uint32_t m = 7u + wv, added = wv == 0 ? 0u : wv == 1 ? 1u << 23 : wv == 2 ? 1u << 27 : 1u << 29;
+        const uint32_t xh = (uint32_t)((one - excl) >> (kMaxCodeLen - 31)), xl = (uint32_t)((one - incl) >> (kMaxCodeLen - 31));
+        uint32_t left = xh - xl;
+        if (lane <= 24) {
+            const uint32_t wide_from = lane <= (int)m ? 0xffffffffu : 1u << (32u + m - (uint32_t)lane);      // of x + 2^j
+            const uint32_t from = wide_from > xl + added ? wide_from - added : xl, b = from < xh ? from : xh;      // no entry in [b, xh)
+            const uint32_t smallest = wv == 0 ? (1u << (31 - kPowers7)) + (1u << (31 - kPowers7 - 7)) : 0u, d = smallest < b ? smallest : b;
+            left = (xh - b) + (xl < d ? d - xl : 0u);                                                        // nor in [xl, d)
         }
-        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum((uint32_t)(left >> (kMaxCodeLen - 31))), 63);
-        const unsigned long long some = __ballot(left != 0);
+        left = cnt ? left : 0u;
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(left), 63);
+        const unsigned long long some = __ballot(left != 0 || (cnt != 0 && lane > 24));
         if (lane == 0) {
             left_s[wv] = total;
-            from_s[wv] = some ? (uint32_t)__ffsll((long long)some) - 1u : 1u;
+            from_s[wv] = some ? (uint32_t)__ffsll((long long)some) - 1u : 0u;
         }
     }
     __syncthreads();
+    if (*bad_s) return *bad_s;
     if (*bad2_s) return *bad2_s;
 
     // The scale to take.  An index on x with m = 7 takes two instructions more than a linear one and one on x + 2^j three, of some
@@ -272,11 +269,11 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
     scale = uniform_u32(scale);
     const uint32_t m = 7u + scale, j = scale == 1u ? 24u : scale == 2u ? 28u : scale == 3u ? 30u : 32u;
     const uint32_t shift = 23u - m, least_f = (127u + (scale ? j : 32u - kPowers7)) << 23;
-    const uint64_t added = scale ? 1ull << j : 0ull;
+    const uint32_t added8 = scale ? 1u << (j - 8u) : 0u;
     if (tid == 0) {
         T.scale_min = least_f; T.scale_shift = shift;
-        T.offset = (float)added;
-        T.from = from_s[scale];
+        T.offset = scale ? __uint_as_float((127u + j) << 23) : 0.0f;
+        T.from = from_s[scale] ? from_s[scale] : 1u;
         T.searched = left_s[scale] < 0x7fffffffu ? 2u * left_s[scale] : 0xffffffffu;
     }
 
@@ -292,10 +289,12 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
 #pragma unroll
         for (uint32_t i = 0; i < kPer; ++i) {
             const uint32_t idx = tid + i * NT;
-            const uint32_t f = least_f + (idx << shift), power = (f >> 23) - 127u;                     // at most 33
-            const uint64_t end = (((uint64_t)((f & 0x7fffffu) | 0x800000u) << power) >> 23) + (1ull << (power - m)) - added;     // of its x
-            v[i] = 0u - (uint32_t)end;
-            longest[i] = end <= (1ull << 32) && (idx || added) ? 32u - (power - m) : 0u;
+            // x where the entry begins (with 2^j added) and ends, in units of 2^8, which no entry divides
+            const uint32_t f = least_f + (idx << shift), power = (f >> 23) - 127u;                 // at most 33
+            const uint32_t begin = (((f << 2) & 0x1ffffffu) | 0x2000000u) >> (33u - power);
+            const uint32_t end = begin + (1u << (power - m - 8u)) - added8;
+            v[i] = 0u - (end << 8);
+            longest[i] = end <= (1u << 24) && (idx || added8) ? 32u - (power - m) : 0u;
             l[i] = 0;                                            // lengths whose codes all lie below v (no more than 31 count)
         }
 #pragma unroll
@@ -313,8 +312,8 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
             T.entry[tid + i * NT] = (uint16_t)(l[i] <= longest[i] ? e : 0u);
         }
     }
-    // the ordered symbols in their packed form, for the codewords that the table leaves
-    {
+    // the ordered symbols in their packed form, if there are codewords that the table leaves
+    if (from_s[scale]) {                                         // uniform
         const uint32_t used = *used_s;
         for (uint32_t w = tid; w < (kMaxSym + 2) / 3; w += NT) {
             uint32_t v = 0;
