@@ -48,7 +48,6 @@ struct DecodeTables {
     uint32_t scale_shift;         // 23 - m
     float    offset;              // 2^j, or 0
     uint32_t from;                // shortest length that the table leaves to the search, for some of its codes
-    uint32_t searched;            // share of the code space that it leaves, in units of 2^-32
     uint32_t max_len;
     uint32_t payload_units;
     uint32_t n_outliers;
@@ -274,7 +273,6 @@ __device__ __forceinline__ uint32_t build_tables(DecodeTables &T, const Decompre
         T.scale_min = least_f; T.scale_shift = shift;
         T.offset = scale ? __uint_as_float((127u + j) << 23) : 0.0f;
         T.from = from_s[scale] ? from_s[scale] : 1u;
-        T.searched = left_s[scale] < 0x7fffffffu ? 2u * left_s[scale] : 0xffffffffu;
     }
 
     // symbols ordered by (length, symbol)

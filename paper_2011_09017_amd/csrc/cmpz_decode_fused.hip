@@ -32,7 +32,7 @@
 // sum their rows in LDS, and the rest is the same.
 // With sub-blocks of 64 or 128 codes the bands of two or four waves are decoded by
 // one wave (a band alone would fill 32 or 16 of its lanes), two barriers per band,
-// unless the codebook sends too many codes past the tables or a band does not fit the staging buffer.
+// unless a band does not fit the staging buffer.
 // Software pipeline: the bit counts of the next band are fetched during the
 // decode of the current one, and its payload during the column pass.
 #include "cmpz_decode_core.h"
@@ -102,19 +102,12 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     // or four waves (128) of the workgroup are decoded by one of them, a lane per sub-block, between
     // two barriers.  The chain of a lane's dependent steps bounds this, not their number: the loop has
     // a fixed count, so that it unrolls and the look-ahead word is not waited for in the step that
-    // fetches it.  64x256x56x56 at eb 1e-2: 236 -> 166 us at 128 codes, 147 -> 113 at 64 (pooled with
-    // the loop's count per lane: 226 and 135; a raised wave priority: 172 and 116); at eb 5e-3,
-    // with its longer codes, 261 -> 232 us at 128 (220 with the search in decode_lds as it is).
+    // fetches it.  Together / each band by its own wave, in us: 64x256x56x56 with 128 codes at eb 1e-2 149 / 242, at eb 1e-3 251 /
+    // 290, at eb 2e-4 with 90 % zeros, where the table leaves 0.019 of the code space to the search, 251 / 287; with 64 codes 102 / 142, 157 /
+    // 166, 166 / 180; 8x64x28x28 with 128 codes 23 / 41, 33 / 45, 42 / 49.  (While the table left ten times as much to the search, a rule
+    // kept codebooks apart by that share.)
     constexpr bool kPool = kND < kWave;
     constexpr int kPoolWaves = kWave / kND;               // bands decoded together
-    // But a step waits for the canonical search as soon as one of its lanes needs it, and a pooled wave
-    // has two or four times the lanes.  So a codebook pools only if a sub-block is expected to search
-    // less than 0.64 times (the code space that the tables leave open is the share of codes that land
-    // there).  Pooled / each band by its own wave, with 128 codes: share 0.0013 2048 planes of 55x55
-    // 60 / 69 us, 512 of 112x112 66 / 75; 0.0035 64x256x56x56 213 / 264; 0.0064 100 / 83 and 105 / 92;
-    // 0.022 182 / 126 and 224 / 150.  With 64 codes: 0.0064 67 / 59 and 63 / 65; 0.011 103 / 81 and 101 / 82;
-    // 0.022 116 / 90 and 121 / 95.
-    constexpr uint32_t kPoolSearched = (uint32_t)(0.64 / SUB * 4294967296.0);
     static_assert(2 * kND <= kStageWords, "the lane records live in the staging buffer");
     static_assert(kStageWords / 4 == 2 * kWave, "two units per lane");
 
@@ -195,9 +188,9 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
     // carry), .y = the carry
     uint2 *RC = reinterpret_cast<uint2 *>(S + kStagePad);
     const uint32_t payload_units = T.payload_units, n_outl = T.n_outliers;
-    // (uniform in the workgroup; nor where a band's share of the payload does not fit the staging buffer)
+    // (uniform in the workgroup; not where a band's share of the payload does not fit the staging buffer)
     const uint32_t band_n = pl.big ? pl.Rb * a.W : pl.G * a.HW;
-    const bool pool = kPool && (uint32_t)__builtin_amdgcn_readfirstlane((int)T.searched) < kPoolSearched &&
+    const bool pool = kPool &&
                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)T.payload_units) * 128u * band_n <= (uint64_t)a.numel * (kStageWords * 32u);
 
     const uint32_t W = a.W, H = a.H, HW = a.HW;
