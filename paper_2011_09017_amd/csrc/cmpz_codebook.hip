@@ -255,7 +255,7 @@ __global__ __launch_bounds__(kCbThreads) void k_codebook(BatchC b)
     //    until it leads to the root, at twice the distance each time.  The words are read and written
     //    whole, so a link is right whether the other has been replaced already or not: no barriers.
     {
-        const uint32_t root = 2 * n - 2;
+        const uint32_t root = n > 1 ? 2 * n - 2 : 0;             // (no tree: nobody has a way to go)
         volatile uint32_t *const links = link;
         const uint32_t leaf = tid, node = n + tid;
         const bool is_leaf = n > 1 && leaf < n, is_node = node < root && n > 1;

@@ -118,3 +118,28 @@ def test_heavy_symbols(gpu, orc):
     buf, size, rc = ctx.compress(torch.from_numpy(x).cuda(), EB)
     want, want_size = oracle(orc, x, 32, False)
     assert rc == 0 and size == want_size and np.array_equal(buf[:size].cpu().numpy(), want)
+
+
+# no used symbol at all (container version 2, nothing but zeros): the kernel has less to do than with two symbols.  Walking
+# links that are not there took 5 us of 25
+def test_no_used_symbol_costs_nothing(gpu, orc):
+    us = {}
+    for used in (0, 2):
+        x = np.zeros((1, 1, 64, 64), np.float32)
+        if used:
+            x[0, 0, 3, 4] = 0.5
+        t = torch.from_numpy(x).cuda()
+        ctx = gpu.Context(sub=32, max_numel=x.size, zero_blocks=1)
+        buf, size, rc = ctx.compress(t, EB)
+        want, want_size = oracle(orc, x, 32, 1)
+        assert rc == 0 and size == want_size and np.array_equal(buf[:size].cpu().numpy(), want)
+        us[used] = float("inf")
+        for _ in range(10):
+            t0, t1 = torch.cuda.Event(True), torch.cuda.Event(True)
+            t0.record()
+            for _ in range(30):
+                ctx.compress(t, EB, out=buf, sync=False)
+            t1.record()
+            torch.cuda.synchronize()
+            us[used] = min(us[used], t0.elapsed_time(t1) * 1e3 / 30)
+    assert us[0] < 1.05 * us[2], us
