@@ -102,8 +102,9 @@ void cmp_default_config(cmp_config *cfg);
 /* The framework of Section 4.4 compresses the activation of every convolutional layer in every
  * iteration: what the kernels need between their stages (Section 3.1: symbols between the two
  * sweeps, histograms, code tables) is allocated once, here, and reused by every call.
- * Creates a context on GPU `device` with its scratch (about 2 bytes * max_numel + 9 bytes per chunk
- * + 1.3 MB of device memory, owned by the context).  cfg == NULL means defaults.  Returns CMP_E_ARG
+ * Creates a context on GPU `device` with its scratch: 2.51 bytes * max_numel + 2 MB of device memory, owned
+ * by the context (2 bytes per symbol, and for every 4096 of them 2 KB of counts; 0.68 GB for the
+ * default max_numel: set it to the largest launch group in use).  cfg == NULL means defaults.  Returns CMP_E_ARG
  * for an unsupported configuration or device, CMP_E_HIP if the allocation fails (*out = NULL). */
 int cmp_create(cmp_ctx **out, const cmp_config *cfg, int device);
 /* Waits for the device and frees the context's scratch; containers and tensors are the caller's
@@ -143,7 +144,7 @@ int cmp_compress_batch(cmp_ctx *ctx, int n, const float *const *d_x, const int64
 /* cmp_compress for callers that cannot allocate device memory and therefore cannot hold a
  * context: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * It runs the same kernels as cmp_compress and gives the same container, with its scratch in an
- * array that is part of the library's device image: about 14.4 MB on every GPU the library is
+ * array that is part of the library's device image: about 13.9 MB on every GPU the library is
  * loaded on, held until the process ends.  The call allocates nothing (no hipMalloc, no
  * hipFree, no pinned memory) and does not synchronise.
  *   device   the GPU of d_x and d_out;

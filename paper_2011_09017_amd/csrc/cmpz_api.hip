@@ -21,8 +21,8 @@ using namespace cmpz;
 // Device memory of a context, carved out of one block (from hipMalloc in cmp_create).
 struct Scratch {
     // compression (see BatchC)
-    uint16_t   *sym, *chunk_hist, *chunk_hist_all;
-    uint32_t   *hist, *hist_copy, *enc32, *outl_cnt, *has_all, *wide, *chunk_bits, *range_units, *range_outl, *range_bits, *status;
+    uint16_t   *sym, *chunk_hist, *others_hist;
+    uint32_t   *hist, *hist_copy, *enc32, *outl_cnt, *has_others, *wide, *chunk_bits, *range_units, *range_outl, *range_bits, *status;
     uint8_t    *lens;
     uint64_t   *codes;
     TensorMeta *tmeta;
@@ -102,8 +102,8 @@ uint64_t carve_scratch(Scratch *sc, uint8_t *base, uint64_t max_numel, uint64_t 
     uint64_t off = 0;
     auto carve = [&](uint64_t bytes) { uint64_t o = off; off = align_up(off + bytes, 256); return base + o; };
     s.sym = reinterpret_cast<uint16_t *>(carve(2 * (s.max_chunks * kChunk + 16)));   // whole chunks: readable past numel
-    s.chunk_hist = reinterpret_cast<uint16_t *>(carve(2ull * 256 * s.max_chunks));
-    s.chunk_hist_all = reinterpret_cast<uint16_t *>(carve(2ull * kMaxSym * s.max_chunks));
+    s.chunk_hist = reinterpret_cast<uint16_t *>(carve(2ull * kByteSyms * s.max_chunks));
+    s.others_hist = reinterpret_cast<uint16_t *>(carve(2ull * kOtherSyms * s.max_chunks));
     if (zero_from) *zero_from = off;
     s.hist = reinterpret_cast<uint32_t *>(carve(4ull * kMaxSym * kHistCopies * kBatchMax));
     s.hist_copy = reinterpret_cast<uint32_t *>(carve(4ull * kMaxSym * kBatchMax));
@@ -111,7 +111,7 @@ uint64_t carve_scratch(Scratch *sc, uint8_t *base, uint64_t max_numel, uint64_t 
     s.codes = reinterpret_cast<uint64_t *>(carve(8ull * kMaxSym * kBatchMax));
     s.enc32 = reinterpret_cast<uint32_t *>(carve(4ull * kMaxSym * kBatchMax));
     s.outl_cnt = reinterpret_cast<uint32_t *>(carve(4 * s.max_chunks));
-    s.has_all = reinterpret_cast<uint32_t *>(carve(4 * s.max_chunks));
+    s.has_others = reinterpret_cast<uint32_t *>(carve(4 * s.max_chunks));
     s.wide = reinterpret_cast<uint32_t *>(carve(16 * s.max_chunks));
     s.chunk_bits = reinterpret_cast<uint32_t *>(carve(4 * s.max_chunks));
     s.range_units = reinterpret_cast<uint32_t *>(carve(4 * s.max_ranges));
@@ -255,7 +255,7 @@ void group_begin(BatchC *b, const cmp_config &cfg, const Scratch &s)
     std::memset(b, 0, sizeof(*b));
     b->radius = cfg.radius; b->sub = cfg.sub; b->guard_shift = cfg.guard_shift;
     b->zero_blocks = (cfg.flags & CMP_F_ZERO_BLOCKS) ? 1u : 0u;
-    b->sym = s.sym; b->chunk_hist = s.chunk_hist; b->chunk_hist_all = s.chunk_hist_all; b->has_all = s.has_all; b->hist = s.hist; b->hist_copy = s.hist_copy; b->lens = s.lens; b->codes = s.codes;
+    b->sym = s.sym; b->chunk_hist = s.chunk_hist; b->others_hist = s.others_hist; b->has_others = s.has_others; b->hist = s.hist; b->hist_copy = s.hist_copy; b->lens = s.lens; b->codes = s.codes;
     b->enc32 = s.enc32; b->outl_cnt = s.outl_cnt; b->wide = s.wide; b->chunk_bits = s.chunk_bits;
     b->sym_off = byte_form_base(cfg.radius);
     b->range_units = s.range_units; b->range_outl = s.range_outl; b->range_bits = s.range_bits;
@@ -416,7 +416,7 @@ int cmp_compress(cmp_ctx *ctx, const float *d_x, const int64_t shape[4], float e
 // own copy at its own address, looked up once (static_scratch_of) and kept.
 constexpr uint64_t kStaticMaxNumel = CMP_STATIC_MAX_NUMEL;
 constexpr uint64_t kStaticChunks   = kStaticMaxNumel / kChunk + kBatchMax + 1;
-constexpr uint64_t kStaticBytes    = 2 * kStaticChunks * (kChunk + 256 + kMaxSym) + (3ull << 20);
+constexpr uint64_t kStaticBytes    = 2 * kStaticChunks * (kChunk + kByteSyms + kOtherSyms) + (3ull << 20);
 static __device__ __align__(256) __attribute__((used)) unsigned char scratch[kStaticBytes];
 
 namespace {

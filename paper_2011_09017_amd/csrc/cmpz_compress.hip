@@ -126,10 +126,10 @@ __global__ __launch_bounds__(kThreads) void k_quant_lorenzo_split_hist(BatchC b,
     __syncthreads();
     // the counts so far to the chunk's rows
     const uint64_t g = (uint64_t)tc.chunk_base + (uint64_t)blockIdx.x * kTileChunks + ch;
-    for (int k = tid; k < (int)kMaxSym; k += kThreads) b.chunk_hist_all[g * kMaxSym + k] = (uint16_t)hist[k];
-    static_assert(kThreads == 256, "one symbol with a byte form per thread");
-    b.chunk_hist[g * 256 + tid] = (uint16_t)hist[b.sym_off + tid];
-    if (tid == 0) b.has_all[g] = 1;
+    for (uint32_t k = tid; k < kOtherSyms; k += kThreads) b.others_hist[g * kOtherSyms + k] = (uint16_t)hist[k < b.sym_off ? k : k + kByteSyms];
+    static_assert(kThreads == kByteSyms, "one symbol with a byte form per thread");
+    b.chunk_hist[g * kByteSyms + tid] = (uint16_t)hist[b.sym_off + tid];
+    if (tid == 0) b.has_others[g] = 1;
     __syncthreads();
     }
     for (int k = tid; k < (int)kMaxSym; k += kThreads) {

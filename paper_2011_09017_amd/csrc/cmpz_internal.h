@@ -26,11 +26,14 @@ constexpr uint32_t kHistCopies  = 8;        // global histogram replicas that wo
 // has taken so far, this one included (a run of at most kRunMax chunks, so that the counts fit).
 // With the code lengths, these counts less those of the chunk before give the chunk's bit count without a
 // second look at its symbols.  Those of the 256 symbols with a byte form have a row of their own; from the
-// first chunk of a run on that is not all bytes, there is a row of all symbols too.
+// first chunk of a run on that is not all bytes, there is a row of all other symbols too.
 constexpr uint32_t kRunMax      = 15;
 constexpr uint32_t kUntiledChunks = 4;      // run of the first sweep's kernel for wide rows
+static_assert(kRunMax * kChunk <= 0xffffu && kUntiledChunks <= kRunMax, "running counts of 16 bits, two to a word");
+constexpr uint32_t kByteSyms    = 256;
+constexpr uint32_t kOtherSyms   = kMaxSym - kByteSyms;
 // First symbol with a byte form: 128 below the zero residual, rounded down to a multiple of four entries of
-// a row (radii up to 128: all symbols have one).
+// a row (radii up to 128: all symbols have one).  The row of the others closes the gap that these leave.
 __host__ __device__ inline uint32_t byte_form_base(uint32_t radius) { return radius > 128u ? (radius - 128u) & ~3u : 0u; }
 
 // Container header, little-endian, 256 bytes; bytes 144..255 are zero.
@@ -205,11 +208,11 @@ struct BatchC {
     uint8_t    *lens;           // [slot][kMaxSym]
     uint64_t   *codes;          // [slot][kMaxSym]: len << 56 | code
     uint32_t   *enc32;          // [slot][kMaxSym]: the first 24 bits of the left-aligned code, length in the low 8; 0: unused
-    uint16_t   *chunk_hist;     // [global chunk][256]: counts of the symbols from sym_off on, see kRunMax.  What
+    uint16_t   *chunk_hist;     // [global chunk][kByteSyms]: counts of the symbols from sym_off on, see kRunMax.  What
                                 // stands for the zero residual holds only in container version 2, where it counts
                                 // those that are coded; elsewhere they are the elements that are no other symbol
-    uint16_t   *chunk_hist_all; // [global chunk][kMaxSym]: counts of all symbols
-    uint32_t   *has_all;        // [global chunk]: nonzero = the row in chunk_hist_all is there
+    uint16_t   *others_hist;    // [global chunk][kOtherSyms]: counts of the other symbols
+    uint32_t   *has_others;     // [global chunk]: nonzero = the row in others_hist is there
     uint32_t   *outl_cnt;       // [global chunk]: outliers
     uint32_t   *chunk_bits;     // [global chunk]: sum of codeword lengths
     uint32_t   *range_units;    // [chunk range]: payload units, later their exclusive prefix within the tensor

@@ -9,7 +9,7 @@ namespace cmpz {
 // Bit counts of chunks from the counts that the first sweep left behind each of them (see kRunMax).  A lane
 // holds four neighbouring symbols; lens4: the code lengths of all symbols, one byte each, in LDS.
 struct ChunkBits {
-    const uint2 *byte_rows, *all_rows;               // 64 and kMaxSym / 4 per chunk
+    const uint2 *byte_rows, *other_rows;             // kByteSyms / 4 and kOtherSyms / 4 per chunk
     const uint32_t *lens4;
     const BatchC &b;
     uint32_t byte_quad;                              // the first four symbols with a byte form
@@ -21,7 +21,7 @@ struct ChunkBits {
     bool have_before = false;                        // uniform
 
     __device__ __forceinline__ ChunkBits(const BatchC &batch, const uint32_t *lens, int ln)
-        : byte_rows(reinterpret_cast<const uint2 *>(batch.chunk_hist)), all_rows(reinterpret_cast<const uint2 *>(batch.chunk_hist_all)),
+        : byte_rows(reinterpret_cast<const uint2 *>(batch.chunk_hist)), other_rows(reinterpret_cast<const uint2 *>(batch.others_hist)),
           lens4(lens), b(batch), byte_quad(batch.sym_off / 4),
           zero_len(batch.zero_blocks ? 0 : (int32_t)reinterpret_cast<const uint8_t *>(lens)[batch.radius]), lane(ln)
     {
@@ -36,19 +36,19 @@ struct ChunkBits {
                (int32_t)(n.y & 0xffffu) * ((int32_t)((L >> 16) & 0xffu) - zero_len) + (int32_t)(n.y >> 16) * ((int32_t)(L >> 24) - zero_len);
     }
     // the symbols without a byte form, of the counts after chunk g (the lane's share)
-    static constexpr uint32_t kOthers = kMaxSym / 4 / kWave;
+    static constexpr uint32_t kOthers = kOtherSyms / 4 / kWave;
     __device__ __forceinline__ void fetch_others(uint32_t g, uint2 (&n)[kOthers]) const
     {
 #pragma unroll
-        for (uint32_t i = 0; i < kOthers; ++i) n[i] = all_rows[(uint64_t)g * (kMaxSym / 4) + i * kWave + lane];
+        for (uint32_t i = 0; i < kOthers; ++i) n[i] = other_rows[(uint64_t)g * (kOtherSyms / 4) + i * kWave + lane];
     }
     __device__ __forceinline__ int32_t others_bits(const uint2 (&n)[kOthers]) const
     {
         int32_t bits = 0;
 #pragma unroll
         for (uint32_t i = 0; i < kOthers; ++i) {
-            const uint32_t quad = i * kWave + lane;
-            if (quad - byte_quad >= (uint32_t)kWave) bits += quad_bits(n[i], quad);
+            const uint32_t at = i * kWave + lane;
+            bits += quad_bits(n[i], at < byte_quad ? at : at + kByteSyms / 4);
         }
         return bits;
     }
@@ -76,7 +76,7 @@ struct ChunkBits {
         if (wide) {
             const int32_t all = others_now();
             bits += all;
-            if (!first) bits -= have_before ? others_before : uniform_u32(b.has_all[g - 1]) ? others(g - 1) : 0;
+            if (!first) bits -= have_before ? others_before : uniform_u32(b.has_others[g - 1]) ? others(g - 1) : 0;
             others_before = all;
         }
         have_before = wide;

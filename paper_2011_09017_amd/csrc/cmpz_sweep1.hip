@@ -67,9 +67,9 @@ __global__ __launch_bounds__(kThreads, 8) void k_quant_lorenzo_split_hist_tiled(
         const uint64_t g = tc.chunk_base + c;
         const uint32_t quad = my_quad(), byte_quad = quad - b.sym_off / 4u;      // below 64: symbols with a byte form
         const uint2 pk = make_uint2(n.x | (n.y << 16), n.z | (n.w << 16));
-        if (byte_quad < 64u) reinterpret_cast<uint2 *>(b.chunk_hist + g * 256)[byte_quad] = pk;
-        if (wide) reinterpret_cast<uint2 *>(b.chunk_hist_all + g * kMaxSym)[quad] = pk;
-        if (quad == 0) { b.has_all[g] = wide; b.outl_cnt[g] = outl - outl_before; }
+        if (byte_quad < kByteSyms / 4) reinterpret_cast<uint2 *>(b.chunk_hist + g * kByteSyms)[byte_quad] = pk;
+        else if (wide) reinterpret_cast<uint2 *>(b.others_hist + g * kOtherSyms)[quad < b.sym_off / 4u ? quad : quad - kByteSyms / 4] = pk;
+        if (quad == 0) { b.has_others[g] = wide; b.outl_cnt[g] = outl - outl_before; }
         outl_before = outl;
     };
 

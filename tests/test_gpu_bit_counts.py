@@ -10,6 +10,13 @@ import torch
 pytestmark = pytest.mark.gpu
 
 EB = 1e-2
+# workgroups of the first sweep that are resident together: a call of up to four chunks each takes runs of that many
+
+
+def SWEEP_SLOTS():
+    return 8 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
 STEP = float(np.float32(2) * (np.float32(EB) - np.float32(np.ldexp(np.float32(EB), -7))))
 
 
@@ -63,17 +70,39 @@ def test_codes_longer_than_an_entry(gpu, orc, order, largest, sub, zero_blocks):
 @pytest.mark.parametrize("sub,zero_blocks", [(32, 0), (128, 1)])
 def test_running_counts(gpu, orc, sub, zero_blocks):
     rng = np.random.default_rng(5)
-    planes = 4300
+    planes = 2 * SWEEP_SLOTS() + 204                                 # of one chunk each
     q = np.zeros((1, planes, 64, 64), np.int64)
     kind = rng.integers(0, 4, planes)
     for amplitude, k in ((60, 1), (300, 2), (900, 3)):
         for p in np.nonzero(kind == k)[0]:
             at = rng.integers(0, 4096, 40)
             q[0, p].reshape(-1)[at] = rng.integers(1, amplitude + 1, 40)
-    assert planes > 2 * 2048
     x = q * STEP
     check(gpu, orc, x, sub, zero_blocks)
-    check(gpu, orc, x.reshape(-1)[:7500 * 37 * 61].reshape(1, 7500, 37, 61), sub, zero_blocks)
+    cut = planes * 4096 // (37 * 61)
+    check(gpu, orc, x.reshape(-1)[:cut * 37 * 61].reshape(1, cut, 37, 61), sub, zero_blocks)
+
+
+# one symbol that fills every element of runs of eight chunks: a count of 32768, with a byte form and without
+@pytest.mark.parametrize("residual", [1, -300])
+def test_running_counts_of_full_runs(gpu, orc, residual):
+    n = (8 * SWEEP_SLOTS() - 1) * 4096 + 5
+    x = np.full((1, n, 1, 1), residual * STEP, np.float32)           # planes of one element
+    x[0, ::5000] = 0
+    check(gpu, orc, x, 32, 0)
+
+
+# what include/cmpz.h promises for cmp_create, and two steps of the allocator
+def test_scratch_of_a_context(gpu):
+    n = 1 << 28
+    first = gpu.Context(max_numel=4096)                              # what the runtime sets up on its first use
+    first.compress(torch.zeros((1, 1, 64, 64), device="cuda"), EB)
+    before = torch.cuda.mem_get_info()[0]
+    ctx = gpu.Context(max_numel=n)
+    used = before - torch.cuda.mem_get_info()[0]
+    ctx.close()
+    first.close()
+    assert 2 * n < used < 2.51 * n + 2e6 + 2 * (2 << 20)
 
 
 # rows too wide for the first sweep's tile: its other kernel, runs of four chunks
