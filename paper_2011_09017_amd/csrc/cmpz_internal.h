@@ -118,10 +118,12 @@ enum MetaWord : int {
 // consecutively too (tensor t owns pack_base .. ).
 constexpr int      kBatchMax   = 24;        // tensors per launch group (kernel arguments hold their descriptors)
 // Most chunks of a tensor whose offsets and header the codebook kernel finds, rather than two kernels that spread
-// this over the chip.  In us, two kernels / the codebook kernel: one tensor of 49 chunks, there and back, 79.2 /
-// 76.7; a batch of up to 131 chunks 42.7 / 41.2; the saved activations of ResNet-18 at batch 16 with the tensors up to
-// 128 chunks this way 1104 / 1098, to 256 / 1101, to 512 / 1123; a tensor of 580 chunks at a tight bound 270 / 324.
-constexpr uint32_t kSmallChunks = 256;
+// this over the chip.  The line lies where a loose bound gains twice what a tight one, with a second row of counts for every
+// chunk, loses; with many tensors in a call both gain.
+// Compression in us, two kernels / the codebook kernel, at eb 1e-2; 1e-3; 6e-4: one tensor of 48 chunks 33.9 / 30.6; 50.2 / 47.5;
+// 56.5 / 53.4, of 96 34.3 / 32.3; 49.5 / 49.4; 56.5 / 56.1, of 112 34.3 / 32.6; 50.1 / 50.4; 56.6 / 56.8, of 128 34.2 / 33.3; 50.4 / 51.1; 56.4 /
+// 57.4, of 255 35.1 / 36.8; 51.1 / 56.8; 57.2 / 63.1; seventeen tensors of 112 57.1 / 51.0; 76.7 / 72.2; 85.3 / 80.7.
+constexpr uint32_t kSmallChunks = 128;
 constexpr uint32_t kPackChunks = 28;        // chunks per workgroup of the bit-count and packing kernels: at most,
 constexpr uint32_t kPackChunksMin = 4;      // and at least (one per wave); always a multiple of that
 

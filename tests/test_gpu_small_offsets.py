@@ -1,5 +1,5 @@
 """GPU parity where the kernel that builds the code also finds a tensor's offsets and header (tensors of at
-most 256 chunks), and the device-side stack's bookkeeping by the kernels that write and read the containers.
+most 128 chunks), and the device-side stack's bookkeeping by the kernels that write and read the containers.
 
 Bar: the container equals the CPU oracle's byte for byte.
 """
@@ -39,7 +39,8 @@ def oracle(orc, x, sub, zero_blocks):
 
 # one element; both sides of a chunk, of a wave's four chunks, of the limit
 @pytest.mark.parametrize("sub,zero_blocks", [(32, 0), (128, 1)])
-@pytest.mark.parametrize("n", [1, 4096, 4097, 16 * 4096, 16 * 4096 + 1, 65 * 4096 + 5, 256 * 4096 - 1, 256 * 4096, 256 * 4096 + 1])
+@pytest.mark.parametrize("n", [1, 4096, 4097, 16 * 4096, 16 * 4096 + 1, 65 * 4096 + 5, 128 * 4096 - 1, 128 * 4096, 128 * 4096 + 1,
+                               256 * 4096 - 1, 256 * 4096, 256 * 4096 + 1])
 def test_sizes(gpu, orc, n, sub, zero_blocks):
     x = tensor((1, 1, 1, n) if n < 200 else (1, n, 1, 1) if n % 16 else (n // 16, 1, 4, 4), n)
     ctx = gpu.Context(sub=sub, max_numel=n, zero_blocks=zero_blocks)
