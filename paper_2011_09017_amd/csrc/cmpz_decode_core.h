@@ -496,12 +496,10 @@ __device__ __forceinline__ uint32_t decode_lds(const DecodeTables &T, const uint
         uint32_t e = *reinterpret_cast<const uint16_t *>(table + sc.place<SCALE>(hi));
         if (__builtin_expect(e == 0, 0)) {
             {
-                // canonical search over the lengths that the table does not resolve.  Up to 31 bits the
+                // Canonical search over the lengths that the table does not resolve.  Up to 31 bits the
                 // length is the first one whose limit is not below the window; the next length's limit is
-                // fetched beside the present one's.  Latency of LDS accesses bounds this: four limits per
-                // look, and the way to the symbol behind them, took longer where the first length or two
-                // hit: 64x256x56x56 at eb 5e-3 and 128 codes per sub-block 227 -> 213 us, 16x112x112 at
-                // eb 1e-3 and 32 codes 61.9 -> 59.3 (one length per look: 219 and 60.2).
+                // fetched beside the present one's.  (search() in place of this, where it is hardly ever reached,
+                // makes the whole loop slower: 64x256x56x56 at eb 5e-3 with 128 codes 145 -> 160 us, a plane of 399x225 221 -> 245.)
                 uint32_t len = 0, sy = 0;                     // no match: residual 0
                 const uint32_t max_len = T.max_len;
                 uint32_t L = T.from;

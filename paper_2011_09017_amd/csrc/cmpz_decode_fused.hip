@@ -84,7 +84,7 @@ struct Stage {
 };
 
 // One launch decodes all tensors of a call: a workgroup belongs to one tensor (it validates that
-// container and builds that codebook's decode tables for itself, about a microsecond), its waves
+// container and builds that codebook's decode tables for itself, see build_tables), its waves
 // take every item_stride-th item of the tensor.
 // COOP: 1 the variant for few large planes (plan value big == 2), 2 the same for rows wider than
 // kColGroups waves (big == 3), each a launch of its own.

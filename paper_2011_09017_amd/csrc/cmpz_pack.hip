@@ -264,10 +264,10 @@ __global__ __launch_bounds__(kThreads, 5) void k_pack(BatchC b)
         uint32_t ubase = 0;                          // units of the chunk stored so far: image unit 0 is stream unit ubase
 
         // Bits from each lane into offsets in the image.  The scan's first steps leave in a lane the sum over
-        // the 2, 4 and 8 lanes that end in it (of its row of 16): the last lane of a sub-block, if `mine`,
+        // the 2, 4 and 8 lanes that end in it (of its row of 16): the last lane of a sub-block
         // stores the sub-block's bit count from there.
-        auto offsets = [&](uint32_t bits, uint32_t i0, bool mine) -> uint32_t {
-            const bool ends = mine && ((uint32_t)lane & (GROUP - 1)) == GROUP - 1;
+        auto offsets = [&](uint32_t bits, uint32_t i0) -> uint32_t {
+            const bool ends = ((uint32_t)lane & (GROUP - 1)) == GROUP - 1;
             uint16_t *at = sub_bits + (i0 - e0) / (16u * GROUP);
             uint32_t inc = bits + dpp_u32<0x111, 0xf>(bits);                           // row_shr:1
             if (GROUP == 2 && ends) *at = (uint16_t)inc;
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_pack(BatchC b)
                 bits += len;
                 longest = len > longest ? len : longest;
             }
-            uint32_t pos = offsets(bits, i0, true);
+            uint32_t pos = offsets(bits, i0);
             if (long_codes) {
                 uint32_t most = 0;
                 _Pragma("unroll") for (int k = 0; k < n; ++k) most = e[k] > most ? e[k] : most;
