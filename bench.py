@@ -61,18 +61,18 @@ MEASURED_TRAFFIC = {
     ("cfg5_resnet18_stream", 32, 1e-2): {
         "profile": "profiles/hbm_traffic_cfg5_resnet18_stream.txt",
         "per_elem": {
-            "k_quant_lorenzo_split_hist": 4.0178 + 1.1825,     # 8-bit symbols in the scratch
-            "k_lengths": 0.1413 + 0.0020,
-            "k_pack": 1.0110 + 0.7400,
-            "k_decode_fused": 0.8306 + 4.0090,
+            "k_quant_lorenzo_split_hist": 4.0188 + 1.1821,     # 8-bit symbols in the scratch
+            "k_lengths": 0.1411 + 0.0020,
+            "k_pack": 1.0111 + 0.7406,
+            "k_decode_fused": 0.8356 + 4.0096,
         },
         # vector instructions per element and the fraction of the kernel's time its vector units are busy
         # (profiles/instruction_counters_cfg5_resnet18_stream.txt)
         "valu": {
-            "k_quant_lorenzo_split_hist": (27.47, 0.704),
-            "k_lengths": (0.57, 0.269),
-            "k_pack": (12.01, 0.732),
-            "k_decode_fused": (43.57, 0.828),
+            "k_quant_lorenzo_split_hist": (27.50, 0.695),
+            "k_lengths": (0.57, 0.283),
+            "k_pack": (11.41, 0.709),
+            "k_decode_fused": (43.52, 0.831),
         },
     },
 }
