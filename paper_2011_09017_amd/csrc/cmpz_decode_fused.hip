@@ -703,16 +703,16 @@ __global__ __launch_bounds__(kThreads, 5) void k_decode_fused(BatchD b)
 // Wide planes are always shared by the waves of a workgroup, which walk down the plane: with few
 // planes, or the longer chains of longer sub-blocks, the passes over memory of the unfused kernels,
 // which spread a plane over the chip, are faster.  How many planes it takes depends on the bound: with
-// outliers in every band the walk takes twice as long, and the host does not know of them.  So
+// outliers in every band the walk takes half as long again, and the host does not know of them.  So
 // the lines lie where a tight bound loses nothing.  Fused / unfused in us at eb 1e-2; 1e-3:
 //   planes of one or two rounds of bands, where the unfused kernels' five launches weigh more: 20x512, one
-//     plane: 23 / 37; 33 / 38, 64: 24 / 40; 36 / 44, 192: 24 / 46; 37 / 50; 40x300, one: 25 / 37; 36 / 40
-//   three rounds: 31x512, 64 planes: 31 / 41; 48 / 46; 60x300, 64: 34 / 43; 50 / 48, 128: 35 / 49; 51 / 54
-//   four: 95x300, 128: 45 / 58; 67 / 63, 192: 45 / 64; 67 / 68
-//   more: 190x300, 256: 80 / 108; 125 / 116; 375x500, 192: 179 / 217; 339 / 234, 288: 193 / 313; 362 / 345, 320:
-//     208 / 365; 377 / 413, 512: 227 / 643; 395 / 720; 64x384, 320: 44 / 66; 66 / 71
-//   tensors larger than the memory-side cache (256 MB): 2000x512, 256: 1309 / 1668; 2218 / 1985, 320:
-//     1416 / 2081; 2330 / 2472; 1500x300, 320: 973 / 1108 at eb 1e-3
+//     plane: 20 / 33; 28 / 34, 64: 21 / 36; 29 / 38, 192: 22 / 42; 30 / 44; 40x300, one: 22 / 33; 30 / 34
+//   three rounds: 31x512, 64 planes: 28 / 38; 40 / 39; 60x300, 64: 31 / 40; 43 / 41, 128: 31 / 46; 43 / 48
+//   four: 95x300, 128: 42 / 55; 58 / 56, 192: 42 / 60; 58 / 62
+//   more: 190x300, 256: 76 / 103; 111 / 107; 375x500, 192: 178 / 210; 290 / 217, 288: 190 / 304; 312 / 327, 320:
+//     203 / 369; 330 / 394, 512: 222 / 632; 344 / 694; 64x384, 320: 41 / 62; 58 / 64
+//   tensors larger than the memory-side cache (256 MB): 2000x512, 256: 1276 / 1659; 2044 / 1934, 320:
+//     1380 / 2075; 2155 / 2400; 1500x300, 320: 606 / 976; 898 / 1079
 static bool enough_wide_planes(uint32_t planes, uint32_t nbands)
 {
     return nbands <= 2u * kWaves || planes >= (nbands <= 4u * kWaves ? 192u : 320u);
@@ -764,16 +764,16 @@ void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st
         // waves without a band in the plane's last round and for columns that do not fill four
         // waves: with two or three bands a plane the most.  Shared up to the count of planes from which
         // a wave each is no slower at either of two bounds.  In us, shared / a wave each (eb 1e-2; eb 1e-3):
-        //   2 bands (56x56), 32 codes: 1280 planes 26 / 26; 48 / 59, 1536: 27 / 26; 62 / 59; 128 codes,
-        //     1280: 41 / 51; 85 / 125, 1536: 50 / 51; 134 / 123
-        //   3 bands (64x64), 32 codes: 1792: 32 / 33; 69 / 71, 2048: 36 / 33; 72 / 72; 128 codes,
-        //     2560: 71 / 78; 147 / 160, 3072: 77 / 78; 172 / 161
-        //   4 bands (80x80), 32 codes: 3584: 58 / 56; 125 / 128, 4096: 67 / 56; 138 / 128; 128 codes,
-        //     4608: 112 / 110; 248 / 273, 5056: 128 / 111; 297 / 271
-        //   7 bands (112x112), 32 codes: 3584: 88 / 82; 206 / 217, 4096: 102 / 83; 236 / 218; 128 codes,
-        //     3584: 160 / 168; 426 / 457, 4096: 174 / 169; 514 / 464
-        //   25 bands (224x224), 32 codes: 3584: 284 / 311; 669 / 757, 4096: 322 / 320; 770 / 774; 28 bands,
-        //     128 codes, 4608: 634 / 668; 1450 / 1667, 5056: 707 / 673; 1624 / 1665
+        //   2 bands (56x56), 32 codes: 1280 planes 25 / 23; 31 / 31, 1536: 26 / 22; 33 / 31; 128 codes,
+        //     1280: 36 / 44; 56 / 76, 1536: 45 / 45; 80 / 74
+        //   3 bands (64x64), 32 codes: 1792: 29 / 29; 38 / 43, 2048: 31 / 30; 41 / 43; 128 codes,
+        //     2560: 61 / 68; 92 / 109, 3072: 68 / 69; 102 / 110
+        //   4 bands (80x80), 32 codes: 3584: 51 / 52; 68 / 73, 4096: 59 / 51; 78 / 73; 128 codes,
+        //     4608: 98 / 101; 146 / 165, 5056: 111 / 101; 174 / 165
+        //   7 bands (112x112), 32 codes: 3584: 77 / 76; 108 / 112, 4096: 90 / 76; 129 / 115; 128 codes,
+        //     3584: 141 / 153; 256 / 294, 4096: 157 / 155; 301 / 294
+        //   25 bands (224x224), 32 codes: 3584: 261 / 293; 388 / 438, 4096: 297 / 303; 444 / 453; 28 bands,
+        //     128 codes, 4608: 579 / 632; 860 / 1004, 5056: 632 / 640; 965 / 1005
         // (of 5120 waves; between them 5 and 9 bands would do with fewer planes, 3072 and 3584)
         if (!t.nitems || !t.big || t.big == 3) continue;
         const uint32_t nbands = (t.shape[2] + t.Rb - 1) / t.Rb;
