@@ -786,8 +786,8 @@ void launch_decode_fused(BatchD &b, uint32_t cus, Profiler *prof, hipStream_t st
     // into that launch then, rather than into one of their own that it would add to.  Counted in rounds
     // of bands: at most a quarter of the walk's time on all slots taken without them, and one and a half
     // times that time with them.  In us, together / apart: 16 planes of 224x224 (7 rounds) beside 2048 of
-    // 56x56 (1) 64 / 90, with 128 codes at eb 1e-3 389 / 555; beside 3 x 4096 of them 137 / 144 and 584 / 813; 256 of
-    // 112x112 (2) beside 2048 of 56x56 42 / 55, but 512 of them 71 / 59; 64 of 56x56 beside 4096 72 / 50.
+    // 56x56 (1) 55 / 77, with 128 codes at eb 1e-3 207 / 294; beside 3 x 4096 of them 120 / 124 and 371 / 451; 256 of
+    // 112x112 (2) beside 2048 of 56x56 38 / 48, 512 of them, which this leaves apart, 45 / 50; 64 of 56x56 beside 4096 62 / 45.
     uint64_t walk = 0, load = 0, between = 0;
     auto undecided = [&](const TensorD &t) { return t.nitems && t.big == 1u && t.shape[2] > t.Rb && t.nitems < waves; };
     for (uint32_t k = 0; k < b.n; ++k) {
